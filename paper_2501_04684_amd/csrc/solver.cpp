@@ -3,8 +3,9 @@
 // nrhs independent right-hand sides whose products share each launch.
 //
 // The whole Krylov state lives in the caller's device workspace; the host
-// only enqueues steps and reads a small status block (one pinned copy per
-// step), so steps can be queued back to back without waiting.
+// only enqueues steps and reads a small status block in pinned memory that
+// each step's last kernel writes, so steps can be queued back to back
+// without waiting.
 #include <hip/hip_runtime_api.h>
 
 #include <cmath>
@@ -29,10 +30,13 @@ struct ubf_gmres {
   float2* V = nullptr;  // (m+1) blocks of [R][n]
   float2* W = nullptr;  // [R][n]
   double2* partial = nullptr;
+  double2* partial2 = nullptr;
   ubf::GmresState st{};
-  ubf::GmresStatusRow* d_status = nullptr;
+  int32_t* active[2] = {nullptr, nullptr};  // flags; active[cur] are the current ones
+  int cur = 0;
   // host
-  ubf::GmresStatusRow* h_status = nullptr;  // pinned
+  ubf::GmresStatusRow* h_status = nullptr;  // pinned, written by the kernels
+  ubf::GmresStatusRow* d_status = nullptr;  // its device address
   hipEvent_t ev = nullptr;
   const float2* b = nullptr;
   float2* x = nullptr;
@@ -50,8 +54,8 @@ namespace {
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
 struct GmresLayout {
-  size_t V, W, partial, H, h1, h2, nrm, cs, sn, g, y, scale, bnorm, res, active, k, iters,
-      status, total;
+  size_t V, W, partial, partial2, H, h1, h2, nrm, cs, sn, g, y, scale, bnorm, res, active0,
+      active1, k, iters, total;
 };
 
 GmresLayout gmres_layout(int64_t n, int R, int m) {
@@ -66,6 +70,7 @@ GmresLayout gmres_layout(int64_t n, int R, int m) {
   L.V = take((size_t)(m + 1) * vec);
   L.W = take(vec);
   L.partial = take((size_t)ubf::kDotBlocks * R * (ubf::kMaxRestart + 1) * sizeof(double2));
+  L.partial2 = take((size_t)ubf::kDotBlocks * R * (ubf::kMaxRestart + 1) * sizeof(double2));
   L.H = take((size_t)R * m * (m + 1) * sizeof(double2));
   L.h1 = take((size_t)R * (m + 1) * sizeof(double2));
   L.h2 = take((size_t)R * (m + 1) * sizeof(double2));
@@ -77,10 +82,10 @@ GmresLayout gmres_layout(int64_t n, int R, int m) {
   L.scale = take((size_t)R * sizeof(double));
   L.bnorm = take((size_t)R * sizeof(double));
   L.res = take((size_t)R * sizeof(double));
-  L.active = take((size_t)R * sizeof(int32_t));
+  L.active0 = take((size_t)R * sizeof(int32_t));
+  L.active1 = take((size_t)R * sizeof(int32_t));
   L.k = take((size_t)R * sizeof(int32_t));
   L.iters = take((size_t)R * sizeof(int32_t));
-  L.status = take((size_t)R * sizeof(ubf::GmresStatusRow));
   L.total = at;
   return L;
 }
@@ -93,39 +98,28 @@ float2* col(const ubf_gmres* s, int c) { return s->V + (int64_t)c * s->R * s->n;
     if (e_) return hip_fail(e_, what);       \
   } while (0)
 
-// Norm of `v` ([R][n]) into st.nrm (sum |v|^2 in the real part).
-int norm_into(ubf_gmres* s, const float2* v, hipStream_t q) {
-  UBF_TRY(ubf::launch_gmres_dots(v, 0, 1, v, s->n, s->R, s->partial, s->st.nrm, 1, q),
-          "norm");
-  return UBF_OK;
-}
-
-// New cycle from the residual already in V_0 (unnormalised).
+// New cycle from the residual already in V_0 (unnormalised), whose norm
+// partials the kernel before has left.
 int start_cycle(ubf_gmres* s, int first, hipStream_t q) {
-  int e = norm_into(s, col(s, 0), q);
-  if (e) return e;
-  UBF_TRY(ubf::launch_gmres_cycle_start(s->st, s->R, first, s->tol, q), "cycle start");
-  UBF_TRY(ubf::launch_gmres_scale(col(s, 0), col(s, 0), s->st.scale, s->n, s->R, q),
-          "scale");
+  UBF_TRY(ubf::launch_gmres_cycle_start(s->st, first, s->tol, col(s, 0), s->n, s->R, s->partial,
+                                        s->active[s->cur], s->active[s->cur ^ 1], s->d_status, q),
+          "cycle start");
+  s->cur ^= 1;
   s->j = 0;
   return UBF_OK;
 }
 
 // x += V y over the columns of the current cycle.
 int close_cycle(ubf_gmres* s, hipStream_t q) {
-  UBF_TRY(ubf::launch_gmres_backsolve(s->st, s->R, q), "backsolve");
   UBF_TRY(ubf::launch_gmres_combine(s->V, (int64_t)s->R * s->n, s->st, s->x, s->n, s->R, q),
           "combine");
   return UBF_OK;
 }
 
+// The kernels write the status rows into pinned host memory; the event
+// tells when the last ones are there.
 int publish(ubf_gmres* s, hipStream_t q) {
-  UBF_TRY(ubf::launch_gmres_status(s->st, s->R, s->d_status, q), "status");
-  hipError_t e = hipMemcpyAsync(s->h_status, s->d_status,
-                                (size_t)s->R * sizeof(ubf::GmresStatusRow),
-                                hipMemcpyDeviceToHost, q);
-  if (e != hipSuccess) return hip_fail(e, "hipMemcpyAsync (status)");
-  e = hipEventRecord(s->ev, q);
+  hipError_t e = hipEventRecord(s->ev, q);
   if (e != hipSuccess) return hip_fail(e, "hipEventRecord (status)");
   s->recorded = true;
   return UBF_OK;
@@ -188,6 +182,7 @@ int ubf_gmres_create(ubf_plan* plan, int32_t nrhs, int32_t restart, double sigma
   s->V = (float2*)(ws + L.V);
   s->W = (float2*)(ws + L.W);
   s->partial = (double2*)(ws + L.partial);
+  s->partial2 = (double2*)(ws + L.partial2);
   ubf::GmresState& st = s->st;
   st.m = restart;
   st.H = (double2*)(ws + L.H);
@@ -201,18 +196,23 @@ int ubf_gmres_create(ubf_plan* plan, int32_t nrhs, int32_t restart, double sigma
   st.scale = (double*)(ws + L.scale);
   st.bnorm = (double*)(ws + L.bnorm);
   st.res = (double*)(ws + L.res);
-  st.active = (int32_t*)(ws + L.active);
+  s->active[0] = (int32_t*)(ws + L.active0);
+  s->active[1] = (int32_t*)(ws + L.active1);
   st.k = (int32_t*)(ws + L.k);
   st.iters = (int32_t*)(ws + L.iters);
-  s->d_status = (ubf::GmresStatusRow*)(ws + L.status);
   hipError_t e = hipHostMalloc((void**)&s->h_status, (size_t)nrhs * sizeof(ubf::GmresStatusRow),
-                               hipHostMallocDefault);
+                               hipHostMallocMapped | hipHostMallocCoherent);
   if (e != hipSuccess) {
     s->h_status = nullptr;
     delete s;
     return hip_fail(e, "hipHostMalloc (status)");
   }
   std::memset(s->h_status, 0, (size_t)nrhs * sizeof(ubf::GmresStatusRow));
+  e = hipHostGetDevicePointer((void**)&s->d_status, s->h_status, 0);
+  if (e != hipSuccess) {
+    delete s;
+    return hip_fail(e, "hipHostGetDevicePointer (status)");
+  }
   e = hipEventCreateWithFlags(&s->ev, hipEventDisableTiming);
   if (e != hipSuccess) {
     s->ev = nullptr;
@@ -238,9 +238,7 @@ int ubf_gmres_start(ubf_gmres* s, const void* d_b, void* d_x, void* hip_stream) 
   s->restarts = 0;
   s->finished = false;
   // x_0 = 0, so r_0 = b
-  UBF_TRY(ubf::launch_gmres_zero(s->x, (int64_t)s->R * s->n, q), "zero x");
-  hipError_t he = hipMemcpyAsync(col(s, 0), s->b, vec, hipMemcpyDeviceToDevice, q);
-  if (he != hipSuccess) return hip_fail(he, "hipMemcpyAsync (start)");
+  UBF_TRY(ubf::launch_gmres_begin(s->b, s->x, col(s, 0), s->n, s->R, s->partial, q), "begin");
   e = start_cycle(s, 1, q);
   if (e) return e;
   e = publish(s, q);
@@ -254,23 +252,17 @@ int ubf_gmres_step(ubf_gmres* s, void* hip_stream) {
   if (e) return e;
   if (!s->started || s->finished) return fail(UBF_ESTATE, "solver not started or finished");
   hipStream_t q = (hipStream_t)hip_stream;
-  const int R = s->R, j = s->j, ld = s->m + 1;
+  const int R = s->R, j = s->j;
   const int64_t n = s->n, vs = (int64_t)R * n;
   // w = (sigma I + Z^F) v_j
   e = ubf::enqueue_mvm(s->plan->p, col(s, j), s->W, R, q, s->plan->next_events());
   if (e) return e;
-  UBF_TRY(ubf::launch_gmres_add_shift(s->W, col(s, j), s->sr, s->si, vs, q), "shift");
-  // two classical Gram-Schmidt passes against v_0..v_j
-  UBF_TRY(ubf::launch_gmres_dots(s->V, vs, j + 1, s->W, n, R, s->partial, s->st.h1, ld, q),
-          "dots");
-  UBF_TRY(ubf::launch_gmres_update(s->V, vs, j + 1, s->st.h1, ld, s->W, n, R, q), "update");
-  UBF_TRY(ubf::launch_gmres_dots(s->V, vs, j + 1, s->W, n, R, s->partial, s->st.h2, ld, q),
-          "dots");
-  UBF_TRY(ubf::launch_gmres_update(s->V, vs, j + 1, s->st.h2, ld, s->W, n, R, q), "update");
-  e = norm_into(s, s->W, q);
-  if (e) return e;
-  UBF_TRY(ubf::launch_gmres_tail(s->st, R, j, s->tol, q), "arnoldi");
-  UBF_TRY(ubf::launch_gmres_scale(col(s, j + 1), s->W, s->st.scale, n, R, q), "scale");
+  // the shift, two classical Gram-Schmidt passes against v_0..v_j, v_{j+1}
+  UBF_TRY(ubf::launch_gmres_step(s->st, s->V, vs, j, s->W, col(s, j + 1), s->sr, s->si, s->tol,
+                                 n, R, s->partial, s->partial2, s->active[s->cur],
+                                 s->active[s->cur ^ 1], s->d_status, q),
+          "arnoldi");
+  s->cur ^= 1;
   s->j = j + 1;
   s->steps += 1;
   if (s->j == s->m) {  // restart: x += V y, r = b - A x
@@ -278,7 +270,8 @@ int ubf_gmres_step(ubf_gmres* s, void* hip_stream) {
     if (e) return e;
     e = ubf::enqueue_mvm(s->plan->p, s->x, s->W, R, q, s->plan->next_events());
     if (e) return e;
-    UBF_TRY(ubf::launch_gmres_residual(col(s, 0), s->b, s->x, s->W, s->sr, s->si, vs, q),
+    UBF_TRY(ubf::launch_gmres_residual(col(s, 0), s->b, s->x, s->W, s->sr, s->si, n, R,
+                                       s->partial, q),
             "residual");
     e = start_cycle(s, 0, q);
     if (e) return e;
@@ -344,9 +337,9 @@ int ubf_gmres_norm_estimate(ubf_gmres* s, int32_t iters, uint64_t seed, void* hi
   float2* u = col(s, 1);
   s->started = false;     // the Krylov blocks are overwritten
   UBF_TRY(ubf::launch_gmres_rand(v, n, seed, q), "rand");
-  UBF_TRY(ubf::launch_gmres_dots(v, 0, 1, v, n, 1, s->partial, s->st.nrm, 1, q), "norm");
+  UBF_TRY(ubf::launch_gmres_dot(v, v, n, s->partial, s->st.nrm, q), "norm");
   UBF_TRY(ubf::launch_gmres_inv_norm(s->st.nrm, s->st.scale, q), "inv norm");
-  UBF_TRY(ubf::launch_gmres_scale(v, v, s->st.scale, n, 1, q), "scale");
+  UBF_TRY(ubf::launch_gmres_scale(v, v, s->st.scale, n, q), "scale");
   for (int it = 0; it < iters; ++it) {
     // u = conj(Z conj(Z v)) = Z^H Z v  (Z complex symmetric)
     e = ubf::enqueue_mvm(s->plan->p, v, s->W, 1, q, nullptr);
@@ -356,10 +349,10 @@ int ubf_gmres_norm_estimate(ubf_gmres* s, int32_t iters, uint64_t seed, void* hi
     if (e) return e;
     UBF_TRY(ubf::launch_gmres_conj(u, s->W, n, q), "conj");
     // Rayleigh quotient v^H u (||v|| = 1), then v = u / ||u||
-    UBF_TRY(ubf::launch_gmres_dots(v, 0, 1, u, n, 1, s->partial, s->st.h1, 1, q), "dots");
-    UBF_TRY(ubf::launch_gmres_dots(u, 0, 1, u, n, 1, s->partial, s->st.nrm, 1, q), "norm");
+    UBF_TRY(ubf::launch_gmres_dot(v, u, n, s->partial, s->st.h1, q), "dots");
+    UBF_TRY(ubf::launch_gmres_dot(u, u, n, s->partial, s->st.nrm, q), "norm");
     UBF_TRY(ubf::launch_gmres_inv_norm(s->st.nrm, s->st.scale, q), "inv norm");
-    UBF_TRY(ubf::launch_gmres_scale(v, u, s->st.scale, n, 1, q), "scale");
+    UBF_TRY(ubf::launch_gmres_scale(v, u, s->st.scale, n, q), "scale");
   }
   double2 rq;
   hipError_t he = hipMemcpyAsync(&rq, s->st.h1, sizeof(rq), hipMemcpyDeviceToHost, q);

@@ -252,3 +252,41 @@ def test_norm_estimate_rejects_explicit_T():
     assert e.value.status == -1 and "explicit T" in str(e.value)
     sol.close()
     ff.close()
+
+
+@pytest.mark.parametrize("shape, n_d, restart, steps", [
+    ((4, 4, 4), 2, 9, 12),       # one slice (1,536 elements); a ninth column, a restart
+    ((5, 5, 4), 2, 17, 18),      # 2,400 elements: two slices; three column tiles
+    ((29, 28, 28), 2, 3, 4),     # 545,664 elements: more than 256 slices of 2,048
+])
+def test_history_over_slices_and_column_tiles(shape, n_d, restart, steps):
+    """The residual estimates of every step against the FP64 oracle at the
+    edges of the solver's slices (2,048 elements of a vector) and column
+    tiles (8), with a shift of five times the norm: a Krylov process that
+    FP32 vectors perturb by their own rounding only (1e-7 of ||b||)."""
+    boxes = W.grid_boxes(*shape)
+    announce("gmres slices", shape, "restart", restart)
+    ff = U.FarField(boxes, A_SIDE, K, n_d, max_nrhs=2)
+    sigma = 5.0 * _shift(boxes, n_d)
+    b = W.complex_normal((2, ff.nb_total), 31)
+    tol = 1e-14                  # never reached: a fixed number of steps
+    solver = U.Solver(ff, sigma, nrhs=2, restart=restart, tol=tol, max_steps=steps)
+    bd = to_dev(b)
+    xd = torch.empty_like(bd)
+    solver.start(bd, xd)
+    hist = [solver.poll(wait=True)["rel_res"].copy()]
+    for _ in range(steps):
+        solver.step()
+        hist.append(solver.poll(wait=True)["rel_res"].copy())
+    solver.finish()
+    x = to_host(xd)
+
+    def A(u):
+        return sigma * u + O.far_mvm(u[None], boxes, A_SIDE, K, n_d)[0]
+    r = 1
+    _, h_o = G.gmres(A, b[r].astype(np.complex128), restart, tol, steps)
+    hist = np.array(hist)
+    for s in range(steps + 1):
+        assert abs(hist[s, r] - h_o[s]) <= 1e-3 * h_o[s] + 1e-7, (s, hist[s, r], h_o[s])
+    true = np.linalg.norm(b[r] - A(x[r].astype(np.complex128))) / np.linalg.norm(b[r])
+    assert true <= hist[-1, r] + 1e-6
