@@ -24,6 +24,12 @@
  * keeps only pairs whose parent boxes floor(c/2) are Chebyshev-adjacent
  * (the one-box-buffer interaction list of a two-level tree; its 316
  * distinct offsets are the translation vectors counted in Sec. 2.2).
+ * The FULL product of a scatterer with many pairs runs as a convolution
+ * over the lattice of its sites (FP32 FFTs) plus the pairs exactly two boxes
+ * apart, except in the single FP16 form: its rounding errors are relative to
+ * the scatterer's whole field, and a non-finite coefficient makes the whole
+ * scatterer's result non-finite. Which way is taken depends on the
+ * scatterer's boxes, n_d and precision alone.
  *
  * Operators: G_w[(l,alpha),(s,beta)] = D(a*w + r_l - r_s)[alpha][beta],
  * D the free-space dyadic Green's function of Eq. (5)-(6) with time
@@ -130,7 +136,8 @@ typedef struct ubf_info {
   int32_t n_u;              /* uniform-basis coefficients per box, 3*n_d^3 */
   int32_t n_d;
   int64_t n_chunks;         /* translation work units (per RHS) */
-  int64_t table_bytes;      /* device operator table */
+  int64_t table_bytes;      /* device operator table (with a convolution: that of
+                               the pairs left) */
   double translate_flops;   /* real flops per RHS: 8 * n_u^2 * n_pairs */
   int32_t mfma;             /* 1 if stage 2 runs on the matrix cores */
   int32_t precision;        /* enum ubf_precision of the plan */

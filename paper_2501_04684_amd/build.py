@@ -20,7 +20,7 @@ ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
 ARCH = "gfx950"
 
 HOST_SOURCES = ["plan.cpp", "capi.cpp", "solver.cpp"]
-HIP_SOURCES = ["kernels.hip", "gmres.hip", "networks.hip", "noalloc.hip"]
+HIP_SOURCES = ["kernels.hip", "gmres.hip", "networks.hip", "fft.hip", "noalloc.hip"]
 
 HOST_FLAGS = ["-O2", "-fPIC", "-std=c++17", "-pthread", "-Wall", "-Wextra",
               "-Wno-unused-parameter", "-D__HIP_PLATFORM_AMD__",
@@ -29,6 +29,10 @@ HOST_FLAGS = ["-O2", "-fPIC", "-std=c++17", "-pthread", "-Wall", "-Wextra",
 HIP_FLAGS = ["-O3", "-fPIC", "-std=c++17", f"--offload-arch={ARCH}",
              "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
              "-ffp-contract=fast", f"-I{os.path.join(ROOT, 'include')}"]
+
+
+# Per file. fft.hip: sums with the zero padding (constant zeros) fold away.
+HIP_EXTRA = {"fft.hip": ["-fno-signed-zeros", "-ffinite-math-only"]}
 
 
 def _run(cmd):
@@ -63,7 +67,7 @@ def build(verbose: bool = True, sanitize: bool = False) -> str:
     for src in HIP_SOURCES:
         obj = os.path.join(BUILD, src + ".o")
         if not (sanitize and os.path.exists(obj)):
-            _run([hipcc, *HIP_FLAGS, "-c", os.path.join(CSRC, src), "-o", obj])
+            _run([hipcc, *HIP_FLAGS, *HIP_EXTRA.get(src, []), "-c", os.path.join(CSRC, src), "-o", obj])
         objs.append(obj)
     lib = SANITIZE_LIB if sanitize else LIB
     tmp = lib + ".tmp"

@@ -11,6 +11,7 @@
 #include <vector>
 
 #include "capi_internal.hpp"
+#include "fft.hpp"
 #include "kernels.hpp"
 #include "networks.hpp"
 
@@ -37,14 +38,29 @@ int hip_fail(int err, const char* what) {
 
 const std::string& last_error_text() { return g_last_error; }
 
-// Stage 2 by the plan's networks when it has them, else by the operator
-// table (the staged kernel for box sizes too wide for the register kernels).
-int launch_stage2(const Plan& p, const float* P, float* part, int nrhs, hipStream_t s,
-                  const StageEvents* ev) {
-  if (p.hidden > 0) return launch_translate_cvfcnn(p, P, part, nrhs, s, ev);
+// Stage 2 by the plan's networks when it has them, else by the convolution
+// of a FULL far set and the operators of the pairs it leaves, else by the
+// operators of every pair (the staged kernel for box sizes too wide for the
+// register kernels).
+int launch_operators(const Plan& p, const float* P, float* part, int nrhs, hipStream_t s,
+                     const StageEvents* ev) {
   if (staged_translate_supported(p)) return launch_translate_staged(p, P, part, nrhs, s, ev);
   return launch_translate(p, P, part, nrhs, s, ev);
 }
+int launch_stage2(const Plan& p, const float* P, float* part, int nrhs, hipStream_t s,
+                  const StageEvents* ev) {
+  if (p.hidden > 0) return launch_translate_cvfcnn(p, P, part, nrhs, s, ev);
+  if (!p.rest) return launch_operators(p, P, part, nrhs, s, ev);
+  const bool pairs = p.rest->n_chunks() > 0;
+  int e = launch_fft(p, P, part, nrhs, s, ev ? ev->start : nullptr,
+                     ev && !pairs ? ev->stop : nullptr);
+  if (e || !pairs) return e;
+  const StageEvents end{nullptr, ev ? ev->stop : nullptr};
+  return launch_operators(*p.rest, P, part, nrhs, s, ev ? &end : nullptr);
+}
+
+// The plan whose rows stage 2 writes.
+const Plan& rows_plan(const Plan& p) { return p.hidden > 0 ? p : p.pairs_plan(); }
 
 int enqueue_mvm(const Plan& p, const void* d_x, void* d_y, int32_t nrhs, hipStream_t s,
                 hipEvent_t* ev) {
@@ -55,7 +71,7 @@ int enqueue_mvm(const Plan& p, const void* d_x, void* d_y, int32_t nrhs, hipStre
   if (e) return hip_fail(e, "aggregate launch");
   e = launch_stage2(p, p.d_P, p.d_part, nrhs, s, ev ? &st[1] : nullptr);
   if (e) return hip_fail(e, "translate launch");
-  e = launch_disaggregate(p, true, p.d_part, nullptr, d_y, nrhs, s, false,
+  e = launch_disaggregate(p, &rows_plan(p), p.d_part, nullptr, d_y, nrhs, s, false,
                           ev ? &st[2] : nullptr);
   if (e) return hip_fail(e, "disaggregate launch");
   return ok();
@@ -289,46 +305,79 @@ int ubf_plan_bind(ubf_plan* plan, void* d_workspace, size_t bytes,
   } else {
     for (int64_t i = 0; i <= p.n_box; ++i) nb[i] = i * p.nu;
   }
-  const Copy copies[] = {
-      {L.table, p.split() ? (const void*)p.table_bf16.data() : (const void*)p.table.data(),
-       p.table_bytes()},
-      {L.chunks, p.chunks.data(), p.chunks.size() * sizeof(int32_t)},
-      {L.items, p.items.data(), p.items.size() * sizeof(int32_t)},
-      {L.wg_ptr, p.wg_ptr.data(), p.wg_ptr.size() * sizeof(int32_t)},
-      {L.rounds, p.rounds.data(), p.rounds.size() * sizeof(int32_t)},
-      {L.wg_round_ptr, p.wg_round_ptr.data(), p.wg_round_ptr.size() * sizeof(int32_t)},
-      {L.pair_src, p.pair_src.data(), p.pair_src.size() * sizeof(int32_t)},
-      {L.pair_dst, p.pair_dst.data(), p.pair_dst.size() * sizeof(int32_t)},
-      {L.test_ptr, p.test_ptr.data(), p.test_ptr.size() * sizeof(int32_t)},
-      {L.nb_ptr, nb.data(), nb.size() * sizeof(int64_t)},
-      {L.off_scale, p.off_scale.data(), p.off_scale.size() * sizeof(float)},
-      {L.offsets, p.offsets.data(), p.offsets.size() * sizeof(int32_t)},
+  std::vector<Copy> copies;
+  std::vector<int32_t> offsets4[2];  // alive until the copies have ended
+  auto copy_pairs = [&](const ubf::Plan& q, const ubf::Layout::Pairs& a,
+                        std::vector<int32_t>& off) {
+    for (int32_t o = 0; o < q.n_off(); ++o)
+      off.insert(off.end(), {q.offsets[3 * o], q.offsets[3 * o + 1], q.offsets[3 * o + 2],
+                             q.masked(o) ? 1 : 0});
+    auto ints = [&](size_t at, const std::vector<int32_t>& v) {
+      copies.push_back({at, v.data(), v.size() * sizeof(int32_t)});
+    };
+    copies.push_back({a.table,
+                      q.split() ? (const void*)q.table_bf16.data() : (const void*)q.table.data(),
+                      q.table_bytes()});
+    ints(a.chunks, q.chunks);
+    ints(a.items, q.items);
+    ints(a.wg_ptr, q.wg_ptr);
+    ints(a.rounds, q.rounds);
+    ints(a.wg_round_ptr, q.wg_round_ptr);
+    ints(a.pair_src, q.pair_src);
+    ints(a.pair_dst, q.pair_dst);
+    ints(a.test_ptr, q.test_ptr);
+    copies.push_back({a.off_scale, q.off_scale.data(), q.off_scale.size() * sizeof(float)});
+    ints(a.offsets, off);
   };
+  if (ubf::holds_own_pairs(p)) copy_pairs(p, L.own, offsets4[0]);
+  if (p.rest) {
+    copy_pairs(*p.rest, L.rest, offsets4[1]);
+    copies.push_back({L.fft_tw, p.fft_twiddles.data(), p.fft_twiddles.size() * sizeof(float)});
+    copies.push_back({L.fft_map, p.fft_map.data(), p.fft_map.size() * sizeof(int32_t)});
+  }
+  copies.push_back({L.nb_ptr, nb.data(), nb.size() * sizeof(int64_t)});
+  hipError_t e = hipSuccess;
   for (const Copy& c : copies) {
     if (c.n == 0) continue;
-    hipError_t e = hipMemcpyAsync(ws + c.at, c.src, c.n, hipMemcpyHostToDevice, s);
-    if (e != hipSuccess) return hip_fail(e, "hipMemcpyAsync (bind)");
+    e = hipMemcpyAsync(ws + c.at, c.src, c.n, hipMemcpyHostToDevice, s);
+    if (e != hipSuccess) break;
   }
-  hipError_t e = hipStreamSynchronize(s);
-  if (e != hipSuccess) return hip_fail(e, "hipStreamSynchronize (bind)");
+  // the copies read host memory that ends with this call
+  const hipError_t es = hipStreamSynchronize(s);
+  if (e != hipSuccess) return hip_fail(e, "hipMemcpyAsync (bind)");
+  if (es != hipSuccess) return hip_fail(es, "hipStreamSynchronize (bind)");
   p.ws = ws;
   p.ws_bytes = bytes;
   p.max_nrhs = max_nrhs;
-  p.d_table = (float*)(ws + L.table);
-  p.d_chunks = (int32_t*)(ws + L.chunks);
-  p.d_items = (int32_t*)(ws + L.items);
-  p.d_wg_ptr = (int32_t*)(ws + L.wg_ptr);
-  p.d_rounds = (int32_t*)(ws + L.rounds);
-  p.d_wg_round_ptr = (int32_t*)(ws + L.wg_round_ptr);
-  p.d_pair_src = (int32_t*)(ws + L.pair_src);
-  p.d_test_ptr = (int32_t*)(ws + L.test_ptr);
-  p.d_pair_dst = (int32_t*)(ws + L.pair_dst);
   p.d_nb_ptr = (int64_t*)(ws + L.nb_ptr);
   p.d_P = (float*)(ws + L.P);
   p.d_part = (float*)(ws + L.part);
-  p.d_off_scale = (float*)(ws + L.off_scale);
   p.d_box_scale = (float*)(ws + L.box_scale);
-  p.d_offsets = (int32_t*)(ws + L.offsets);
+  auto point = [ws](ubf::Plan& q, const ubf::Layout::Pairs& a) {
+    q.d_table = (float*)(ws + a.table);
+    q.d_chunks = (int32_t*)(ws + a.chunks);
+    q.d_items = (int32_t*)(ws + a.items);
+    q.d_wg_ptr = (int32_t*)(ws + a.wg_ptr);
+    q.d_rounds = (int32_t*)(ws + a.rounds);
+    q.d_wg_round_ptr = (int32_t*)(ws + a.wg_round_ptr);
+    q.d_pair_src = (int32_t*)(ws + a.pair_src);
+    q.d_pair_dst = (int32_t*)(ws + a.pair_dst);
+    q.d_test_ptr = (int32_t*)(ws + a.test_ptr);
+    q.d_off_scale = (float*)(ws + a.off_scale);
+    q.d_offsets = (int32_t*)(ws + a.offsets);
+  };
+  if (ubf::holds_own_pairs(p)) point(p, L.own);
+  if (!p.rest) return ok();
+  point(*p.rest, L.rest);
+  p.rest->max_nrhs = max_nrhs;
+  p.rest->d_box_scale = p.d_box_scale;
+  p.d_fft = (float*)(ws + L.fft);
+  p.d_fft_spec = (float*)(ws + L.fft_spec);
+  p.d_fft_tw = (float*)(ws + L.fft_tw);
+  p.d_fft_map = (int32_t*)(ws + L.fft_map);
+  int le = ubf::launch_fft_spectra(p, s);
+  if (!le) le = (int)hipStreamSynchronize(s);
+  if (le) return hip_fail(le, "spectra (bind)");
   return ok();
 }
 
@@ -436,7 +485,7 @@ int ubf_plan_schedule(ubf_plan* plan, int32_t kernel, int32_t groups, void* hip_
     return fail(UBF_EINVAL, "this plan's stage 2 (networks, or 192 coefficients per box) runs "
                             "one workgroup per item and has no schedule to choose");
   plan->drop_graph();
-  const int e = apply_schedule(p, kernel, groups, (hipStream_t)hip_stream);
+  const int e = apply_schedule(p.pairs_plan(), kernel, groups, (hipStream_t)hip_stream);
   if (e) return hip_fail(e, "upload (schedule)");
   return ok();
 }
@@ -449,13 +498,16 @@ int ubf_plan_tune(ubf_plan* plan, int32_t nrhs, int32_t reps, void* hip_stream,
   if (nrhs < 1 || nrhs > p.max_nrhs)
     return fail(UBF_EINVAL, "nrhs must be in 1..max_nrhs of the binding");
   if (reps < 1 || reps > 1000) return fail(UBF_EINVAL, "reps must be in 1..1000");
-  if (p.hidden > 0 || ubf::staged_translate_supported(p)) {
-    // stage 2 runs one workgroup per 32 pairs here: nothing to choose
-    if (groups_out) *groups_out = (int32_t)p.n_groups();
+  if (p.hidden > 0 || ubf::staged_translate_supported(p) || p.pairs_plan().n_chunks() == 0) {
+    // stage 2 runs one workgroup per 32 pairs here, or has no pairs for the
+    // translation kernels: nothing to choose
+    if (groups_out) *groups_out = (int32_t)p.pairs_plan().n_groups();
     return ok();
   }
   plan->drop_graph();
   hipStream_t s = (hipStream_t)hip_stream;
+  // beside a convolution the schedule is that of the pairs left
+  ubf::Plan& q = p.pairs_plan();
   const std::string key = tune_key(p, nrhs);
   const char* cache = std::getenv("UBF_TUNE_CACHE");
   int kernel = -1, groups = 0;
@@ -465,9 +517,9 @@ int ubf_plan_tune(ubf_plan* plan, int32_t nrhs, int32_t reps, void* hip_stream,
                           (!p.gen_ops && (k == ubf::kSplitRounds || k == ubf::kSplitRoundsDouble))));
   };
   if (cache && *cache && cache_lookup(cache, key, &kernel, &groups) && usable(kernel)) {
-    const int e = apply_schedule(p, kernel, groups, s);
+    const int e = apply_schedule(q, kernel, groups, s);
     if (e) return hip_fail(e, "upload (tune cache)");
-    if (groups_out) *groups_out = current_groups(p);
+    if (groups_out) *groups_out = current_groups(q);
     return ok();
   }
   const ubf::Layout L = ubf::workspace_layout(p, p.max_nrhs);
@@ -480,43 +532,43 @@ int ubf_plan_tune(ubf_plan* plan, int32_t nrhs, int32_t reps, void* hip_stream,
     (void)hipEventDestroy(t0);
     return hip_fail(e, "hipEventCreate");
   }
-  const int before_kernel = p.split_kernel;
-  const int before_groups = current_groups(p);
+  const int before_kernel = q.split_kernel;
+  const int before_groups = current_groups(q);
   int best_kernel = before_kernel, best_groups = before_groups;
   float best_ms = 0.f;
   int status = UBF_OK;
   std::string why, report;
-  for (const Candidate& c : tune_candidates(p, nrhs)) {
-    int le = apply_schedule(p, c.kernel, c.groups, s);
+  for (const Candidate& c : tune_candidates(q, nrhs)) {
+    int le = apply_schedule(q, c.kernel, c.groups, s);
     if (le) { status = hip_fail(le, "upload (tune)"); break; }
-    le = ubf::launch_translate(p, p.d_P, p.d_part, nrhs, s);  // warm-up
+    le = ubf::launch_translate(q, p.d_P, p.d_part, nrhs, s);  // warm-up
     if (!le && hipEventRecord(t0, s) != hipSuccess) le = (int)hipGetLastError();
-    for (int r = 0; r < reps && !le; ++r) le = ubf::launch_translate(p, p.d_P, p.d_part, nrhs, s);
+    for (int r = 0; r < reps && !le; ++r) le = ubf::launch_translate(q, p.d_P, p.d_part, nrhs, s);
     if (!le && hipEventRecord(t1, s) != hipSuccess) le = (int)hipGetLastError();
     if (!le) le = (int)hipEventSynchronize(t1);
     float ms = 0.f;
     if (!le) le = (int)hipEventElapsedTime(&ms, t0, t1);
     if (le) { status = hip_fail(le, "translate (tune)"); break; }
     ms /= (float)reps;
-    report += " " + std::to_string(c.kernel) + ":" + std::to_string(current_groups(p)) + ":" +
+    report += " " + std::to_string(c.kernel) + ":" + std::to_string(current_groups(q)) + ":" +
               std::to_string(ms * 1e3f);
     if (best_ms == 0.f || ms < best_ms) {
       best_ms = ms;
       best_kernel = c.kernel;
-      best_groups = current_groups(p);
+      best_groups = current_groups(q);
     }
   }
   (void)hipEventDestroy(t0);
   (void)hipEventDestroy(t1);
   if (status != UBF_OK) {
     why = ubf::last_error_text();
-    (void)apply_schedule(p, before_kernel, before_groups, s);
+    (void)apply_schedule(q, before_kernel, before_groups, s);
     return fail(status, why);
   }
-  if ((e = (hipError_t)apply_schedule(p, best_kernel, best_groups, s)) != hipSuccess)
+  if ((e = (hipError_t)apply_schedule(q, best_kernel, best_groups, s)) != hipSuccess)
     return hip_fail(e, "upload (tune)");
   if (cache && *cache) cache_store(cache, key, best_kernel, best_groups, best_ms, report);
-  if (groups_out) *groups_out = current_groups(p);
+  if (groups_out) *groups_out = current_groups(q);
   return ok();
 }
 
@@ -597,7 +649,7 @@ int ubf_translate(ubf_plan* plan, const void* d_P, void* d_E, int32_t nrhs,
   if (e) return hip_fail(e, "pack launch");
   e = ubf::launch_stage2(p, p.d_P, p.d_part, nrhs, (hipStream_t)hip_stream, nullptr);
   if (e) return hip_fail(e, "translate launch");
-  e = ubf::launch_disaggregate(p, true, p.d_part, nullptr, d_E, nrhs, hip_stream,
+  e = ubf::launch_disaggregate(p, &ubf::rows_plan(p), p.d_part, nullptr, d_E, nrhs, hip_stream,
                                /*identity=*/true);
   if (e) return hip_fail(e, "reduce launch");
   return ok();
@@ -610,7 +662,7 @@ int ubf_disaggregate(ubf_plan* plan, const void* d_E, void* d_y, int32_t nrhs,
                       plan ? basis_vec_bytes(plan->p, nrhs) : 0);
   if (st != UBF_OK) return st;
   const ubf::Plan& p = plan->p;
-  int e = ubf::launch_disaggregate(p, false, nullptr, d_E, d_y, nrhs, hip_stream);
+  int e = ubf::launch_disaggregate(p, nullptr, nullptr, d_E, d_y, nrhs, hip_stream);
   if (e) return hip_fail(e, "disaggregate launch");
   return ok();
 }
@@ -665,14 +717,14 @@ int ubf_plan_info(const ubf_plan* plan, ubf_info* out) {
   out->n_u = p.nu;
   out->n_d = p.n_d;
   out->n_chunks = p.n_chunks();
-  out->table_bytes = (int64_t)p.table_bytes();
+  out->table_bytes = (int64_t)p.pairs_plan().table_bytes();
   out->translate_flops = 8.0 * p.nu * (double)p.nu * (double)p.n_pairs();
   out->mfma = (ubf::translate_uses_mfma(p) || ubf::staged_translate_supported(p)) ? 1 : 0;
   out->precision = p.precision;
   out->n_scatterers = p.n_scat();
   out->n_items = p.n_items();
-  out->translate_kernel = p.split_kernel;
-  out->translate_groups = current_groups(p);
+  out->translate_kernel = p.pairs_plan().split_kernel;
+  out->translate_groups = current_groups(p.pairs_plan());
   out->operators = p.gen_ops ? UBF_OPERATORS_GENERATED : UBF_OPERATORS_TABLE;
   return ok();
 }

@@ -619,7 +619,7 @@ __device__ inline void transpose_tile(unsigned waddr, unsigned raddr, floatx4 w0
 // read from a table: the integer offsets of the plan and the problem's box
 // side, wavenumber and impedance.
 struct GenArgs {
-  const int32_t* offsets;  // 3 per offset
+  const int32_t* offsets;  // 4 per offset: x, y, z, masked
   double a, k;
   float inv_k;  // 1 / k
   float psi0;   // k eta / (4 pi): |psi| R
@@ -691,13 +691,21 @@ __device__ void generate_operator(const GenArgs& ga, int o, unsigned short* img,
   constexpr int KHB = (NU + 7) & ~7, PLANE = NU * KHB;
   static_assert(NDIFF <= kBlock, "one lattice difference per thread");
   const int t = threadIdx.x;
-  const int wx = ga.offsets[3 * o], wy = ga.offsets[3 * o + 1], wz = ga.offsets[3 * o + 2];
+  const int4 w = reinterpret_cast<const int4*>(ga.offsets)[o];
+  const int wx = w.x, wy = w.y, wz = w.z;
   float vmax = 0.f;
   if (t < NDIFF) {
     const int dx = t / (SPAN * SPAN), dy = (t / SPAN) % SPAN, dz = t % SPAN;
     const double step = ga.a / ND;
-    vmax = dyadic_green(ga.a * wx + step * (dx - (ND - 1)), ga.a * wy + step * (dy - (ND - 1)),
+    // a masked operator keeps the differences below 2 n_d on every axis
+    if (w.w && max(abs(ND * wx + dx - (ND - 1)), max(abs(ND * wy + dy - (ND - 1)),
+                                                   abs(ND * wz + dz - (ND - 1)))) >= 2 * ND) {
+#pragma unroll
+      for (int e = 0; e < 9; ++e) blk[9 * t + e] = make_float2(0.f, 0.f);
+    } else {
+      vmax = dyadic_green(ga.a * wx + step * (dx - (ND - 1)), ga.a * wy + step * (dy - (ND - 1)),
                         ga.a * wz + step * (dz - (ND - 1)), ga, blk + 9 * t);
+    }
   }
   if (F16) {
 #pragma unroll
@@ -1757,9 +1765,12 @@ int launch_translate(const Plan& p, const float* P, float* part, int nrhs,
   return (int)hipGetLastError();
 }
 
-int launch_disaggregate(const Plan& p, bool from_parts, const float* part,
+int launch_disaggregate(const Plan& p, const Plan* rows, const float* part,
                         const void* E, void* y, int nrhs, void* stream,
                         bool identity, const StageEvents* ev) {
+  const bool from_parts = rows != nullptr;
+  const int32_t* test_ptr = rows ? rows->d_test_ptr : nullptr;
+  const int64_t n_rows = rows ? rows->n_pairs() : 0;
   const int mode = (identity || !p.has_basis) ? 0 : (p.d_T ? 2 : 1);
   const int64_t nb_total = mode == 0 ? p.n_box * (int64_t)p.nu : p.nb_total();
   const dim3 grid((unsigned)p.n_box, nrhs);
@@ -1767,13 +1778,13 @@ int launch_disaggregate(const Plan& p, bool from_parts, const float* part,
   const bool small = p.nu <= 84;  // at most 21 rows of E_j per lane
 #define UBF_DISAGG(PARTS, EQ)                                                     \
   UBF_LAUNCH(ev, (disaggregate_kernel<PARTS, EQ>), grid, dim3(kBlock), s, part,        \
-             p.d_test_ptr, p.n_pairs(), (const float2*)E, p.d_nb_ptr,                 \
+             test_ptr, n_rows, (const float2*)E, p.d_nb_ptr,                 \
              (const float2*)p.d_S, (const float2*)p.d_T, mode, (float2*)y, p.n_box,    \
              nb_total, p.nu, p.kh)
   // One wavefront per box while a box has up to a few hundred partial rows
   // on average (interaction lists: tens); with thousands per box (FULL far
   // sets) the row sums want a whole workgroup per box.
-  const bool few_rows = p.n_pairs() <= 256 * p.n_box;
+  const bool few_rows = n_rows <= 256 * p.n_box;
   // When the boxes fill about two rounds of the chip (up to 16 resident
   // wavefronts per CU), one wavefront per workgroup lets the dispatcher
   // spread them evenly (with four per workgroup a quarter of the CUs of the
@@ -1789,7 +1800,7 @@ int launch_disaggregate(const Plan& p, bool from_parts, const float* part,
   const dim3 wgrid((unsigned)((p.n_box + wpg - 1) / wpg), (unsigned)nrb), wblock(64 * wpg);
 #define UBF_WAVE(IDENT, RB)                                                                \
   UBF_LAUNCH(ev, (disaggregate_wave_kernel<21, IDENT, RB>), wgrid, wblock, s, part,        \
-             p.d_test_ptr, p.n_pairs(), p.d_nb_ptr, (const float2*)p.d_S, (float2*)y,     \
+             test_ptr, n_rows, p.d_nb_ptr, (const float2*)p.d_S, (float2*)y,     \
              p.n_box, nb_total, p.nu, p.kh, nrhs)
   if (from_parts && mode == 1 && small && few_rows) {
     if (rb == 1) UBF_WAVE(false, 1); else if (rb == 2) UBF_WAVE(false, 2); else UBF_WAVE(false, 4);

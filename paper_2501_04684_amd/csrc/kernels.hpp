@@ -36,9 +36,10 @@ int launch_translate(const Plan& p, const float* P, float* part, int nrhs,
                      void* stream, const StageEvents* ev = nullptr);
 
 // Stage 3: y_j = T_j E_j, where E_j is either the sum of the test box's
-// partial products (from_parts) or read from a complex vector `E`.
+// partial rows (`rows`: the plan whose rows they are) or, with `rows` NULL,
+// read from a complex vector `E`.
 // `identity` forces y_j = E_j whatever basis the plan holds.
-int launch_disaggregate(const Plan& p, bool from_parts, const float* part,
+int launch_disaggregate(const Plan& p, const Plan* rows, const float* part,
                         const void* E, void* y, int nrhs, void* stream,
                         bool identity = false, const StageEvents* ev = nullptr);
 

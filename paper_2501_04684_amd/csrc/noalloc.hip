@@ -11,6 +11,7 @@
 // that device current, and is kept per device.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <mutex>
 #include <string>
 
@@ -60,8 +61,11 @@ int ubf_far_mvm_noalloc(ubf_plan* plan, const void* d_x, void* d_y, int32_t nrhs
   if (st != UBF_OK) return st;
   ubf::Plan& p = plan->p;
   const ubf::ScratchLayout L = ubf::scratch_layout(p, nrhs);
-  if (L.total > kScratchBytes)
-    return ubf::fail(UBF_EINVAL, "this product needs " + std::to_string(L.total) +
+  // the limit is that of the rows of every far pair, whatever stage 2 does
+  // with them, so that which products are taken depends on the far set alone
+  const size_t need = std::max(L.total, L.direct);
+  if (need > kScratchBytes)
+    return ubf::fail(UBF_EINVAL, "this product needs " + std::to_string(need) +
                                      " bytes of static scratch; the limit is " +
                                      std::to_string(kScratchBytes) + " bytes (" +
                                      std::to_string(kScratchBytes >> 20) + " MiB)");
@@ -79,16 +83,27 @@ int ubf_far_mvm_noalloc(ubf_plan* plan, const void* d_x, void* d_y, int32_t nrhs
   float* const keep_P = p.d_P;
   float* const keep_part = p.d_part;
   float* const keep_box_scale = p.d_box_scale;
+  float* const keep_fft = p.d_fft;
   const int32_t keep_max_nrhs = p.max_nrhs;
   p.d_P = reinterpret_cast<float*>(b + L.P);
   p.d_part = reinterpret_cast<float*>(b + L.part);
   p.d_box_scale = reinterpret_cast<float*>(b + L.box_scale);
   p.max_nrhs = nrhs;
+  if (p.rest) {
+    p.d_fft = reinterpret_cast<float*>(b + L.fft);
+    p.rest->d_box_scale = p.d_box_scale;
+    p.rest->max_nrhs = nrhs;
+  }
   st = ubf::enqueue_mvm(p, d_x, d_y, nrhs, (hipStream_t)hip_stream, plan->next_events());
   p.d_P = keep_P;
   p.d_part = keep_part;
   p.d_box_scale = keep_box_scale;
   p.max_nrhs = keep_max_nrhs;
+  if (p.rest) {
+    p.d_fft = keep_fft;
+    p.rest->d_box_scale = keep_box_scale;
+    p.rest->max_nrhs = keep_max_nrhs;
+  }
   return st;
 }
 

@@ -91,6 +91,22 @@ int32_t cheb(int64_t x, int64_t y, int64_t z) {
 
 int64_t floordiv2(int64_t c) { return c >= 0 ? c / 2 : -((-c + 1) / 2); }
 
+// The site pairs of an operator that a convolution leaves (FftGrid): those
+// whose lattice difference n_d w + m_l - m_s stays below 2 n_d on every axis.
+void mask_operator(const int32_t* w, int n_d, std::vector<std::complex<double>>& G) {
+  const int nd3 = n_d * n_d * n_d, nu = 3 * nd3;
+  auto axis = [n_d](int s, int d) { return d == 0 ? s / (n_d * n_d) : d == 1 ? (s / n_d) % n_d : s % n_d; };
+  for (int l = 0; l < nd3; ++l)
+    for (int s = 0; s < nd3; ++s) {
+      bool keep = true;
+      for (int d = 0; d < 3; ++d)
+        keep = keep && std::abs(n_d * w[d] + axis(l, d) - axis(s, d)) < 2 * n_d;
+      if (keep) continue;
+      for (int al = 0; al < 3; ++al)
+        for (int be = 0; be < 3; ++be) G[(size_t)(3 * l + al) * nu + 3 * s + be] = 0.0;
+    }
+}
+
 // One offset's operator image in the table layout. FP32: planes re, im of
 // nu rows of kh floats. Split: G is rounded to FP32 first (as in the FP32
 // path), then hi = bf16(G), lo = bf16(G - hi); planes re.hi, im.hi, re.lo,
@@ -131,9 +147,10 @@ void staged_split_image(const Plan& P, const std::vector<std::complex<double>>& 
           }
 }
 
-void offset_image(const Plan& P, const int32_t* w, std::vector<std::complex<double>>& G,
-                  char* dst, float* scale) {
+void offset_image(const Plan& P, const int32_t* w, bool masked,
+                  std::vector<std::complex<double>>& G, char* dst, float* scale) {
   operator_fp64(w, P.a, P.k, P.eta, P.n_d, G);
+  if (masked) mask_operator(w, P.n_d, G);
   *scale = 1.0f;
   if (P.staged_split()) {
     double inv = 1.0;
@@ -226,9 +243,9 @@ void offset_image(const Plan& P, const int32_t* w, std::vector<std::complex<doub
 // repeated problems (serving) then skip the FP64 Green's evaluations.
 struct ImageKey {
   double a, k, eta;
-  int32_t n_d, precision, w0, w1, w2;
+  int32_t n_d, precision, w0, w1, w2, masked;
   bool operator==(const ImageKey& o) const {
-    return a == o.a && k == o.k && eta == o.eta && n_d == o.n_d &&
+    return a == o.a && k == o.k && eta == o.eta && n_d == o.n_d && masked == o.masked &&
            precision == o.precision && w0 == o.w0 && w1 == o.w1 && w2 == o.w2;
   }
 };
@@ -241,7 +258,7 @@ struct ImageKeyHash {
     std::memcpy(&bits, &x.k, 8); mix(bits);
     std::memcpy(&bits, &x.eta, 8); mix(bits);
     mix((uint32_t)x.n_d); mix((uint32_t)x.precision);
-    mix((uint32_t)x.w0); mix((uint32_t)x.w1); mix((uint32_t)x.w2);
+    mix((uint32_t)x.w0); mix((uint32_t)x.w1); mix((uint32_t)x.w2); mix((uint32_t)x.masked);
     return (size_t)h;
   }
 };
@@ -253,28 +270,29 @@ size_t g_image_bytes = 0;
 bool cacheable(const int32_t* w) {
   return std::abs(w[0]) <= 3 && std::abs(w[1]) <= 3 && std::abs(w[2]) <= 3;
 }
-ImageKey image_key(const Plan& P, const int32_t* w) {
-  return ImageKey{P.a, P.k, P.eta, P.n_d, P.precision, w[0], w[1], w[2]};
+ImageKey image_key(const Plan& P, const int32_t* w, bool masked) {
+  return ImageKey{P.a, P.k, P.eta, P.n_d, P.precision, w[0], w[1], w[2], masked ? 1 : 0};
 }
 // An entry holds the image followed by its float scale.
-bool image_cache_get(const Plan& P, const int32_t* w, char* dst, size_t bytes, float* scale) {
+bool image_cache_get(const Plan& P, const int32_t* w, bool masked, char* dst, size_t bytes,
+                     float* scale) {
   if (!cacheable(w)) return false;
   std::lock_guard<std::mutex> lock(g_image_mu);
-  auto it = g_images.find(image_key(P, w));
+  auto it = g_images.find(image_key(P, w, masked));
   if (it == g_images.end() || it->second.size() != bytes + sizeof(float)) return false;
   std::memcpy(dst, it->second.data(), bytes);
   std::memcpy(scale, it->second.data() + bytes, sizeof(float));
   return true;
 }
-void image_cache_put(const Plan& P, const int32_t* w, const char* src, size_t bytes,
-                     float scale) {
+void image_cache_put(const Plan& P, const int32_t* w, bool masked, const char* src,
+                     size_t bytes, float scale) {
   if (!cacheable(w)) return;
   std::lock_guard<std::mutex> lock(g_image_mu);
   if (g_image_bytes + bytes > kImageCacheBytes) return;
   std::vector<char> entry(src, src + bytes);
   entry.resize(bytes + sizeof(float));
   std::memcpy(entry.data() + bytes, &scale, sizeof(float));
-  auto ins = g_images.emplace(image_key(P, w), std::move(entry));
+  auto ins = g_images.emplace(image_key(P, w, masked), std::move(entry));
   if (ins.second) g_image_bytes += bytes;
 }
 
@@ -390,48 +408,356 @@ int64_t max_rounds(const Plan& p) {
   return p.n_items() / 4 + p.n_off() + kMaxTranslateGroups + 1;
 }
 
-Layout workspace_layout(const Plan& p, int32_t max_nrhs) {
-  Layout L{};
+namespace {
+
+// Places allocations one after another, 256-byte aligned.
+struct Taker {
   size_t at = 0;
-  auto take = [&](size_t bytes) {
-    size_t here = at;
+  size_t operator()(size_t bytes) {
+    const size_t here = at;
     at = align256(at + bytes);
     return here;
+  }
+};
+
+size_t row_bytes(const Plan& p, int32_t nrhs) {
+  // one spare row at the end receives the stores of idle matrix-core lanes
+  return ((size_t)nrhs * p.n_pairs() + 1) * p.pstride() * sizeof(float);
+}
+
+}  // namespace
+
+int64_t fft_block(const Plan& p, int32_t max_nrhs) {
+  const int64_t one = std::max<int64_t>(8 * p.fft_scratch_len(), 1);
+  return std::max<int64_t>(1, std::min<int64_t>(max_nrhs, (64ll << 20) / one));
+}
+
+Layout workspace_layout(const Plan& p, int32_t max_nrhs) {
+  Layout L{};
+  Taker take;
+  auto pairs = [&take](const Plan& q) {
+    Layout::Pairs a{};
+    a.table = take(q.table_bytes());
+    a.chunks = take(q.chunks.size() * sizeof(int32_t));
+    a.items = take(q.items.size() * sizeof(int32_t));
+    a.wg_ptr = take((size_t)(kMaxTranslateGroups + 1) * sizeof(int32_t));
+    a.rounds = take((size_t)max_rounds(q) * 16 * sizeof(int32_t));
+    a.wg_round_ptr = take((size_t)(kMaxTranslateGroups + 1) * sizeof(int32_t));
+    a.pair_src = take(q.pair_src.size() * sizeof(int32_t));
+    a.pair_dst = take(q.pair_dst.size() * sizeof(int32_t));
+    a.test_ptr = take(q.test_ptr.size() * sizeof(int32_t));
+    a.off_scale = take((size_t)std::max<int32_t>(q.n_off(), 1) * sizeof(float));
+    a.offsets = take((size_t)q.n_off() * 4 * sizeof(int32_t));
+    return a;
   };
-  L.table = take(p.table_bytes());
-  L.chunks = take(p.chunks.size() * sizeof(int32_t));
-  L.items = take(p.items.size() * sizeof(int32_t));
-  L.wg_ptr = take((size_t)(kMaxTranslateGroups + 1) * sizeof(int32_t));
-  L.rounds = take((size_t)max_rounds(p) * 16 * sizeof(int32_t));
-  L.wg_round_ptr = take((size_t)(kMaxTranslateGroups + 1) * sizeof(int32_t));
-  L.pair_src = take(p.pair_src.size() * sizeof(int32_t));
-  L.pair_dst = take(p.pair_dst.size() * sizeof(int32_t));
-  L.test_ptr = take(p.test_ptr.size() * sizeof(int32_t));
+  if (holds_own_pairs(p)) L.own = pairs(p);
+  if (p.rest) L.rest = pairs(*p.rest);
   L.nb_ptr = take((size_t)(p.n_box + 1) * sizeof(int64_t));
   L.P = take((size_t)max_nrhs * p.n_box * p.vstride() * sizeof(float));
-  // one spare row at the end receives the stores of idle matrix-core lanes
-  L.part = take(((size_t)max_nrhs * p.n_pairs() + 1) * p.pstride() * sizeof(float));
-  L.off_scale = take((size_t)std::max<int32_t>(p.n_off(), 1) * sizeof(float));
+  size_t rows = 0;
+  if (holds_own_pairs(p)) rows = row_bytes(p, max_nrhs);
+  if (p.rest) rows = std::max(rows, row_bytes(*p.rest, max_nrhs));
+  L.part = take(rows);
   L.box_scale = take((size_t)max_nrhs * p.n_box * sizeof(float));
-  L.offsets = take(p.offsets.size() * sizeof(int32_t));
-  L.total = at;
+  if (p.rest) {
+    L.fft = take((size_t)fft_block(p, max_nrhs) * p.fft_scratch_len() * 8);
+    L.fft_spec = take((size_t)p.fft_spec_len * 8);
+    L.fft_tw = take(p.fft_twiddles.size() * sizeof(float));
+    L.fft_map = take(p.fft_map.size() * sizeof(int32_t));
+  }
+  L.total = take.at;
   return L;
 }
 
 ScratchLayout scratch_layout(const Plan& p, int32_t nrhs) {
   ScratchLayout L{};
-  size_t at = 0;
-  auto take = [&](size_t bytes) {
-    size_t here = at;
-    at = align256(at + bytes);
-    return here;
+  auto lay = [&](bool direct) {
+    Taker take;
+    L.P = take((size_t)nrhs * p.n_box * p.vstride() * sizeof(float));
+    L.part = take(row_bytes(direct ? p : p.pairs_plan(), nrhs));
+    L.box_scale = take((size_t)nrhs * p.n_box * sizeof(float));
+    L.fft = take(direct ? 0 : (size_t)fft_block(p, nrhs) * p.fft_scratch_len() * 8);
+    return take.at;
   };
-  L.P = take((size_t)nrhs * p.n_box * p.vstride() * sizeof(float));
-  L.part = take(((size_t)nrhs * p.n_pairs() + 1) * p.pstride() * sizeof(float));
-  L.box_scale = take((size_t)nrhs * p.n_box * sizeof(float));
-  L.total = at;
+  L.direct = lay(true);
+  // networks take the rows of every far pair
+  L.total = p.rest && p.hidden == 0 ? lay(false) : L.direct;
   return L;
 }
+
+namespace {
+
+// Work units of a plan's pairs: chunks of up to kChunk and items of up to 32
+// consecutive pairs of one offset, and their default partitions.
+void build_units(Plan& P) {
+  P.chunks.clear();
+  P.items.clear();
+  auto cut = [&P](std::vector<int32_t>& out, int64_t size) {
+    for (int32_t o = 0; o < P.n_off(); ++o)
+      for (int64_t s = P.off_ptr[o]; s < P.off_ptr[o + 1]; s += size) {
+        out.push_back(o);
+        out.push_back((int32_t)s);
+        out.push_back((int32_t)std::min<int64_t>(size, P.off_ptr[o + 1] - s));
+        out.push_back(0);
+      }
+  };
+  cut(P.chunks, kChunk);
+  cut(P.items, 32);
+  partition_groups(P, kTranslateGroups);
+  build_rounds(P, kRoundGroups);
+}
+
+// Bytes of one offset's image in the table layout of the plan's form.
+size_t image_bytes(const Plan& P) {
+  return P.staged_split() ? P.staged_split_halves() * sizeof(uint16_t)
+         : P.split()      ? (size_t)4 * P.nu * P.khb * sizeof(uint16_t)
+         : P.staged()     ? P.staged_op_floats() * sizeof(float)
+                          : (size_t)2 * P.nu * P.kh * sizeof(float);
+}
+
+// Operator table image, one offset at a time (cached across plans). Large
+// tables (FULL far sets have one operator per distinct offset, ~10^5 on a
+// few-thousand-box scatterer) are built on several host threads, each over a
+// contiguous range of offsets.
+void build_table(Plan& P) {
+  const int64_t n_off = P.n_off();
+  const size_t img_bytes = image_bytes(P);
+  P.off_scale.assign(n_off, 1.0f);
+  if (P.gen_ops) return;  // evaluated by the translation kernel
+  if (P.split())
+    P.table_bf16.assign((size_t)n_off * img_bytes / sizeof(uint16_t), 0);
+  else
+    P.table.assign((size_t)n_off * img_bytes / sizeof(float), 0.0f);
+  char* table = P.split() ? (char*)P.table_bf16.data() : (char*)P.table.data();
+  auto build_range = [&](int64_t lo, int64_t hi) {
+    std::vector<std::complex<double>> G;
+    for (int64_t o = lo; o < hi; ++o) {
+      char* dst = table + (size_t)o * img_bytes;
+      const int32_t* w = &P.offsets[3 * o];
+      const bool m = P.masked((int32_t)o);
+      if (!image_cache_get(P, w, m, dst, img_bytes, &P.off_scale[o])) {
+        offset_image(P, w, m, G, dst, &P.off_scale[o]);
+        image_cache_put(P, w, m, dst, img_bytes, P.off_scale[o]);
+      }
+    }
+  };
+  const int64_t kPerThread = 1024;
+  const int hw = (int)std::max(1u, std::thread::hardware_concurrency());
+  const int64_t nthr = std::min<int64_t>(std::min(hw, 16), (n_off + kPerThread - 1) / kPerThread);
+  if (nthr <= 1) {
+    build_range(0, n_off);
+  } else {
+    std::vector<std::thread> pool;
+    for (int64_t t = 0; t < nthr; ++t)
+      pool.emplace_back(build_range, n_off * t / nthr, n_off * (t + 1) / nthr);
+    for (auto& th : pool) th.join();
+  }
+}
+
+// Smallest 5-smooth length >= n, split into radices of 2..8, the largest
+// first and the last at most 6 (the x kernel keeps the last stage's three
+// components in registers): as few as possible, and among those the split
+// whose smallest radix is largest (L / radix butterflies run side by side).
+// False above kMaxFftLength.
+bool fft_axis(int64_t n, FftAxis& ax) {
+  for (int64_t L = std::max<int64_t>(n, 1); L <= kMaxFftLength; ++L) {
+    int64_t m = L;
+    for (int f : {2, 3, 5})
+      while (m % f == 0) m /= f;
+    if (m != 1) continue;
+    std::vector<std::vector<int>> level = {{}};
+    for (int depth = 0; depth <= kMaxFftStages; ++depth) {
+      const std::vector<int>* best = nullptr;
+      std::vector<std::vector<int>> next;
+      for (const auto& f : level) {
+        int64_t q = L;
+        for (int r : f) q /= r;
+        if (q == 1 && (f.empty() || f.back() <= 6)) {
+          if (!best || (!f.empty() && f.back() > best->back())) best = &f;
+        }
+        for (int r : {8, 6, 5, 4, 3, 2})
+          if (q % r == 0 && (f.empty() || r <= f.back())) {
+            next.push_back(f);
+            next.back().push_back(r);
+          }
+      }
+      if (best) {
+        ax.L = (int32_t)L;
+        ax.stages = (int32_t)best->size();
+        for (size_t i = 0; i < best->size(); ++i) ax.radix[i] = (*best)[i];
+        return true;
+      }
+      level.swap(next);
+    }
+  }
+  return false;
+}
+
+// Whether a scatterer's FULL product runs as a convolution: by estimates of
+// both ways' microseconds, fitted to both measured side by side on grids,
+// plates, shells, cubes and masks of 125 to 800 boxes, n_d 1..4.
+// Direct: 15 + 5 ns per offset (a work unit of its own) + the operators and
+// the partial rows, out and in, at 3.3 TB/s (5^3 boxes, n_d = 3: 45 us
+// direct, 55 as a convolution; 6^3: 67 and 57; the 762-box shell with 19,408
+// offsets: n_d = 1 100 and 35, n_d = 2 148 and 56, n_d = 3 525 and 108).
+// Convolution: 30 + 12 if pairs are left + the lattices, each transform in
+// and out, and the spectrum at 1.8 TB/s + the rows of the pairs left.
+bool convolution_pays(const Plan& P, const FftGrid& g, int64_t n_box, int64_t n_pairs,
+                      int64_t n_rest, int64_t n_off) {
+  const double row = 4.0 * P.pstride();
+  // the scratch has to fit where the rows of the pairs would be (a caller
+  // without allocation has room for those)
+  if (8.0 * (g.zlen() + g.yzlen()) + row * (double)(n_rest + 2 * n_box) >
+      0.9 * row * (double)n_pairs)
+    return false;
+  const double direct = 15.0 + 5e-3 * (double)n_off +
+                        ((double)n_off * image_bytes(P) + 2.0 * row * (double)n_pairs) / 3.3e6;
+  const double lattices = 8.0 * (4.0 * g.zlen() + 4.0 * g.yzlen() + g.spec_len());
+  const double conv =
+      30.0 + (n_rest ? 12.0 : 0.0) + lattices / 1.8e6 + 2.0 * row * (double)n_rest / 3.3e6;
+  return conv < 0.9 * direct;
+}
+
+// Lattices of the scatterers whose FULL product runs as a convolution, and
+// the plan of the pairs left (FftGrid). P's far set is complete and grouped.
+void build_convolution(Plan& P) {
+  // not for the single FP16 product: its result would differ from the one
+  // that form gives by the form's own error (2^-11 a term)
+  if (P.far_mode != 1 || P.precision == 3) return;
+  const int64_t np = P.n_pairs();
+  const int32_t n_scat = P.n_scat();
+  auto scat_of = [&P](int32_t box) {
+    return (int32_t)(std::upper_bound(P.scat_ptr.begin(), P.scat_ptr.end(), (int64_t)box) -
+                     P.scat_ptr.begin()) - 1;
+  };
+  std::vector<uint8_t> two(P.n_off());  // offsets a masked operator exists for
+  for (int32_t o = 0; o < P.n_off(); ++o) {
+    const int32_t* w = &P.offsets[3 * o];
+    two[o] = P.n_d > 1 && cheb(w[0], w[1], w[2]) == 2;
+  }
+  // per scatterer: pairs, those of two, and offsets (pairs are grouped by
+  // offset: a new one where it differs from the scatterer's last)
+  std::vector<int64_t> n_pairs(n_scat, 0), n_rest(n_scat, 0), n_off(n_scat, 0);
+  std::vector<int32_t> last(n_scat, -1);
+  std::vector<int32_t> scat(n_scat > 1 ? np : 0);
+  for (int64_t q = 0; q < np; ++q) {
+    const int32_t s = n_scat > 1 ? (scat[q] = scat_of(P.pair_test[q])) : 0;
+    n_pairs[s] += 1;
+    n_rest[s] += two[P.pair_off[q]];
+    n_off[s] += last[s] != P.pair_off[q];
+    last[s] = P.pair_off[q];
+  }
+  std::vector<int32_t> grid_of(n_scat, -1);
+  for (int32_t s = 0; s < n_scat; ++s) {
+    FftGrid g{};
+    int64_t lo[3], hi[3];
+    for (int d = 0; d < 3; ++d) {
+      lo[d] = std::numeric_limits<int32_t>::max();
+      hi[d] = 0;
+      for (int64_t i = P.scat_ptr[s]; i < P.scat_ptr[s + 1]; ++i) {
+        lo[d] = std::min<int64_t>(lo[d], P.boxes[3 * i + d]);
+        hi[d] = std::max<int64_t>(hi[d], P.boxes[3 * i + d]);
+      }
+    }
+    bool fits = true;
+    for (int d = 0; d < 3 && fits; ++d) {
+      const int64_t n = hi[d] - lo[d] + 1;
+      fits = n * P.n_d <= kMaxFftLength && fft_axis(2 * n * P.n_d - 1, g.ax[d]);
+      g.n[d] = (int32_t)std::min<int64_t>(n, kMaxFftLength);
+      g.s[d] = g.n[d] * P.n_d;
+    }
+    // z lines run n_d to a workgroup, one butterfly per thread
+    fits = fits && g.ax[2].butterflies() * P.n_d <= kMaxFftThreads;
+    if (!fits || !convolution_pays(P, g, P.scat_ptr[s + 1] - P.scat_ptr[s], n_pairs[s],
+                                   n_rest[s], n_off[s])) continue;
+    grid_of[s] = (int32_t)P.fft.size();
+    g.map = (int64_t)P.fft_map.size() / 2;
+    P.fft_map.resize(P.fft_map.size() + 2 * (size_t)g.n[0] * g.n[1] * g.n[2], -1);
+    for (int64_t i = P.scat_ptr[s]; i < P.scat_ptr[s + 1]; ++i) {
+      const int32_t* c = &P.boxes[3 * i];
+      const int64_t cell =
+          g.map + ((c[0] - lo[0]) * g.n[1] + (c[1] - lo[1])) * g.n[2] + (c[2] - lo[2]);
+      P.fft_map[2 * cell] = (int32_t)i;
+    }
+    // a spectrum depends on the lattice alone: equal lattices share one
+    g.spec = -1;
+    for (const FftGrid& o : P.fft)
+      if (std::equal(o.s, o.s + 3, g.s)) g.spec = o.spec;
+    if (g.spec < 0) {
+      g.spec = P.fft_spec_len;
+      P.fft_spec_len += g.spec_len();
+    }
+    P.fft.push_back(g);
+  }
+  if (P.fft.empty()) return;
+  for (FftGrid& g : P.fft)
+    for (FftAxis& ax : g.ax) {
+      ax.tw = (int32_t)P.fft_twiddles.size() / 2;
+      for (const FftGrid& o : P.fft)
+        for (const FftAxis& b : o.ax)
+          if (&b < &ax && b.L == ax.L) ax.tw = b.tw;
+      if (ax.tw < (int32_t)P.fft_twiddles.size() / 2) continue;
+      for (int32_t k = 0; k < ax.L; ++k) {
+        P.fft_twiddles.push_back((float)std::cos(2.0 * kPi * k / ax.L));
+        P.fft_twiddles.push_back((float)-std::sin(2.0 * kPi * k / ax.L));
+      }
+    }
+
+  // The pairs left: all of a scatterer without a lattice, the masked ones of
+  // the others; grouped by (offset, masked), in P's order within a group.
+  auto R = std::make_unique<Plan>();
+  R->n_box = P.n_box;
+  R->scat_ptr = P.scat_ptr;
+  R->a = P.a;
+  R->k = P.k;
+  R->eta = P.eta;
+  R->n_d = P.n_d;
+  R->nu = P.nu;
+  R->kh = P.kh;
+  R->khb = P.khb;
+  R->far_mode = P.far_mode;
+  R->precision = P.precision;
+  R->gen_ops = P.gen_ops;
+  R->off_ptr.push_back(0);
+  for (int32_t o = 0; o < P.n_off(); ++o)
+    for (int m = 0; m < 2; ++m) {
+      if (m && !two[o]) continue;
+      for (int64_t q = P.off_ptr[o]; q < P.off_ptr[o + 1]; ++q)
+        if ((grid_of[n_scat > 1 ? scat[q] : 0] >= 0) == (m == 1)) {
+          R->pair_test.push_back(P.pair_test[q]);
+          R->pair_src.push_back(P.pair_src[q]);
+        }
+      if ((int64_t)R->pair_src.size() == R->off_ptr.back()) continue;
+      R->off_ptr.push_back((int64_t)R->pair_src.size());
+      R->offsets.insert(R->offsets.end(), &P.offsets[3 * o], &P.offsets[3 * o] + 3);
+      R->op_masked.push_back((uint8_t)m);
+    }
+  // Rows: the convolution's (boxes of a lattice with a far pair; the others
+  // get none, so that a box without far pairs stays exactly zero), then the
+  // pairs' in grouped order.
+  const int64_t nr = (int64_t)R->pair_src.size();
+  std::vector<int32_t> conv(P.n_box, 0);
+  for (int64_t j = 0; j < P.n_box; ++j)
+    conv[j] = P.test_ptr[j + 1] > P.test_ptr[j] && grid_of[scat_of((int32_t)j)] >= 0;
+  R->test_ptr.assign(P.n_box + 1, 0);
+  for (int64_t q = 0; q < nr; ++q) R->test_ptr[R->pair_test[q] + 1]++;
+  for (int64_t j = 0; j < P.n_box; ++j) R->test_ptr[j + 1] += R->test_ptr[j] + conv[j];
+  std::vector<int32_t> fill(R->test_ptr.begin(), R->test_ptr.end() - 1);
+  for (size_t c = 0; c < P.fft_map.size(); c += 2) {
+    const int32_t box = P.fft_map[c];
+    if (box >= 0 && conv[box]) P.fft_map[c + 1] = fill[box]++;
+  }
+  const int64_t n_rows = R->test_ptr.back();
+  R->pair_dst.resize(nr);
+  for (int64_t q = 0; q < nr; ++q) R->pair_dst[q] = fill[R->pair_test[q]]++;
+  build_units(*R);
+  R->pair_src.resize(n_rows, 0);
+  R->pair_dst.resize(n_rows, 0);
+  build_table(*R);
+  P.rest = std::move(R);
+}
+
+}  // namespace
 
 std::string build_plan(const int32_t* box_ijk, int64_t n_box, double a,
                        double k, double eta, int n_d, int far_mode,
@@ -558,11 +884,7 @@ std::string build_plan(const int32_t* box_ijk, int64_t n_box, double a,
     for (int64_t p = 0; p < np; ++p) oid[p] = rank[oid[p]];
   }
   const int64_t n_off = (int64_t)uniq.size();
-  // bytes of one offset's image in the table layout of the plan's form
-  const size_t img_bytes = P.staged_split() ? P.staged_split_halves() * sizeof(uint16_t)
-                           : P.split()        ? (size_t)4 * P.nu * P.khb * sizeof(uint16_t)
-                           : P.staged()       ? P.staged_op_floats() * sizeof(float)
-                                              : (size_t)2 * P.nu * P.kh * sizeof(float);
+  const size_t img_bytes = image_bytes(P);
   if (!P.gen_ops && (double)n_off * (double)img_bytes > kMaxTableBytes)
     return "operator table would exceed 16 GiB";
   P.offsets.resize(3 * n_off);
@@ -596,26 +918,7 @@ std::string build_plan(const int32_t* box_ijk, int64_t n_box, double a,
   P.pair_dst.resize(np);
   for (int64_t q = 0; q < np; ++q) P.pair_dst[P.test_pos[q]] = (int32_t)q;
 
-  // Work units: up to kChunk consecutive pairs of one offset.
-  P.chunks.clear();
-  for (int64_t o = 0; o < n_off; ++o)
-    for (int64_t s = P.off_ptr[o]; s < P.off_ptr[o + 1]; s += kChunk) {
-      P.chunks.push_back((int32_t)o);
-      P.chunks.push_back((int32_t)s);
-      P.chunks.push_back((int32_t)std::min<int64_t>(kChunk, P.off_ptr[o + 1] - s));
-      P.chunks.push_back(0);
-    }
-  P.items.clear();
-  for (int64_t o = 0; o < n_off; ++o)
-    for (int64_t s = P.off_ptr[o]; s < P.off_ptr[o + 1]; s += 32) {
-      P.items.push_back((int32_t)o);
-      P.items.push_back((int32_t)s);
-      P.items.push_back((int32_t)std::min<int64_t>(32, P.off_ptr[o + 1] - s));
-      P.items.push_back(0);
-    }
-
-  partition_groups(P, kTranslateGroups);
-  build_rounds(P, kRoundGroups);
+  build_units(P);
 
   // Orbits under the 48 signed permutations: key = sorted |w|.
   std::vector<std::array<int32_t, 3>> keys(n_off);
@@ -629,38 +932,8 @@ std::string build_plan(const int32_t* box_ijk, int64_t n_box, double a,
   P.n_orbits = (int32_t)(std::unique(keys.begin(), keys.end()) - keys.begin());
 
   P.off_scale.assign(n_off, 1.0f);
-  if (P.gen_ops) return std::string();  // evaluated by the translation kernel
-
-  // Operator table image, one offset at a time (cached across plans).
-  if (P.split())
-    P.table_bf16.assign((size_t)n_off * img_bytes / sizeof(uint16_t), 0);
-  else
-    P.table.assign((size_t)n_off * img_bytes / sizeof(float), 0.0f);
-  char* table = P.split() ? (char*)P.table_bf16.data() : (char*)P.table.data();
-  // Offsets are independent: large tables (FULL far sets have one operator
-  // per distinct offset, ~10^5 on a few-thousand-box scatterer) are built
-  // on several host threads, each over a contiguous range of offsets.
-  auto build_range = [&](int64_t lo, int64_t hi) {
-    std::vector<std::complex<double>> G;
-    for (int64_t o = lo; o < hi; ++o) {
-      char* dst = table + (size_t)o * img_bytes;
-      if (!image_cache_get(P, &P.offsets[3 * o], dst, img_bytes, &P.off_scale[o])) {
-        offset_image(P, &P.offsets[3 * o], G, dst, &P.off_scale[o]);
-        image_cache_put(P, &P.offsets[3 * o], dst, img_bytes, P.off_scale[o]);
-      }
-    }
-  };
-  const int64_t kPerThread = 1024;
-  const int hw = (int)std::max(1u, std::thread::hardware_concurrency());
-  const int64_t nthr = std::min<int64_t>(std::min(hw, 16), (n_off + kPerThread - 1) / kPerThread);
-  if (nthr <= 1) {
-    build_range(0, n_off);
-  } else {
-    std::vector<std::thread> pool;
-    for (int64_t t = 0; t < nthr; ++t)
-      pool.emplace_back(build_range, n_off * t / nthr, n_off * (t + 1) / nthr);
-    for (auto& th : pool) th.join();
-  }
+  build_convolution(P);
+  if (!P.rest) build_table(P);
   return std::string();
 }
 

@@ -7,6 +7,7 @@
 #include <cstddef>
 #include <cstdint>
 #include <cstring>
+#include <memory>
 #include <string>
 #include <vector>
 
@@ -109,6 +110,43 @@ std::vector<double> site_offsets(double a, int n_d);
 void operator_fp64(const int32_t w[3], double a, double k, double eta, int n_d,
                    std::vector<std::complex<double>>& G);
 
+// FULL far sets as a convolution. The sites of all boxes lie on one uniform
+// lattice of step a / n_d, and D depends on the site difference d alone, so
+// the part of the FULL product with max |d_i| >= 2 n_d sites (which only
+// pairs of boxes two or more apart have) is a discrete convolution over the
+// lattice, done with FFTs of the zero-padded lattice. What is left are the
+// pairs of boxes exactly two apart, with the site pairs max |d_i| < 2 n_d:
+// a far set of at most 98 offsets with masked operators, which the
+// translation kernels take (Plan::rest). Everything summed is far field:
+// no near-field term is added and taken away again.
+constexpr int kMaxFftLength = 768;
+constexpr int kMaxFftStages = 6;
+constexpr int kMaxFftThreads = 1024;  // threads of a transform's workgroup
+// Transform along one axis: length (5-smooth), its radices, and where its
+// twiddle factors exp(-2 pi i k / L) start in Plan::fft_twiddles.
+struct FftAxis {
+  int32_t L = 1, stages = 0;
+  int32_t radix[kMaxFftStages] = {};
+  int32_t tw = 0;
+  // butterflies of one line in the stage that has most (the last)
+  int butterflies() const { return stages ? L / radix[stages - 1] : 1; }
+};
+// The lattice of one scatterer.
+struct FftGrid {
+  int32_t n[3];   // boxes per axis of the bounding grid
+  int32_t s[3];   // sites per axis, n * n_d
+  FftAxis ax[3];  // L >= 2 s - 1
+  int64_t map;    // first cell in Plan::fft_map ((x n_y + y) n_z + z)
+  int64_t spec;   // first value of its spectrum (complex values)
+  int64_t spec_len() const {
+    return 6LL * (ax[0].L / 2 + 1) * (ax[1].L / 2 + 1) * (ax[2].L / 2 + 1);
+  }
+  // scratch of one right-hand side (complex values): transformed along z,
+  // and along y and z
+  int64_t zlen() const { return 3LL * s[0] * s[1] * ax[2].L; }
+  int64_t yzlen() const { return 3LL * s[0] * ax[1].L * ax[2].L; }
+};
+
 struct Plan {
   // Problem.
   int64_t n_box = 0;
@@ -193,6 +231,33 @@ struct Plan {
     return split() ? table_bf16.size() * sizeof(uint16_t) : table.size() * sizeof(float);
   }
 
+  // FULL far sets as a convolution (see FftGrid): the scatterers' lattices,
+  // per cell of their bounding grids the box and its partial row (-1: none),
+  // the twiddle factors of the lengths in use, and the remaining pairs as a
+  // plan of their own, which stage 2 runs in place of this one (whose pairs
+  // then serve introspection and, in the FP32 form, networks). In that plan
+  // an operator is masked where op_masked is set, each box of a lattice has
+  // one partial row more (its first, written by the convolution), and
+  // pair_src / pair_dst are padded to the number of rows.
+  std::vector<FftGrid> fft;
+  std::vector<int32_t> fft_map;
+  std::vector<float> fft_twiddles;
+  int64_t fft_spec_len = 0;     // complex values of all spectra
+  std::unique_ptr<Plan> rest;
+  std::vector<uint8_t> op_masked;  // per offset; empty: none
+  bool masked(int32_t o) const { return !op_masked.empty() && op_masked[o]; }
+  int64_t fft_scratch_len() const {
+    int64_t z = 0, yz = 0;
+    for (const FftGrid& g : fft) {
+      z = z > g.zlen() ? z : g.zlen();
+      yz = yz > g.yzlen() ? yz : g.yzlen();
+    }
+    return z + yz;
+  }
+  // The plan whose pairs, rows and schedule stage 2 with operators uses.
+  const Plan& pairs_plan() const { return rest ? *rest : *this; }
+  Plan& pairs_plan() { return rest ? *rest : *this; }
+
   // Binding.
   char* ws = nullptr;
   size_t ws_bytes = 0;
@@ -211,7 +276,11 @@ struct Plan {
   float* d_P = nullptr;
   float* d_part = nullptr;
   float* d_off_scale = nullptr;  // [n_off] (FP16 forms)
-  int32_t* d_offsets = nullptr;  // [n_off][3] integer offsets (generated operators)
+  int32_t* d_offsets = nullptr;  // [n_off][4] offset, masked (generated operators)
+  float* d_fft = nullptr;          // scratch of the convolution
+  float* d_fft_spec = nullptr;
+  float* d_fft_tw = nullptr;
+  int32_t* d_fft_map = nullptr;
   float* d_box_scale = nullptr;  // [max_nrhs][n_box] box-vector scales (FP16 forms)
 
   // Networks standing in for the operators (Sec. 3): hidden width (0 = none,
@@ -231,16 +300,31 @@ struct Plan {
 
 // Workspace layout, in bytes from the workspace start.
 struct Layout {
-  size_t table, chunks, items, wg_ptr, rounds, wg_round_ptr, pair_src, pair_dst, test_ptr, nb_ptr,
-      P, part, off_scale, box_scale, offsets, total;
+  // arrays of the far set: of this plan, and of the one left beside a
+  // convolution
+  struct Pairs {
+    size_t table, chunks, items, wg_ptr, rounds, wg_round_ptr, pair_src, pair_dst, test_ptr,
+        off_scale, offsets;
+  };
+  Pairs own, rest;
+  size_t nb_ptr, P, part, box_scale, fft, fft_spec, fft_tw, fft_map, total;
 };
 Layout workspace_layout(const Plan& p, int32_t max_nrhs);
+// Whether a bound plan holds its own far set's arrays and rows: without a
+// convolution, or where networks may be set (the FP32 form).
+inline bool holds_own_pairs(const Plan& p) { return !p.rest || p.precision == 0; }
+
+// Right-hand sides that pass through the convolution's scratch together: as
+// many as 64 MB hold (small lattices are bound by their launches, large ones
+// by memory, where one at a time keeps more in the caches).
+int64_t fft_block(const Plan& p, int32_t max_nrhs);
 
 // The per-call intermediates of one product of nrhs right-hand sides (box
 // vectors, partial rows with their spare row, FP16 box scales), laid out
 // from offset 0 of a scratch region, in bytes.
 struct ScratchLayout {
-  size_t P, part, box_scale, total;
+  size_t P, part, box_scale, fft, total;
+  size_t direct;  // bytes with the rows of every far pair and no convolution
 };
 ScratchLayout scratch_layout(const Plan& p, int32_t nrhs);
 
