@@ -717,7 +717,7 @@ int ubf_plan_info(const ubf_plan* plan, ubf_info* out) {
   out->n_u = p.nu;
   out->n_d = p.n_d;
   out->n_chunks = p.n_chunks();
-  out->table_bytes = (int64_t)p.pairs_plan().table_bytes();
+  out->table_bytes = (int64_t)p.pairs_plan().operand_bytes();
   out->translate_flops = 8.0 * p.nu * (double)p.nu * (double)p.n_pairs();
   out->mfma = (ubf::translate_uses_mfma(p) || ubf::staged_translate_supported(p)) ? 1 : 0;
   out->precision = p.precision;

@@ -289,8 +289,9 @@ struct Source {
       const float* b = P + (int64_t)box * 2 * kh;
       return make_float2(b[u], b[kh + u]);
     }
+    const int at = khb == 192 ? (u % 3) * 64 + u / 3 : u;  // pos16 of stage 1
     const unsigned short* q = reinterpret_cast<const unsigned short*>(P + (int64_t)box * 2 * khb) +
-                              32 * (u >> 3) + (u & 7);
+                              32 * (at >> 3) + (at & 7);
     if (mode == 1) {
       auto f = [](unsigned short b) { return __uint_as_float((unsigned)b << 16); };
       return make_float2(f(q[0]) + f(q[16]), f(q[8]) + f(q[24]));

@@ -40,6 +40,12 @@ __device__ inline float f16_f(unsigned short b) { return __half2float(__ushort_a
 // so the two lanes holding a column's K halves read adjacent 16 bytes.
 __device__ inline int q16(int part, int u) { return 32 * (u >> 3) + 8 * part + (u & 7); }
 
+// Position of coefficient u = 3 site + component in a 16-bit box vector of
+// khb coefficients. At n_d = 4 (192) the components come one after another,
+// sites in order within each, so that a k-step's 8 values are two runs of
+// four sites along z (see translate_lattice_kernel).
+__device__ inline int pos16(int u, int khb) { return khb == 192 ? (u % 3) * 64 + u / 3 : u; }
+
 // Writes one box-vector coefficient (re, im) at index u of a box vector
 // starting at Pb. mode 0: FP32 layout [re(kh) | im(kh)]. Otherwise the
 // 16-bit layout of q16 (khb coefficients), with hi = round(v),
@@ -52,6 +58,7 @@ __device__ inline void put_coef(float* Pb, int u, float re, float im, int kh, in
     Pb[kh + u] = im;
     return;
   }
+  u = pos16(u, khb);
   unsigned short* q = reinterpret_cast<unsigned short*>(Pb);
   if (mode == 1) {
     const unsigned rh = bf16_rne(re), ih = bf16_rne(im);
@@ -190,15 +197,16 @@ __global__ __launch_bounds__(kBlock) void unpack_kernel(
     const int64_t row = t / nu;
     const float* Pb = P + row * vs;
     const unsigned short* q = reinterpret_cast<const unsigned short*>(Pb);
+    const int k = pos16(u, khb);
     if (mode == 0) {
       out[t] = make_float2(Pb[u], Pb[kh + u]);
     } else if (mode == 1) {
-      out[t] = make_float2(bf16_f(q[q16(0, u)]) + bf16_f(q[q16(2, u)]),
-                           bf16_f(q[q16(1, u)]) + bf16_f(q[q16(3, u)]));
+      out[t] = make_float2(bf16_f(q[q16(0, k)]) + bf16_f(q[q16(2, k)]),
+                           bf16_f(q[q16(1, k)]) + bf16_f(q[q16(3, k)]));
     } else {
       const float sc = box_scale[row];
-      out[t] = make_float2((f16_f(q[q16(0, u)]) + f16_f(q[q16(2, u)])) * sc,
-                           (f16_f(q[q16(1, u)]) + f16_f(q[q16(3, u)])) * sc);
+      out[t] = make_float2((f16_f(q[q16(0, k)]) + f16_f(q[q16(2, k)])) * sc,
+                           (f16_f(q[q16(1, k)]) + f16_f(q[q16(3, k)])) * sc);
     }
   }
 }

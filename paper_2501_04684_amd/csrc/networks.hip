@@ -466,6 +466,7 @@ __global__ __launch_bounds__(kBlock, 4) void translate_staged_kernel(
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 halfx8 __attribute__((ext_vector_type(8)));
 typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
+typedef unsigned uintx2 __attribute__((ext_vector_type(2)));
 template <bool F16>
 __device__ inline floatx16 mfma16(uintx4 a, uintx4 b, floatx16 c) {
   if constexpr (F16)
@@ -476,92 +477,146 @@ __device__ inline floatx16 mfma16(uintx4 a, uintx4 b, floatx16 c) {
                                                   __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 
-// The split-precision operator-table product for box sizes whose 16-bit
-// columns do not fit in registers (N_u = 192, the paper's 4x4x4 dipoles),
-// on v_mfma_f32_32x32x16_f16 / _bf16: the same products as the register
-// kernels (G_h P_h + G_h P_l + G_l P_h, or G_h P_h alone), one workgroup per
-// work item (up to 32 pairs of one offset). The item's 16-bit box vectors
-// (stage 1's layout: per k-step of 8 coefficients, [re.hi | im.hi | re.lo |
-// im.lo]) are staged whole in LDS, one column per row with a 16-byte pad so
-// that the 32 columns' reads spread over the banks; wavefront w computes the
-// 32-row blocks w, w + 4, w + 8 of [[Gr, -Gi], [Gi, Gr]] (M = K = 2 N_u),
-// with the A values read from the operator image in matrix-core fragment
-// order (per block, k-step and part: 64 lanes x 16 bytes contiguous). FP16:
-// each result is multiplied by its offset's and its source box's scales
-// (powers of two).
-template <int NU, bool F16, int NPROD>
-__global__ __launch_bounds__(kBlock, 2) void translate_staged_split_kernel(
-    const unsigned short* __restrict__ table, const int32_t* __restrict__ items,
+// The split-precision operator product for box sizes whose 16-bit columns do
+// not fit in registers (N_u = 192, the paper's 4x4x4 dipoles), on
+// v_mfma_f32_32x32x16_f16 / _bf16: the same products as the register kernels
+// (G_h P_h + G_h P_l + G_l P_h, or G_h P_h alone), one workgroup per work
+// item (up to 32 pairs of one offset); wavefront w computes the 32-row blocks
+// w, w + 4, w + 8 of [[Gr, -Gi], [Gi, Gr]] (M = K = 2 N_u).
+//
+// An operator entry depends on the difference of the two sites alone, so the
+// 384 x 384 operand is never stored: with the coefficients of a box vector
+// ordered component by component, the 8 values of a k-step are two runs of
+// four source sites along z (one component be, one sx, sy and sy + 1), and a
+// lane's A value is two 8-byte LDS reads from the operator's lattice image
+// (Plan::kLatticeHalves). Read from memory as matrix-core operands (590 KB an
+// offset, 186 MB for the 316 offsets of a sphere, several times over by its
+// items) they took 69 us on the 762-box sphere, 31 us so.
+//
+// The source components are taken one after another: 19 KB of image, copied
+// global -> LDS without registers, and 17 KB of box vectors, whose loads for
+// the next component are in flight during the products. That leaves room for
+// four workgroups per compute unit, which hide each other's copies (the
+// whole image and two vector buffers, two workgroups per unit: 37 us; two
+// tiles of columns per workgroup, which halves the LDS reads, 44 us: too few
+// workgroups to fill the chip evenly). FP16: each result is multiplied by
+// its offset's and its source box's scales (powers of two).
+template <bool F16, int NPROD>
+__global__ __launch_bounds__(kBlock, 4) void translate_lattice_kernel(
+    const uintx2* __restrict__ table, const int32_t* __restrict__ items,
     const int32_t* __restrict__ pair_src, const int32_t* __restrict__ pair_dst,
     const float* __restrict__ P, float* __restrict__ part, int64_t n_box, int64_t n_pairs,
     int n_items, const float* __restrict__ off_scale, const float* __restrict__ box_scale) {
-  constexpr int KH = (NU + 3) & ~3;
-  constexpr int KHB = (NU + 7) & ~7;
-  constexpr int NGB = KHB / 8;            // k-steps per half
-  constexpr int VU = NGB * 4;             // 16-byte units per box vector
-  constexpr int CPU = VU + 1;             // LDS pitch per column (units)
-  constexpr int OB = (2 * NU + 31) / 32;  // 32-row blocks
-  constexpr int PER = (OB + 3) / 4;       // blocks per wavefront
+  constexpr int NU = 192, NS = 64;        // coefficients, sites
+  constexpr int NG = NS / 8;              // k-steps per component and half
   constexpr int NPART = NPROD == 3 ? 2 : 1;
-  constexpr int PSTR = 2 * KH;
+  constexpr int VU = NU / 8 * 4;          // 16-byte units per box vector
+  constexpr int CU = NG * 2 * NPART;      // units of one component staged per column
+  constexpr int CPU = CU + 1;             // LDS pitch per column (units)
+  constexpr int RUNS = Plan::kLatticePart;  // 8-byte runs of one component and part
+  constexpr int U16 = NPART * RUNS / 2;   // 16-byte units of one component's image
+  constexpr int UIT = (U16 + kBlock - 1) / kBlock;
+  constexpr int PSTR = 2 * NU;
+  constexpr int PER = 3;                  // row blocks per wavefront
+  constexpr int LD = 32 * CU / kBlock;    // staged units per thread and component
+  static_assert(RUNS % 2 == 0, "whole 16-byte units");
+  __shared__ uintx4 img4[UIT * kBlock];
   __shared__ uintx4 cols[32 * CPU];
 
   int o, first, ncol;
   if (!load_item(items, n_items, o, first, ncol)) return;  // grid padding
   const int rhs = blockIdx.y;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
   const int r = lane & 31, h = lane >> 5;
   const uintx4* Pv = reinterpret_cast<const uintx4*>(P) + (int64_t)rhs * n_box * VU;
-  // stage the item's columns (past ncol: the last pair again)
-  for (int u = threadIdx.x; u < 32 * VU; u += kBlock) {
-    const int c = u / VU, q = u - c * VU;
-    const int src = pair_src[first + min(c, ncol - 1)];
-    cols[c * CPU + q] = Pv[(int64_t)src * VU + q];
-  }
+  const uintx4* tab = reinterpret_cast<const uintx4*>(table + (size_t)o * 3 * NPART * RUNS);
+  auto copy_image = [&](int be) {
+#pragma unroll
+    for (int it = 0; it < UIT; ++it)  // threads past the image read its last unit into padding
+      __builtin_amdgcn_global_load_lds(
+          reinterpret_cast<const void*>(tab + be * U16 + min(t + it * kBlock, U16 - 1)),
+          (__attribute__((address_space(3))) void*)(img4 + it * kBlock + wave * 64), 16, 0, 0);
+  };
+  copy_image(0);
+  // staging: thread t takes unit t % CU of columns t / CU, + kBlock / CU ...
+  // (columns past ncol: the last pair again)
+  const int su = t % CU, sc0 = t / CU;
+  const int unit = NPART == 2 ? su : 4 * (su >> 1) + (su & 1);  // hi only: skip the lo units
+  int src[LD];
+  uintx4 v[LD];
+#pragma unroll
+  for (int i = 0; i < LD; ++i)
+    src[i] = pair_src[first + min(sc0 + i * (kBlock / CU), ncol - 1)];
+  auto fetch = [&](int be) {
+#pragma unroll
+    for (int i = 0; i < LD; ++i) v[i] = Pv[(int64_t)src[i] * VU + be * NG * 4 + unit];
+  };
+  fetch(0);
   const int src_r = pair_src[first + min(r, ncol - 1)];
   const int dst = pair_dst[first + min(r, ncol - 1)];
   const float sc = F16 ? off_scale[o] * box_scale[(int64_t)rhs * n_box + src_r] : 1.f;
-  __syncthreads();
 
-  const uintx4* Ao = reinterpret_cast<const uintx4*>(table) + (size_t)o * OB * NGB * NPART * 64;
-  const uintx4* arow[PER];
+  // A of row block rb: this lane's row (test site l, component al) of Er (re
+  // for the real half h = 0, -im for h = 1) or Ei (im, re); its runs start at
+  // run[i] for (sx, sy) = (3, 3), 4 runs apart per step of sy, 28 per step of
+  // sx
+  const uintx2* img = reinterpret_cast<const uintx2*>(img4);
+  int run[PER];
+  unsigned sgn[PER];
   floatx16 acc[PER];
 #pragma unroll
   for (int i = 0; i < PER; ++i) {
-    arow[i] = Ao + (size_t)min(wave + 4 * i, OB - 1) * NGB * NPART * 64 + lane;
+    const int row = (wave + 4 * i) * 32 + r;
+    const bool er = row < NU;
+    const int u = er ? row : row - NU, l = u / 3, al = u - 3 * l;
+    const int plane = er == (h == 1) ? 1 : 0;
+    sgn[i] = er && h == 1 ? 0x80008000u : 0u;
+    run[i] = plane * Plan::kLatticePlane + al * Plan::kLatticeAl +
+             ((l >> 4) * 7 + ((l >> 2) & 3)) * 4 + (l & 3);
     acc[i] = floatx16{};
   }
-  const uintx4* col = cols + r * CPU;
-#pragma unroll 4
-  for (int g = 0; g < NGB; ++g) {
-    const uintx4 bh = col[4 * g + h];
-    const uintx4 bl = NPROD == 3 ? col[4 * g + 2 + h] : uintx4{};
+  for (int be = 0; be < 3; ++be) {
+    if (be > 0) {
+      __syncthreads();  // every wavefront is done with the last component
+      copy_image(be);
+    }
 #pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      const uintx4 ah = arow[i][(g * NPART) * 64];
-      acc[i] = mfma16<F16>(ah, bh, acc[i]);
-      if (NPROD == 3) {
-        const uintx4 al = arow[i][(g * NPART + 1) * 64];
-        acc[i] = mfma16<F16>(ah, bl, acc[i]);
-        acc[i] = mfma16<F16>(al, bh, acc[i]);
+    for (int i = 0; i < LD; ++i) cols[(sc0 + i * (kBlock / CU)) * CPU + su] = v[i];
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the image's copies into LDS
+    __syncthreads();
+    if (be < 2) fetch(be + 1);
+#pragma unroll 2
+    for (int g = 0; g < NG; ++g) {
+      const uintx4* col = cols + r * CPU + 2 * NPART * g;
+      const uintx4 bh = col[h];
+      const uintx4 bl = NPROD == 3 ? col[2 + h] : uintx4{};
+      // k-step g: sx = g / 2, sy = 2 (g % 2) and the next
+      const int at0 = ((3 - (g >> 1)) * 7 + (3 - 2 * (g & 1))) * 4, at1 = at0 - 4;
+#pragma unroll
+      for (int i = 0; i < PER; ++i) {
+        const uintx2* p = img + run[i];
+        const uintx2 h0 = p[at0], h1 = p[at1];
+        const uintx4 ah = uintx4{h0.x, h0.y, h1.x, h1.y} ^ sgn[i];
+        acc[i] = mfma16<F16>(ah, bh, acc[i]);
+        if (NPROD == 3) {
+          const uintx2 l0 = p[RUNS + at0], l1 = p[RUNS + at1];
+          const uintx4 al = uintx4{l0.x, l0.y, l1.x, l1.y} ^ sgn[i];
+          acc[i] = mfma16<F16>(ah, bl, acc[i]);
+          acc[i] = mfma16<F16>(al, bh, acc[i]);
+        }
       }
     }
   }
   if (r < ncol) {
     float* prow = part + ((int64_t)rhs * n_pairs + dst) * PSTR;
 #pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      const int ob = wave + 4 * i;
-      if (ob >= OB) continue;
+    for (int i = 0; i < PER; ++i)
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const int r0 = ob * 32 + 8 * q + 4 * h;
-        if (r0 < 2 * NU)
-          *reinterpret_cast<floatx4*>(prow + r0) =
-              floatx4{acc[i][4 * q], acc[i][4 * q + 1], acc[i][4 * q + 2], acc[i][4 * q + 3]} *
-              sc;
+        const int r0 = (wave + 4 * i) * 32 + 8 * q + 4 * h;
+        *reinterpret_cast<floatx4*>(prow + r0) =
+            floatx4{acc[i][4 * q], acc[i][4 * q + 1], acc[i][4 * q + 2], acc[i][4 * q + 3]} * sc;
       }
-    }
   }
 }
 
@@ -655,9 +710,9 @@ int launch_translate_staged(const Plan& p, const float* P, float* part, int nrhs
                p.d_pair_src, p.d_pair_dst, P, part, p.n_box, p.n_pairs(), nit);
     return (int)hipGetLastError();
   }
-  const unsigned short* tb = reinterpret_cast<const unsigned short*>(p.d_table);
+  const uintx2* tb = reinterpret_cast<const uintx2*>(p.d_table);
 #define UBF_STAGED16(F16, NPROD)                                                             \
-  UBF_LAUNCH(t0, t1, (translate_staged_split_kernel<192, F16, NPROD>), grid, s, tb, p.d_items, \
+  UBF_LAUNCH(t0, t1, (translate_lattice_kernel<F16, NPROD>), grid, s, tb, p.d_items,           \
              p.d_pair_src, p.d_pair_dst, P, part, p.n_box, p.n_pairs(), nit, p.d_off_scale,    \
              p.d_box_scale)
   if (p.precision == 1) UBF_STAGED16(false, 3);

@@ -107,46 +107,42 @@ void mask_operator(const int32_t* w, int n_d, std::vector<std::complex<double>>&
     }
 }
 
+// The 16-bit image of 192-coefficient boxes by lattice difference
+// (Plan::kLatticeHalves): value sz of run (be, part, plane, al, dx, dy, lz)
+// is that of a site pair with l - s = (dx - 3, dy - 3, lz - sz). Each
+// operator value v (divided by the offset's power-of-two scale in the FP16
+// forms) is hi = round16(v), lo = round16(v - hi).
+void staged_split_image(const Plan& P, const std::vector<std::complex<double>>& G, double inv,
+                        uint16_t* out) {
+  const int np = P.precision == 3 ? 1 : 2;
+  std::fill(out, out + P.staged_split_halves(), (uint16_t)0);
+  for (int be = 0; be < 3; ++be)
+    for (int c = 0; c < 2; ++c)
+      for (int al = 0; al < 3; ++al)
+        for (int dx = -3; dx <= 3; ++dx)
+          for (int dy = -3; dy <= 3; ++dy)
+            for (int lz = 0; lz < 4; ++lz)
+              for (int sz = 0; sz < 4; ++sz) {
+                // any site pair with this difference
+                const int l = (std::max(dx, 0) * 4 + std::max(dy, 0)) * 4 + lz;
+                const int s = (std::max(-dx, 0) * 4 + std::max(-dy, 0)) * 4 + sz;
+                const std::complex<double> g = G[(size_t)(3 * l + al) * P.nu + 3 * s + be];
+                const float f = (float)((c ? g.imag() : g.real()) * inv);
+                const size_t run = (size_t)be * np * Plan::kLatticePart +
+                                   c * Plan::kLatticePlane + al * Plan::kLatticeAl +
+                                   ((dx + 3) * 7 + dy + 3) * 4 + lz;
+                const uint16_t hi = P.fp16() ? fp16_bits(f) : bf16_bits(f);
+                out[run * 4 + sz] = hi;
+                if (np == 2)
+                  out[(run + Plan::kLatticePart) * 4 + sz] =
+                      P.fp16() ? fp16_bits(f - fp16_value(hi)) : bf16_bits(f - bf16_value(hi));
+              }
+}
+
 // One offset's operator image in the table layout. FP32: planes re, im of
 // nu rows of kh floats. Split: G is rounded to FP32 first (as in the FP32
 // path), then hi = bf16(G), lo = bf16(G - hi); planes re.hi, im.hi, re.lo,
 // im.lo of nu rows of khb values. Padding columns are zero.
-// The 16-bit image of 192-coefficient boxes, in the matrix-core fragment
-// order of the staged split kernel: per 32-row block b of the real form
-// [[Gr, -Gi], [Gi, Gr]], k-step g (8 values of each K half) and part (hi,
-// then lo unless the single-product form), 64 lanes x 8 values: lane l holds
-// row 32 b + l % 32 and K half l / 32 (the real inputs for 0, the imaginary
-// ones for 1), values k = 8 g .. 8 g + 7. Each operator value v (divided by
-// the offset's power-of-two scale in the FP16 forms) is hi = round16(v),
-// lo = round16(v - hi), as in the plane layout.
-void staged_split_image(const Plan& P, const std::vector<std::complex<double>>& G, double inv,
-                        uint16_t* out) {
-  const int nb = (2 * P.nu + 31) / 32, ng = P.khb / 8, np = P.precision == 3 ? 1 : 2;
-  for (int b = 0; b < nb; ++b)
-    for (int g = 0; g < ng; ++g)
-      for (int q = 0; q < np; ++q)
-        for (int l = 0; l < 64; ++l)
-          for (int j = 0; j < 8; ++j) {
-            const int row = 32 * b + (l & 31), h = l >> 5, k = 8 * g + j;
-            double v = 0.0;
-            if (row < 2 * P.nu && k < P.nu) {
-              const bool ei = row >= P.nu;
-              const std::complex<double> c = G[(size_t)(ei ? row - P.nu : row) * P.nu + k];
-              v = !ei ? (h == 0 ? c.real() : -c.imag()) : (h == 0 ? c.imag() : c.real());
-            }
-            const float f = (float)(v * inv);
-            uint16_t bits;
-            if (P.fp16()) {
-              const uint16_t hi = fp16_bits(f);
-              bits = q == 0 ? hi : fp16_bits(f - fp16_value(hi));
-            } else {
-              const uint16_t hi = bf16_bits(f);
-              bits = q == 0 ? hi : bf16_bits(f - bf16_value(hi));
-            }
-            out[((((size_t)b * ng + g) * np + q) * 64 + l) * 8 + j] = bits;
-          }
-}
-
 void offset_image(const Plan& P, const int32_t* w, bool masked,
                   std::vector<std::complex<double>>& G, char* dst, float* scale) {
   operator_fp64(w, P.a, P.k, P.eta, P.n_d, G);

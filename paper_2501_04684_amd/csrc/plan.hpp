@@ -216,17 +216,32 @@ struct Plan {
   // k-steps, 64 lanes x 4 floats.
   bool staged() const { return !split() && nu == 192; }
   size_t staged_op_floats() const { return (size_t)((2 * nu + 31) / 32) * (kh / 4) * 256; }
-  // 16-bit operators of 192-coefficient boxes are stored in the fragment
-  // order of the staged split kernel: per 32-row block, k-step of 8 and part
-  // (hi, lo; hi only for the single-product form), 64 lanes x 8 values.
+  // 16-bit operators of 192-coefficient boxes are stored by lattice
+  // difference, not by entry, since G_w[(l,al),(s,be)] depends on l - s alone.
+  // Per source component be (the kernel takes them one after another), part
+  // (hi, lo; hi only for the single-product form) and plane (re, im), the
+  // test component al, difference (dx, dy) of 7 x 7 and test site lz have a
+  // run of the four values of the source sites along z: 29 KB per part
+  // against 295 KB for the entries in matrix-core order. Within a plane run
+  // (al, dx, dy, lz) is at kLatticeAl al + (7 dx + dy) * 4 + lz, which puts
+  // the three components of a test site 11 and 22 runs past a multiple of 32
+  // (256 bytes of LDS banks) apart.
+  static constexpr int kLatticeAl = 203;
+  static constexpr int kLatticePlane = 2 * kLatticeAl + 196;  // runs
+  static constexpr int kLatticePart = 2 * kLatticePlane;      // one component and part
+  static constexpr int kLatticeHalves = 3 * kLatticePart * 4;
   bool staged_split() const { return split() && nu == 192; }
-  size_t staged_split_halves() const {
-    return (size_t)((2 * nu + 31) / 32) * (khb / 8) * (precision == 3 ? 1 : 2) * 64 * 8;
-  }
+  size_t staged_split_halves() const { return (size_t)kLatticeHalves * (precision == 3 ? 1 : 2); }
   int pstride() const { return 2 * kh; }              // partial rows, floats
   // Box vectors of stage 1 -> 2, in floats: FP32 [re | im] halves, or in
   // split mode [re: hi, lo | im: hi, lo] BF16 runs of khb values.
   int vstride() const { return split() ? 2 * khb : 2 * kh; }
+  // Operator table as the plan's information reports it: the matrix-core
+  // operands of every offset's operator.
+  size_t operand_bytes() const {
+    if (!staged_split()) return table_bytes();
+    return table_bytes() / (kLatticeHalves * sizeof(uint16_t)) * ((size_t)2 * nu * 2 * nu * 2);
+  }
   size_t table_bytes() const {
     return split() ? table_bf16.size() * sizeof(uint16_t) : table.size() * sizeof(float);
   }
