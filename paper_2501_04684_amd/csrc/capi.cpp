@@ -206,7 +206,9 @@ std::vector<Candidate> tune_candidates(const ubf::Plan& p, int nrhs) {
       if (x.kernel == kernel && x.groups == eff) return;
     c.push_back({kernel, eff});
   };
-  for (int64_t g : grids) add(ubf::kSplitChunks, g, p.n_chunks());
+  for (int64_t g : grids)
+    if (!p.row_split() || g == grids[0] || g <= p.n_items())
+      add(ubf::kSplitChunks, g, p.grid_units());
   if (p.split()) {
     if (nrhs > 1)
       for (int64_t g : grids) add(ubf::kSplitChunksWalk, g, p.n_chunks());

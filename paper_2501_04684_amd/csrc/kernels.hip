@@ -5,6 +5,7 @@
 // per box (kh = N_u + 1 rounded up to even), which is also the K-axis
 // layout the matrix-core translation consumes.
 #include <algorithm>
+#include <type_traits>
 
 #include <hip/hip_ext.h>
 #include <hip/hip_fp16.h>
@@ -575,6 +576,185 @@ __global__ __launch_bounds__(kBlock, 2) void translate_mfma_kernel(
     }
     o0 = o1; n0 = n1; dst0 = dst1;
     o1 = o2; n1 = n2; src1 = src2; dst1 = dst2;
+  }
+}
+
+// The FP32 translation at N_u = 81 by items of up to 32 pairs of one offset
+// with the rows split over wavefronts, for plans with few pairs per offset:
+// the products of translate_mfma_kernel in the same order (the same bits),
+// but the five 32-row blocks of an item's columns go to the four wavefronts
+// of a workgroup, one of which takes two (another one with each item), the
+// last also the two leftover rows on the VALU.
+//
+// Operator and box vectors sit in LDS; the next item's vectors are loaded
+// into registers while this one computes (their indices an item earlier) and
+// written to LDS once every wavefront is done, before this item's rows leave,
+// so that neither loads nor stores are waited for; another operator is loaded
+// when the item before it is done. (Direct copies into LDS made the compiler
+// wait for all memory operations before the item's first LDS read; five
+// wavefronts with a block each left a SIMD with two of them; 16 x 16 blocks
+// divide evenly, but their products run at two thirds of the rate.) A
+// wavefront per 32 columns with all rows takes chunks of 128 columns, where
+// a wavefront without columns idles: 216-box grid (56 pairs per offset) 38 us
+// against 25 here; the 3,338-box shell (345 per offset) 76 against 83, so the
+// rule (Plan::row_split) lies between.
+template <int NU>
+__global__ __launch_bounds__(kBlock, 2) void translate_rows_kernel(
+    const float* __restrict__ table, const int32_t* __restrict__ items, int n_items,
+    const int32_t* __restrict__ pair_src, const int32_t* __restrict__ pair_dst,
+    const float* __restrict__ P, float* __restrict__ part, int64_t n_box, int64_t n_pairs) {
+  constexpr int KH = (NU + 3) & ~3;      // padded half-length, = row pitch
+  constexpr int PLANE = NU * KH;
+  constexpr int M = 2 * NU;
+  constexpr int NB = M / 32;             // 32-row blocks
+  static_assert(M % 32 == 2 && NU % 4 == 1 && NB == 5, "five blocks, two leftover rows");
+  constexpr int NG = NU / 4;             // full groups of 4 k-steps
+  constexpr int PSTR = 2 * KH;
+  constexpr int N4 = 2 * PLANE / 4;      // 16-byte units per operator
+  constexpr int OIT = (N4 + kBlock - 1) / kBlock;
+  constexpr int CU = PSTR / 4;           // units per box vector
+  constexpr int CIT = (32 * CU + kBlock - 1) / kBlock;
+  __shared__ uintx4 op4[N4];
+  __shared__ uintx4 col4[32 * CU];
+
+  const int group = xcd_chunk(blockIdx.x, gridDim.x);
+  const int ibeg = (int)((int64_t)n_items * group / gridDim.x);
+  const int iend = (int)((int64_t)n_items * (group + 1) / gridDim.x);
+  if (ibeg >= iend) return;
+  const int rhs = blockIdx.y;
+  const int t = threadIdx.x, lane = t & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int r = lane & 31, h = lane >> 5;
+  const int4* it4 = reinterpret_cast<const int4*>(items);
+  const uintx4* Pv = reinterpret_cast<const uintx4*>(P) + (int64_t)rhs * n_box * CU;
+  const uintx4* gt = reinterpret_cast<const uintx4*>(table);
+  const float* op = reinterpret_cast<const float*>(op4);
+  const float* col = reinterpret_cast<const float*>(col4) + r * PSTR + h * KH;
+  // Er rows (< NU) read Gr for h = 0 and -Gi for h = 1; Ei rows Gi and Gr
+  auto row_at = [&](int row) {
+    return (row < NU == (h == 1) ? PLANE : 0) + (row < NU ? row : row - NU) * KH;
+  };
+  auto row_sign = [&](int row) { return row < NU && h == 1 ? 0x80000000u : 0u; };
+  const float* vrow = op + row_at(M - 2);  // the leftover rows are Ei rows
+
+  // the units this thread stages of an item's columns (columns past its count
+  // repeat its last pair): source boxes, values
+  int src[CIT];
+  uintx4 cv[CIT];
+  auto sources = [&](const int4& d) {
+#pragma unroll
+    for (int i = 0; i < CIT; ++i)
+      src[i] = pair_src[d.y + min(min((t + i * kBlock) / CU, 31), d.z - 1)];
+  };
+  auto load_columns = [&]() {
+#pragma unroll
+    for (int i = 0; i < CIT; ++i)
+      cv[i] = Pv[(int64_t)src[i] * CU + min(t + i * kBlock, 32 * CU - 1) % CU];
+  };
+  auto stage_columns = [&]() {
+#pragma unroll
+    for (int i = 0; i < CIT; ++i)
+      if ((i + 1) * kBlock <= 32 * CU || t + i * kBlock < 32 * CU) col4[t + i * kBlock] = cv[i];
+  };
+  uintx4 ov[OIT];
+  auto load_operator = [&](int o) {
+#pragma unroll
+    for (int i = 0; i < OIT; ++i) ov[i] = gt[(size_t)o * N4 + min(t + i * kBlock, N4 - 1)];
+  };
+  auto stage_operator = [&]() {
+#pragma unroll
+    for (int i = 0; i < OIT; ++i)
+      if ((i + 1) * kBlock <= N4 || t + i * kBlock < N4) op4[t + i * kBlock] = ov[i];
+  };
+
+  // `n` row blocks from block b0 (LAST: and the leftover rows) of the staged
+  // item; the sums go to the rows of its pairs
+  auto block_product = [&](auto n, auto last, int b0, float* out, bool live, auto between) {
+    constexpr int N = decltype(n)::value;
+    constexpr bool LAST = decltype(last)::value;
+    const float* arow[N];
+    unsigned asgn[N];
+    floatx16 acc[N];
+    float v0 = 0.f, v1 = 0.f;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      arow[i] = op + row_at(32 * (b0 + i) + r);
+      asgn[i] = row_sign(32 * (b0 + i) + r);
+      acc[i] = floatx16{};
+    }
+#pragma unroll
+    for (int g = 0; g <= NG; ++g) {  // the last group holds one k-step
+      const floatx4 b = *reinterpret_cast<const floatx4*>(col + 4 * g);
+      floatx4 a[N];
+#pragma unroll
+      for (int i = 0; i < N; ++i) a[i] = *reinterpret_cast<const floatx4*>(arow[i] + 4 * g);
+#pragma unroll
+      for (int j = 0; j < (g < NG ? 4 : 1); ++j)
+#pragma unroll
+        for (int i = 0; i < N; ++i)
+          acc[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(
+              __uint_as_float(__float_as_uint(a[i][j]) ^ asgn[i]), b[j], acc[i], 0, 0, 0);
+      if (LAST) {
+        const floatx4 e = *reinterpret_cast<const floatx4*>(vrow + 4 * g);
+        const floatx4 f = *reinterpret_cast<const floatx4*>(vrow + KH + 4 * g);
+#pragma unroll
+        for (int j = 0; j < (g < NG ? 4 : 1); ++j) {
+          v0 = fmaf(e[j], b[j], v0);
+          v1 = fmaf(f[j], b[j], v1);
+        }
+      }
+    }
+    if (LAST) {  // the other K half
+      v0 += __shfl_xor(v0, 32, 64);
+      v1 += __shfl_xor(v1, 32, 64);
+    }
+    between();
+    if (!live) return;
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        *reinterpret_cast<floatx4*>(out + 32 * (b0 + i) + 8 * q + 4 * h) =
+            floatx4{acc[i][4 * q], acc[i][4 * q + 1], acc[i][4 * q + 2], acc[i][4 * q + 3]};
+    if (LAST && h == 0) *reinterpret_cast<float2*>(out + M - 2) = make_float2(v0, v1);
+  };
+
+  int4 d = it4[ibeg];
+  int4 dn = it4[min(ibeg + 1, iend - 1)];
+  load_operator(d.x);
+  sources(d);
+  load_columns();
+  sources(dn);
+  stage_operator();
+  stage_columns();
+  lds_reads_done_barrier();
+  for (int k = ibeg; k < iend; ++k) {
+    const bool more = k + 1 < iend;
+    const int4 d2 = it4[min(k + 2, iend - 1)];
+    const int dst = pair_dst[d.y + min(r, d.z - 1)];
+    load_columns();
+    sources(d2);
+    auto next = [&]() {  // every wavefront is done with this item: stage the next
+      if (!more) return;
+      const bool reload = dn.x != d.x;  // uniform
+      if (reload) load_operator(dn.x);
+      lds_reads_done_barrier();
+      if (reload) stage_operator();
+      stage_columns();
+    };
+    float* out = part + ((int64_t)rhs * n_pairs + dst) * PSTR;
+    const int role = (wave + k) & 3;
+    const std::integral_constant<int, 1> one;
+    const std::integral_constant<int, 2> two;
+    if (role == 0)
+      block_product(two, std::false_type{}, 0, out, r < d.z, next);
+    else if (role == 3)
+      block_product(one, std::true_type{}, 4, out, r < d.z, next);
+    else
+      block_product(one, std::false_type{}, role + 1, out, r < d.z, next);
+    if (more) lds_reads_done_barrier();  // the staged values are there
+    d = dn;
+    dn = d2;
   }
 }
 
@@ -1622,6 +1802,34 @@ __global__ __launch_bounds__(kBlock) void disaggregate_wave_kernel(
   }
 }
 
+// Stage 3 with the identity basis, y_j = E_j: one thread per real value of a
+// row, 32 of the box's rows in flight per thread, added in order (the order
+// of disaggregate_wave_kernel, whose lanes take 16 bytes of a row and 16 rows
+// at a time).
+__global__ __launch_bounds__(384) void sum_rows_kernel(const float* __restrict__ part,
+                                                       const int32_t* __restrict__ test_ptr,
+                                                       int64_t n_pairs, float2* __restrict__ y,
+                                                       int64_t n_box, int nu, int pstr) {
+  constexpr int RU = 32;
+  const int64_t j = blockIdx.x;
+  const int rhs = blockIdx.y, t = threadIdx.x;
+  if (t >= 2 * nu) return;  // no barriers below
+  const int p0 = test_ptr[j], p1 = test_ptr[j + 1];
+  const float* pr = part + (int64_t)rhs * n_pairs * pstr + t;
+  float acc = 0.f;
+  for (int p = p0; p < p1; p += RU) {
+    float v[RU];
+#pragma unroll
+    for (int i = 0; i < RU; ++i)
+      v[i] = __builtin_nontemporal_load(pr + (int64_t)min(p + i, p1 - 1) * pstr);
+#pragma unroll
+    for (int i = 0; i < RU; ++i)
+      if (p + i < p1) acc += v[i];
+  }
+  float* yj = reinterpret_cast<float*>(y + ((int64_t)rhs * n_box + j) * nu);
+  yj[t < nu ? 2 * t : 2 * (t - nu) + 1] = acc;
+}
+
 // Launch with the stage's timing events when it has them.
 #define UBF_LAUNCH(EV, KERNEL, GRID, BLOCK, STREAM, ...)                                 \
   do {                                                                                  \
@@ -1754,8 +1962,12 @@ int launch_translate(const Plan& p, const float* P, float* part, int nrhs,
   }
   switch (p.nu) {
     case 81:
-      UBF_LAUNCH(ev, translate_mfma_kernel<81>, groups, dim3(kBlock), s, p.d_table, p.d_chunks,
-                 p.d_wg_ptr, p.d_pair_src, p.d_pair_dst, P, part, p.n_box, p.n_pairs(), trash);
+      if (p.row_split())
+        UBF_LAUNCH(ev, translate_rows_kernel<81>, groups, dim3(kBlock), s, p.d_table, p.d_items,
+                   (int)p.n_items(), p.d_pair_src, p.d_pair_dst, P, part, p.n_box, p.n_pairs());
+      else
+        UBF_LAUNCH(ev, translate_mfma_kernel<81>, groups, dim3(kBlock), s, p.d_table, p.d_chunks,
+                   p.d_wg_ptr, p.d_pair_src, p.d_pair_dst, P, part, p.n_box, p.n_pairs(), trash);
       break;
     case 24:
       UBF_LAUNCH(ev, translate_mfma_kernel<24>, groups, dim3(kBlock), s, p.d_table, p.d_chunks,
@@ -1812,6 +2024,14 @@ int launch_disaggregate(const Plan& p, const Plan* rows, const float* part,
              p.n_box, nb_total, p.nu, p.kh, nrhs)
   if (from_parts && mode == 1 && small && few_rows) {
     if (rb == 1) UBF_WAVE(false, 1); else if (rb == 2) UBF_WAVE(false, 2); else UBF_WAVE(false, 4);
+  } else if (from_parts && mode == 0 &&
+             (p.nu == 192 || (p.nu == 81 && few_rows && p.n_box * nrhs <= 2048))) {
+    // a thread per value while the boxes are few (216 boxes of 83 rows: 7.0
+    // against 13.7 us, 762 of 30: 5.4 against 6.5); 16 bytes per lane moves
+    // long runs faster (464,440 box vectors: 2.75 against 3.25 ms). Both add
+    // the rows in order. Rows of 384 values do not fit one wavefront's lanes.
+    UBF_LAUNCH(ev, sum_rows_kernel, grid, dim3((2 * p.nu + 63) / 64 * 64), s, part, test_ptr,
+               n_rows, (float2*)y, p.n_box, p.nu, p.pstride());
   } else if (from_parts && mode == 0 && small && few_rows) {
     UBF_WAVE(true, 1);
   } else if (from_parts) {

@@ -363,7 +363,7 @@ void operator_fp64(const int32_t w[3], double a, double k, double eta, int n_d,
 // chunk count. Trailing groups may get empty ranges.
 void partition_groups(Plan& P, int64_t groups) {
   const int64_t nch = P.n_chunks();
-  groups = std::min<int64_t>(groups, std::max<int64_t>(nch, 1));
+  groups = std::min<int64_t>(groups, std::max<int64_t>(P.grid_units(), 1));
   groups = std::min<int64_t>((groups + 7) / 8 * 8, kMaxTranslateGroups);
   P.wg_ptr.assign(groups + 1, (int32_t)nch);
   P.wg_ptr[0] = 0;

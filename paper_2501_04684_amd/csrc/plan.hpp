@@ -205,6 +205,14 @@ struct Plan {
   int32_t n_off() const { return (int32_t)(offsets.size() / 3); }
   int64_t n_chunks() const { return (int64_t)(chunks.size() / 4); }
   int64_t n_items() const { return (int64_t)(items.size() / 4); }
+  // Work units that the persistent grid of stage 2 divides: items for the
+  // FP32 kernel that splits rows over wavefronts, else chunks. That kernel is
+  // taken where chunks of 128 pairs hold at most 2.5 items of 32 on average
+  // (both give the same bits): a workgroup spends about 10 us on an item and
+  // 21 to 24 on a chunk however full (sphere of 762 boxes, 2.2 items a chunk:
+  // 27 us against 38; 3,338-box shell, 3.7: 83 against 76).
+  bool row_split() const { return !split() && nu == 81 && 2 * n_items() <= 5 * n_chunks(); }
+  int64_t grid_units() const { return row_split() ? n_items() : n_chunks(); }
   int32_t n_groups() const { return (int32_t)wg_ptr.size() - 1; }
   int32_t n_round_groups() const { return (int32_t)wg_round_ptr.size() - 1; }
   int32_t n_scat() const { return (int32_t)scat_ptr.size() - 1; }

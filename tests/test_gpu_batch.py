@@ -226,3 +226,29 @@ def test_batch64_full_size_against_solo_and_oracle():
         ref = O.translate(P, b, w.a, w.k, w.n_d, test_boxes=sample)
         got = y[:, sl].reshape(4, len(b), 81)
         parity(got[:, sample], ref[:, sample], TOL, boxes=81, label=f"batch64 scatterer {s}")
+
+
+@pytest.mark.parametrize("nrhs", [1, 3])
+@pytest.mark.parametrize("shape", [(4, 4, 6), (3, 3, 5), (2, 2, 4)])
+def test_fp32_row_split_and_row_sums_give_the_same_bits(shape, nrhs):
+    """A small scatterer alone has few pairs per offset, so that its rows are
+    split over wavefronts, and few boxes, so that stage 3 takes a thread per
+    value; as one of 48 copies it takes neither. Items of 1 to 32 pairs."""
+    boxes = W.grid_boxes(*shape)
+    announce("fp32 row split", shape, nrhs)
+    n = len(boxes) * 81
+    x = W.complex_normal((nrhs, n), 51)
+    solo = U.FarField(boxes, 0.25, 2 * np.pi, 3, max_nrhs=nrhs)
+    assert 2 * solo.info["n_items"] <= 5 * solo.info["n_chunks"]
+    y = to_host(solo(to_dev(x)))
+    copies = 48
+    many = U.FarField(None, 0.25, 2 * np.pi, 3, max_nrhs=nrhs, scatterers=[boxes] * copies)
+    assert 2 * many.info["n_items"] > 5 * many.info["n_chunks"]
+    xm = np.tile(x, (1, copies))
+    ym = to_host(many(to_dev(xm))).reshape(nrhs, copies, n)
+    assert np.array_equal(ym, np.broadcast_to(y[:, None], ym.shape))
+    ref = O.far_mvm(x.astype(np.complex128), boxes, 0.25, 2 * np.pi, 3)
+    # FP32 sums over up to 162 x 189 terms: 2^-24 sqrt(2 * 162 + 189) ~ 1.4e-6
+    parity(y, ref, 1e-5, boxes=81, label=f"fp32 row split {shape}")
+    solo.close()
+    many.close()
