@@ -591,13 +591,14 @@ bool fft_axis(int64_t n, FftAxis& ax) {
 
 // Whether a scatterer's FULL product runs as a convolution: by estimates of
 // both ways' microseconds, fitted to both measured side by side on grids,
-// plates, shells, cubes and masks of 125 to 800 boxes, n_d 1..4.
-// Direct: 15 + 5 ns per offset (a work unit of its own) + the operators and
-// the partial rows, out and in, at 3.3 TB/s (5^3 boxes, n_d = 3: 45 us
-// direct, 55 as a convolution; 6^3: 67 and 57; the 762-box shell with 19,408
-// offsets: n_d = 1 100 and 35, n_d = 2 148 and 56, n_d = 3 525 and 108).
-// Convolution: 30 + 12 if pairs are left + the lattices, each transform in
-// and out, and the spectrum at 1.8 TB/s + the rows of the pairs left.
+// plates, shells, cubes and masks of 16 to 2,000 boxes, n_d 1..4.
+// Direct: 10 + 1.5 ns per chunk (of a tuned schedule) + the operators and the
+// partial rows, out and in, at 3.3 TB/s. Convolution: 30 (its launches) + 12
+// if pairs are left + the lattices, each transform in and out, and the
+// spectrum at 1.8 TB/s + the rows of the pairs left. Measured, direct and as
+// a convolution: n_d = 1, shells of 314 boxes 16 and 32 us, of 762 100 and
+// 35; n_d = 2, 762 boxes 148 and 56; n_d = 3, 5^3 boxes 45 and 55, 6^3 67 and
+// 57, 762 boxes (19,408 offsets) 525 and 108.
 bool convolution_pays(const Plan& P, const FftGrid& g, int64_t n_box, int64_t n_pairs,
                       int64_t n_rest, int64_t n_off) {
   const double row = 4.0 * P.pstride();
@@ -606,7 +607,7 @@ bool convolution_pays(const Plan& P, const FftGrid& g, int64_t n_box, int64_t n_
   if (8.0 * (g.zlen() + g.yzlen()) + row * (double)(n_rest + 2 * n_box) >
       0.9 * row * (double)n_pairs)
     return false;
-  const double direct = 15.0 + 5e-3 * (double)n_off +
+  const double direct = 10.0 + 1.5e-3 * ((double)n_off + (double)n_pairs / kChunk) +
                         ((double)n_off * image_bytes(P) + 2.0 * row * (double)n_pairs) / 3.3e6;
   const double lattices = 8.0 * (4.0 * g.zlen() + 4.0 * g.yzlen() + g.spec_len());
   const double conv =
