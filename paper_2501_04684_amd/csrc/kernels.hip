@@ -1562,8 +1562,8 @@ __device__ inline void apply_staged(const float2* stage, int shift, int ncol,
 // batch are read with indices clamped into that range, so the loads carry
 // no branches and all are in flight before any is used; the at most two
 // half slots at the ends are read as float2. The first batch is issued
-// before E_j is gathered, overlapping the two streams. mode 2: explicit
-// column-major T_j, one thread per output row.
+// before E_j is gathered, overlapping the two streams. (Explicit T_j:
+// disaggregate_explicit_kernel.)
 // LDS (about 54 KB) allows three workgroups per compute unit; the bound
 // lets the compiler keep a whole staged batch in registers. EQ is the
 // number of E_j rows each lane keeps (ceil(nu / 4) at most).
@@ -1571,8 +1571,8 @@ template <bool FROM_PARTS, int EQ>
 __global__ __launch_bounds__(kBlock, EQ <= 21 ? 3 : 2) void disaggregate_kernel(
     const float* __restrict__ part, const int32_t* __restrict__ test_ptr,
     int64_t n_pairs, const float2* __restrict__ Ein, const int64_t* __restrict__ nb_ptr,
-    const float2* __restrict__ S, const float2* __restrict__ T, int mode,
-    float2* __restrict__ y, int64_t n_box, int64_t nb_total, int nu, int kh) {
+    const float2* __restrict__ S, int mode, float2* __restrict__ y, int64_t n_box,
+    int64_t nb_total, int nu, int kh) {
   constexpr int LD = ((kStage + 1) / 2 + kBlock - 1) / kBlock;
   __shared__ float4 Es4[98];                  // E_j, planar padded (2*kh floats)
   __shared__ float4 stage4[(kStage + 1) / 2];  // S_j batch, or gather scratch
@@ -1591,24 +1591,6 @@ __global__ __launch_bounds__(kBlock, EQ <= 21 ? 3 : 2) void disaggregate_kernel(
   }
   const int64_t start = nb_ptr[j];
   const int64_t nb = nb_ptr[j + 1] - start;
-  if (mode == 2) {
-    gather_E<FROM_PARTS, 0>(part, test_ptr, n_pairs, Ein, j, r, n_box, nu,
-                            kh, stage4, Es4);
-    const float2* Tb = T + start * nu;
-    for (int64_t c = t; c < nb; c += kBlock) {
-      float sr = 0.f, si = 0.f;
-#pragma unroll 9
-      for (int u = 0; u < nu; ++u) {
-        const float2 v = Tb[c + nb * u];
-        const float er = Es[u], ei = Es[nu + u];
-        sr = fmaf(v.x, er, fmaf(-v.y, ei, sr));
-        si = fmaf(v.x, ei, fmaf(v.y, er, si));
-      }
-      yb[start + c] = make_float2(sr, si);
-    }
-    return;
-  }
-
   // mode 1
   const int CB = (kStage - 2) / nu;            // columns per batch
   if (nb <= 0) {
@@ -1694,6 +1676,76 @@ __global__ __launch_bounds__(kBlock, EQ <= 21 ? 3 : 2) void disaggregate_kernel(
       si += __shfl_xor(si, 2, 64);
       if (c < ncol && quarter == 0) yb[start + c0 + c] = make_float2(sr, si);
     }
+  }
+}
+
+// Explicit T_j (nb x N_u, column-major): one workgroup per (test box, NR
+// right-hand sides). Lane c of wavefront g takes row c of columns u = g,
+// g + 4, ... (each a contiguous run of nb values), all of them requested
+// before the E_j are gathered and each used for the NR right-hand sides; the
+// four wavefronts' sums of a row are added in order through LDS, so a
+// right-hand side gets the same bits whatever NR is. Boxes with more than 64
+// rows repeat this. Bound by the bytes of T_j and the partial rows: 2,168
+// boxes of 20 to 100 rows at N_u = 81 with two right-hand sides take 39.7 us;
+// one thread per output row, walking the 81 columns after E_j was gathered
+// and once per right-hand side, kept a quarter of the lanes busy (73.9 us).
+template <bool FROM_PARTS, int NR, int EQ>
+__global__ __launch_bounds__(kBlock, EQ <= 21 ? 4 : 2) void disaggregate_explicit_kernel(
+    const float* __restrict__ part, const int32_t* __restrict__ test_ptr, int64_t n_pairs,
+    const float2* __restrict__ Ein, const int64_t* __restrict__ nb_ptr,
+    const float2* __restrict__ T, float2* __restrict__ y, int64_t n_box, int64_t nb_total,
+    int nu, int kh, int nrhs) {
+  __shared__ float4 Es4[NR][98];  // E_j, planar padded (2*kh floats)
+  __shared__ float4 scratch4[kBlock];
+  __shared__ float2 sums[NR][4][64];
+  const int64_t j = blockIdx.x;
+  const int r0 = blockIdx.y * NR;
+  const int c = threadIdx.x & 63;
+  const int g = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t start = nb_ptr[j];
+  const int64_t nb = nb_ptr[j + 1] - start;
+  if (nb <= 0) return;  // uniform
+  const float2* Tb = T + start * nu;
+  float2 v[EQ];
+  auto load = [&](int64_t c0) {
+    const float2* col = Tb + min(c0 + c, nb - 1);
+#pragma unroll
+    for (int i = 0; i < EQ; ++i) v[i] = col[nb * min(g + 4 * i, nu - 1)];
+  };
+  load(0);
+#pragma unroll
+  for (int q = 0; q < NR; ++q)
+    if (r0 + q < nrhs)  // uniform
+      gather_E<FROM_PARTS, 8>(part, test_ptr, n_pairs, Ein, j, r0 + q, n_box, nu, kh, scratch4,
+                              Es4[q]);
+  for (int64_t c0 = 0; c0 < nb; c0 += 64) {
+#pragma unroll
+    for (int q = 0; q < NR; ++q) {
+      const float* Es = reinterpret_cast<const float*>(Es4[q]);
+      float sr = 0.f, si = 0.f;
+#pragma unroll
+      for (int i = 0; i < EQ; ++i) {
+        const int u = g + 4 * i;
+        if (u < nu) {  // uniform
+          const float er = Es[u], ei = Es[nu + u];
+          sr = fmaf(v[i].x, er, fmaf(-v[i].y, ei, sr));
+          si = fmaf(v[i].x, ei, fmaf(v[i].y, er, si));
+        }
+      }
+      sums[q][g][c] = make_float2(sr, si);
+    }
+    if (c0 + 64 < nb) load(c0 + 64);
+    __syncthreads();
+    if (g < NR && r0 + g < nrhs && c0 + c < nb) {
+      float2 a = sums[g][0][c];
+#pragma unroll
+      for (int w = 1; w < 4; ++w) {
+        a.x += sums[g][w][c].x;
+        a.y += sums[g][w][c].y;
+      }
+      y[(int64_t)(r0 + g) * nb_total + start + c0 + c] = a;
+    }
+    __syncthreads();  // sums are used again
   }
 }
 
@@ -1999,8 +2051,7 @@ int launch_disaggregate(const Plan& p, const Plan* rows, const float* part,
 #define UBF_DISAGG(PARTS, EQ)                                                     \
   UBF_LAUNCH(ev, (disaggregate_kernel<PARTS, EQ>), grid, dim3(kBlock), s, part,        \
              test_ptr, n_rows, (const float2*)E, p.d_nb_ptr,                 \
-             (const float2*)p.d_S, (const float2*)p.d_T, mode, (float2*)y, p.n_box,    \
-             nb_total, p.nu, p.kh)
+             (const float2*)p.d_S, mode, (float2*)y, p.n_box, nb_total, p.nu, p.kh)
   // One wavefront per box while a box has up to a few hundred partial rows
   // on average (interaction lists: tens); with thousands per box (FULL far
   // sets) the row sums want a whole workgroup per box.
@@ -2022,7 +2073,32 @@ int launch_disaggregate(const Plan& p, const Plan* rows, const float* part,
   UBF_LAUNCH(ev, (disaggregate_wave_kernel<21, IDENT, RB>), wgrid, wblock, s, part,        \
              test_ptr, n_rows, p.d_nb_ptr, (const float2*)p.d_S, (float2*)y,     \
              p.n_box, nb_total, p.nu, p.kh, nrhs)
-  if (from_parts && mode == 1 && small && few_rows) {
+  if (mode == 2) {
+    // T_j is read once for two or four right-hand sides
+    const int nr = nrhs <= 2 ? nrhs : 4;
+    const dim3 tgrid((unsigned)p.n_box, (unsigned)((nrhs + nr - 1) / nr));
+#define UBF_EXPLICIT(PARTS, NR, EQ)                                                        \
+  UBF_LAUNCH(ev, (disaggregate_explicit_kernel<PARTS, NR, EQ>), tgrid, dim3(kBlock), s, part, \
+             test_ptr, n_rows, (const float2*)E, p.d_nb_ptr, (const float2*)p.d_T, (float2*)y, \
+             p.n_box, nb_total, p.nu, p.kh, nrhs)
+#define UBF_EXPLICIT_RHS(PARTS, EQ)                                                        \
+  do {                                                                                     \
+    if (nr == 1) UBF_EXPLICIT(PARTS, 1, EQ);                                               \
+    else if (nr == 2) UBF_EXPLICIT(PARTS, 2, EQ);                                          \
+    else UBF_EXPLICIT(PARTS, 4, EQ);                                                       \
+  } while (0)
+    if (from_parts) {
+      if (p.nu <= 24) UBF_EXPLICIT_RHS(true, 6);
+      else if (small) UBF_EXPLICIT_RHS(true, 21);
+      else UBF_EXPLICIT_RHS(true, 48);
+    } else {
+      if (p.nu <= 24) UBF_EXPLICIT_RHS(false, 6);
+      else if (small) UBF_EXPLICIT_RHS(false, 21);
+      else UBF_EXPLICIT_RHS(false, 48);
+    }
+#undef UBF_EXPLICIT_RHS
+#undef UBF_EXPLICIT
+  } else if (from_parts && mode == 1 && small && few_rows) {
     if (rb == 1) UBF_WAVE(false, 1); else if (rb == 2) UBF_WAVE(false, 2); else UBF_WAVE(false, 4);
   } else if (from_parts && mode == 0 &&
              (p.nu == 192 || (p.nu == 81 && few_rows && p.n_box * nrhs <= 2048))) {

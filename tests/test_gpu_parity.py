@@ -119,6 +119,37 @@ def test_ragged_basis_with_empty_boxes():
     parity(y, ref, TOL, boxes=nb_ptr, label="ragged basis")
 
 
+@pytest.mark.parametrize("n_d,nrhs", [(1, 2), (2, 3), (3, 1), (3, 5), (4, 2)])
+def test_explicit_T_ragged_blocks(n_d, nrhs):
+    # stage 3 with explicit T_j takes 64 rows of a box at a time and one, two
+    # or four right-hand sides: blocks at and around 64 and 128 rows, empty
+    # boxes, partial and full right-hand-side blocks, from partial rows and
+    # from complex vectors
+    boxes = W.grid_boxes(4, 4, 5)
+    nu = 3 * n_d ** 3
+    nb = np.resize([0, 1, 63, 64, 65, 127, 128, 129, 5], len(boxes))
+    announce("explicit T", "n_d", n_d, "nrhs", nrhs)
+    nb_ptr, S = W.random_basis(nb, nu, 31)
+    T = W.random_basis(nb, nu, 32)[1]
+    ff = U.FarField(boxes, 0.25, 2 * np.pi, n_d, "ilist", max_nrhs=nrhs)
+    ff.set_basis(nb_ptr, to_dev(S), to_dev(T))
+    x = W.complex_normal((nrhs, int(nb_ptr[-1])), 33)
+    y = to_host(ff(to_dev(x)))
+    ref = O.far_mvm(x.astype(np.complex128), boxes, 0.25, 2 * np.pi, n_d, nb_ptr,
+                    S.astype(np.complex128), T.astype(np.complex128))
+    parity(y, ref, TOL, boxes=nb_ptr, label=f"explicit T n_d {n_d} nrhs {nrhs}")
+    for r in range(nrhs):
+        assert np.array_equal(y[r:r + 1], to_host(ff(to_dev(x[r:r + 1])))), f"rhs {r}"
+    E = W.complex_normal((nrhs, len(boxes), nu), 34)
+    out = torch.empty((nrhs, int(nb_ptr[-1])), dtype=torch.complex64, device="cuda")
+    U.disaggregate(ff.plan, to_dev(E), out)
+    want = np.concatenate([np.stack([
+        T[p * nu:q * nu].reshape(nu, q - p).T.astype(np.complex128) @ E[r, j] for r in range(nrhs)])
+        for j, (p, q) in enumerate(zip(nb_ptr[:-1], nb_ptr[1:]))], axis=1)
+    parity(to_host(out), want, TOL, boxes=nb_ptr, label="explicit T of given vectors")
+    ff.close()
+
+
 def test_stages_separately():
     w = W.config(1)
     announce("stages separately", w.name)
