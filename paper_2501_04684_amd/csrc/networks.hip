@@ -32,32 +32,43 @@ namespace {
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
 
 constexpr int kBlock = 256;
 
 // Network image of one offset, in floats. The weights are stored in the
-// matrix-core fragment order of the kernel below (sign of -W1i / -W2i
-// included), so that a wavefront's 16-byte loads of one group of four
-// k-steps are 1 KB contiguous:
-//   W1 fragments [2 HB row blocks][KH/4 groups][64 lanes][4]: row block rb of
-//     [[W1r, -W1i], [W1i, W1r]] (rows: real then imaginary hidden units, HP
-//     each), lane l = row l % 32 of the block and input half l / 32
+// matrix-core fragment order of the kernel below, so that a wavefront's
+// 16-byte loads of one group of four k-steps are 1 KB contiguous:
+//   W1 fragments [HB row blocks][KH/4 groups][64 lanes][4]: lane l = hidden
+//     unit l % 32 of the block, lanes 0..31 W1r, lanes 32..63 W1i
 //   b1 (re, im)  [2][HP]
-//   W2 fragments [OB row blocks][HP/4 groups][64 lanes][4]: row block ob of
-//     [[W2r, -W2i], [W2i, W2r]] (rows: Er then Ei, N_u each), lane l = row
-//     l % 32 and hidden half l / 32
+//   W2 fragments [ceil(N_u/32) row blocks][HP/4 groups][64 lanes][4]: lane l
+//     = output row l % 32 of the block, lanes 0..31 W2r, lanes 32..63 W2i
 //   b2 (re, im)  [2][KH]
-// Entries past the network's width, N_u or 2 N_u rows are zero.
+// Entries past the network's width or N_u are zero. One fragment [Xr | Xi]
+// serves both output parts, the inputs differ (InputHalf): [xr | -xi] gives
+// the real part, [xi | xr] the imaginary one. So the image holds every weight
+// once; with the two parts' fragments stored apart (twice the bytes) the
+// 124 MB of 316 networks of 192 inputs and 50 hidden units set the time.
+__host__ __device__ constexpr int row_blocks(int nu) { return (nu + 31) / 32; }
 __host__ __device__ constexpr int64_t image_floats(int nu, int kh, int hp) {
-  return (2LL * hp / 32) * (kh / 4) * 256 + 2LL * hp +
-         (int64_t)((2 * nu + 31) / 32) * (hp / 4) * 256 + 2LL * kh;
+  return (int64_t)(hp / 32) * (kh / 4) * 256 + 2LL * hp +
+         (int64_t)row_blocks(nu) * (hp / 4) * 256 + 2LL * kh;
 }
 
-// Value of the real form [[Xr, -Xi], [Xi, Xr]] at a row of the real
-// (im_row false) or imaginary part and column half h, from the entry c.
-__device__ inline float real_form(float2 c, bool im_row, int h) {
-  return !im_row ? (h == 0 ? c.x : -c.y) : (h == 0 ? c.y : c.x);
-}
+// Where a lane of half h reads its inputs for the real or the imaginary
+// output part (0: real inputs, 1: imaginary), and their sign bit.
+struct InputHalf {
+  int half;
+  unsigned sign;
+  __device__ InputHalf(bool im_part, int h)
+      : half(im_part ? 1 - h : h), sign(!im_part && h == 1 ? 0x80000000u : 0u) {}
+  __device__ floatx4 operator()(floatx4 v) const {
+    uintx4 u = __builtin_bit_cast(uintx4, v);
+    u ^= sign;
+    return __builtin_bit_cast(floatx4, u);
+  }
+};
 
 // Caller layout (complex64, offsets in plan order): W1 [n_off][H][NU],
 // b1 [n_off][H], W2 [n_off][NU][H], b2 [n_off][NU].
@@ -67,8 +78,8 @@ __global__ __launch_bounds__(kBlock) void network_pack_kernel(
     int64_t n_off, int nu, int kh, int hp, int hidden) {
   const int64_t nf = image_floats(nu, kh, hp);
   const int g1 = kh / 4, g2 = hp / 4, hb = hp / 32;
-  const int64_t w1 = (int64_t)(2 * hb) * g1 * 256, bb1 = 2LL * hp;
-  const int64_t w2 = (int64_t)((2 * nu + 31) / 32) * g2 * 256;
+  const int64_t w1 = (int64_t)hb * g1 * 256, bb1 = 2LL * hp;
+  const int64_t w2 = (int64_t)row_blocks(nu) * g2 * 256;
   for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < n_off * nf;
        t += (int64_t)gridDim.x * blockDim.x) {
     const int64_t o = t / nf;
@@ -78,10 +89,11 @@ __global__ __launch_bounds__(kBlock) void network_pack_kernel(
       const int j = (int)(i & 3), l = (int)((i >> 2) & 63);
       const int64_t bg = i >> 8;
       const int g = (int)(bg % g1), rb = (int)(bg / g1);
-      const int row = rb * 32 + (l & 31), h = l >> 5, k = 4 * g + j;
-      const bool im_row = row >= hp;
-      const int m = im_row ? row - hp : row;
-      if (m < hidden && k < nu) v = real_form(W1[(o * hidden + m) * nu + k], im_row, h);
+      const int m = rb * 32 + (l & 31), k = 4 * g + j;
+      if (m < hidden && k < nu) {
+        const float2 c = W1[(o * hidden + m) * nu + k];
+        v = l >> 5 ? c.y : c.x;
+      }
     } else if ((i -= w1) < bb1) {
       const int64_t plane = i / hp, m = i % hp;
       if (m < hidden) {
@@ -92,11 +104,10 @@ __global__ __launch_bounds__(kBlock) void network_pack_kernel(
       const int j = (int)(i & 3), l = (int)((i >> 2) & 63);
       const int64_t bg = i >> 8;
       const int g = (int)(bg % g2), ob = (int)(bg / g2);
-      const int row = ob * 32 + (l & 31), h = l >> 5, m = 4 * g + j;
-      if (row < 2 * nu && m < hidden) {
-        const bool im_row = row >= nu;
-        const int u = im_row ? row - nu : row;
-        v = real_form(W2[(o * nu + u) * hidden + m], im_row, h);
+      const int u = ob * 32 + (l & 31), m = 4 * g + j;
+      if (u < nu && m < hidden) {
+        const float2 c = W2[(o * nu + u) * hidden + m];
+        v = l >> 5 ? c.y : c.x;
       }
     } else {
       i -= w2;
@@ -114,16 +125,13 @@ __global__ __launch_bounds__(kBlock) void network_pack_kernel(
 // four k-steps: per group one 16-byte A load per block and lane (fragment
 // order: arow[i] points at the lane's piece of group 0, the next group is
 // 64 pieces on) and one 16-byte B load from LDS shared by all blocks;
-// consecutive MFMAs go to different blocks' accumulators. The group count
-// is G, or ng where it is given (a run-time count of at most G). The loop
-// is unrolled U times: measured best at two for the network kernel and at
-// one (rolled) for the operator-table kernel, whose three row blocks per
-// wavefront already hold three loads in flight.
-template <int PER, int G, int U>
+// consecutive MFMAs go to different blocks' accumulators. Rolled: the three
+// row blocks of a wavefront already hold three loads in flight.
+template <int PER, int G>
 __device__ inline void rowblock_products(floatx16 (&acc)[PER], const floatx4* const (&arow)[PER],
-                                         const floatx4* brow, int ng = G) {
-#pragma unroll U
-  for (int g = 0; g < ng; ++g) {
+                                         const floatx4* brow) {
+#pragma unroll 1
+  for (int g = 0; g < G; ++g) {
     const floatx4 b = brow[g];
     floatx4 a[PER];
 #pragma unroll
@@ -139,10 +147,13 @@ __device__ inline void rowblock_products(floatx16 (&acc)[PER], const floatx4* co
 // acc += A B for one row block, the loads of group g + D issued before the
 // products of group g (a ring of D + 1 register groups), so that loads stay
 // in flight across groups; the products are those of rowblock_products in
-// the same order. Measured 2 us faster than the two-way unrolled loop for
-// layer 1 of the network kernel (64.4 against 62.8 us).
+// the same order. For layer 1 of the network kernel 2 us faster than loads
+// issued with their group; layer 2, with three blocks' loads in flight, and
+// the staging of the second half gained nothing from the same (63.9 against
+// 64.5 us for the kernel at 762 boxes).
 template <int G, int D>
-__device__ inline void rowblock_pipelined(floatx16& acc, const floatx4* arow, const floatx4* brow) {
+__device__ inline void rowblock_pipelined(floatx16& acc, const floatx4* arow, const floatx4* brow,
+                                          InputHalf in) {
   static_assert(G >= D, "the prologue loads D groups");
   floatx4 a[D + 1], b[D + 1];
 #pragma unroll
@@ -156,7 +167,7 @@ __device__ inline void rowblock_pipelined(floatx16& acc, const floatx4* arow, co
       a[(g + D) % (D + 1)] = arow[(g + D) * 64];
       b[(g + D) % (D + 1)] = brow[g + D];
     }
-    const floatx4 ac = a[g % (D + 1)], bc = b[g % (D + 1)];
+    const floatx4 ac = a[g % (D + 1)], bc = in(b[g % (D + 1)]);
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk)
       acc = __builtin_amdgcn_mfma_f32_32x32x2f32(ac[kk], bc[kk], acc, 0, 0, 0);
@@ -235,13 +246,16 @@ __device__ inline bool load_item(const int32_t* __restrict__ items, int n_items,
 // One workgroup per work item (up to 32 pairs of one offset, XCD-aware);
 // at N_u = 192 the LDS of the two-pass staging lets five share a CU, so
 // that the items of a product run in one round. The source box vectors are
-// staged in LDS; wavefront w computes layer-1 row blocks w, w + 4, ... (A
-// from the network image in fragment order, B from LDS), over the k range
-// of each staging pass in turn; after a barrier it writes bias + CReLU into
-// the hidden tile, which reuses the staged vectors' LDS, and after another
-// barrier computes layer-2 row blocks w, w + 4, ... the same way. Lane l owns pair column
+// staged in LDS; wavefront w computes layer-1 row block w (A from the network
+// image in fragment order, B from LDS), over the k range of each staging pass
+// in turn; after a barrier it writes bias + CReLU into the hidden tile, which
+// reuses the staged vectors' LDS, and after another barrier computes its
+// share of the layer-2 row blocks the same way. Lane l owns pair column
 // l % 32; its 4-row pieces of each output block go to the pair's partial
-// row, whose positions are the output rows [Er | Ei].
+// row, whose positions are the output rows [Er | Ei]. Bound by the FP32
+// matrix cores and the uneven deal of items to CUs: 816 items of 192 inputs
+// and 50 hidden units are 34 us of products spread evenly, 42 us on a CU that
+// has four, and take 64.5 us (72 with an image of twice the bytes).
 template <int NU, int HB>
 __global__ __launch_bounds__(kBlock, 5) void translate_cvfcnn_kernel(
     const float* __restrict__ net, const int32_t* __restrict__ items,
@@ -251,14 +265,14 @@ __global__ __launch_bounds__(kBlock, 5) void translate_cvfcnn_kernel(
   constexpr int KH = (NU + 3) & ~3;
   constexpr int HP = 32 * HB;
   constexpr int64_t NF = image_floats(NU, KH, HP);
-  constexpr int B1_OFF = 2 * HB * (KH / 4) * 256;
+  constexpr int B1_OFF = HB * (KH / 4) * 256;
   constexpr int W2_OFF = B1_OFF + 2 * HP;
-  constexpr int B2_OFF = W2_OFF + ((2 * NU + 31) / 32) * (HP / 4) * 256;
+  constexpr int B2_OFF = W2_OFF + row_blocks(NU) * (HP / 4) * 256;
   constexpr int PASSES = staging_passes(KH);
   constexpr int KP = KH / PASSES;
   constexpr int XP = 2 * KP + 4;     // LDS pitch of a staged box vector
   constexpr int HPT = 2 * HP + 4;    // LDS pitch of a hidden column
-  constexpr int OB = (2 * NU + 31) / 32;
+  constexpr int OB = 2 * row_blocks(NU);
   constexpr int PSTR = 2 * KH;
   // the hidden tile reuses the staged vectors' LDS once layer 1 has read them
   constexpr int TILE = 32 * (XP > HPT ? XP : HPT);
@@ -288,20 +302,17 @@ __global__ __launch_bounds__(kBlock, 5) void translate_cvfcnn_kernel(
   float m2 = 0.f, s = 0.f, inv_s = 0.f;
   __syncthreads();
 
-  // layer 1: A row = hidden unit m of part (0: real, 1: imaginary); lane
-  // half h multiplies the real (h = 0) or imaginary (h = 1) inputs. Row
-  // block rb = wave (2 HB <= 4 blocks, so at most one per wavefront).
+  // layer 1: row block rb = wave (2 HB <= 4 blocks, so at most one per
+  // wavefront): hidden units 32 (rb / 2) .. + 31, real (rb even) or imaginary
+  // part; the two parts read the same fragments.
   {
-    constexpr int NB = 2 * HB, PER1 = (NB + 3) / 4;
-    static_assert(PER1 == 1, "one layer-1 row block per wavefront");
-    floatx16 acc[PER1];
-    const floatx4* arow[PER1];
-#pragma unroll
-    for (int i = 0; i < PER1; ++i) {
-      const int rb = min(wave + 4 * i, NB - 1);
-      arow[i] = reinterpret_cast<const floatx4*>(no) + (size_t)rb * (KH / 4) * 64 + lane;
-      acc[i] = floatx16{};
-    }
+    constexpr int NB = 2 * HB;
+    static_assert(NB <= 4, "one layer-1 row block per wavefront");
+    const bool im = wave & 1;
+    const InputHalf in(im, h);
+    floatx16 acc = floatx16{};
+    const floatx4* arow = reinterpret_cast<const floatx4*>(no) +
+                          (size_t)(min(wave, NB - 1) / 2) * (KH / 4) * 64 + lane;
 #pragma unroll
     for (int pass = 0; pass < PASSES; ++pass) {
       if (pass > 0) {
@@ -309,12 +320,10 @@ __global__ __launch_bounds__(kBlock, 5) void translate_cvfcnn_kernel(
         stager.stage(xs4, Pr, ncol, pass);
         __syncthreads();
       }
-      const floatx4* ap[PER1];
-#pragma unroll
-      for (int i = 0; i < PER1; ++i) ap[i] = arow[i] + pass * (KP / 4) * 64;
       if (wave < NB)  // wave-uniform
-        rowblock_pipelined<KP / 4, 3>(acc[0], ap[0],
-                                      reinterpret_cast<const floatx4*>(xs + r * XP + h * KP));
+        rowblock_pipelined<KP / 4, 3>(
+            acc, arow + pass * (KP / 4) * 64,
+            reinterpret_cast<const floatx4*>(xs + r * XP + in.half * KP), in);
 #pragma unroll
       for (int u = mj; u < KP; u += 8) {
         if (pass * KP + u < NU) {
@@ -330,62 +339,82 @@ __global__ __launch_bounds__(kBlock, 5) void translate_cvfcnn_kernel(
     __syncthreads();  // every wavefront is done with the staged vectors
     s = col_scale[r];
     inv_s = s > 0.f ? 1.f / s : 0.f;
-#pragma unroll
-    for (int i = 0; i < PER1; ++i) {
-      const int rb = wave + 4 * i;
-      if (rb >= NB) continue;
-      const int hpart = rb / HB, m0 = (rb % HB) * 32;
-      const float* b1 = bias + hpart * HP + m0;
+    if (wave < NB) {
+      const int m0 = wave / 2 * 32, part0 = im ? HP : 0;
+      const float* b1 = bias + part0 + m0;
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         floatx4 v;
 #pragma unroll
         for (int jj = 0; jj < 4; ++jj) {
           const int row = 8 * q + 4 * h + jj;
-          const float z = fmaf(acc[i][4 * q + jj], inv_s, b1[row]);
+          const float z = fmaf(acc[4 * q + jj], inv_s, b1[row]);
           v[jj] = (m0 + row < hidden) ? fmaxf(z, 0.f) : 0.f;
         }
-        *reinterpret_cast<floatx4*>(hs + r * HPT + rb * 32 + 8 * q + 4 * h) = v;
+        *reinterpret_cast<floatx4*>(hs + r * HPT + part0 + m0 + 8 * q + 4 * h) = v;
       }
     }
   }
   __syncthreads();
 
-  // layer 2: A row = output row of [Er | Ei]; row blocks ob = wave + 4 i
+  // layer 2: row blocks ob = PER wave + i: output rows 32 (ob / 2) .. + 31
+  // of Er (ob even) or Ei, so a wavefront's neighbours share fragments
   float* prow = part + ((int64_t)rhs * n_pairs + dst) * PSTR;
   {
     constexpr int PER = (OB + 3) / 4;
     floatx16 acc[PER];
     const floatx4* arow[PER];
+    const floatx4* brow[PER];
+    unsigned sign[PER];
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
-      const int ob = min(wave + 4 * i, OB - 1);
-      arow[i] = reinterpret_cast<const floatx4*>(no + W2_OFF) + (size_t)ob * (HP / 4) * 64 + lane;
+      const int ob = min(PER * wave + i, OB - 1);
+      const InputHalf in(ob & 1, h);
+      arow[i] = reinterpret_cast<const floatx4*>(no + W2_OFF) + (size_t)(ob / 2) * (HP / 4) * 64 +
+                lane;
+      brow[i] = reinterpret_cast<const floatx4*>(hs + r * HPT + in.half * HP);
+      sign[i] = in.sign;
       acc[i] = floatx16{};
     }
     // hidden units past the network's width are zero in the hidden tile and
     // in W2: the k loop stops at the last group holding a unit
-    rowblock_products<PER, HP / 4, 2>(acc, arow,
-                                   reinterpret_cast<const floatx4*>(hs + r * HPT + h * HP),
-                                   (hidden + 3) / 4);
+    const int ng = (hidden + 3) / 4;
+    for (int g = 0; g < ng; ++g) {
+      floatx4 a[PER], b[PER];
+#pragma unroll
+      for (int i = 0; i < PER; ++i) {
+        a[i] = arow[i][g * 64];
+        uintx4 bits = __builtin_bit_cast(uintx4, brow[i][g]);
+        bits ^= sign[i];
+        b[i] = __builtin_bit_cast(floatx4, bits);
+      }
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+        for (int i = 0; i < PER; ++i)
+          acc[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i][kk], b[i][kk], acc[i], 0, 0, 0);
+    }
     if (live) {
 #pragma unroll
       for (int i = 0; i < PER; ++i) {
-        const int ob = wave + 4 * i;
+        const int ob = PER * wave + i;
         if (ob >= OB) continue;
+        const bool im = ob & 1;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-          const int r0 = ob * 32 + 8 * q + 4 * h;  // first of this lane's 4 rows
-          if (r0 < 2 * NU) {
+          const int u0 = (ob / 2) * 32 + 8 * q + 4 * h;  // first of this lane's 4 rows
+          const float* b2 = bias + 2 * HP + (im ? KH : 0) + u0;
+          float* e = prow + (im ? NU : 0) + u0;
+          if (NU % 4 == 0) {
+            if (u0 >= NU) continue;
             floatx4 v;
 #pragma unroll
-            for (int jj = 0; jj < 4; ++jj) {
-              const int orow = r0 + jj;
-              const float b = orow < NU ? bias[2 * HP + orow]
-                                        : (orow < 2 * NU ? bias[2 * HP + KH + orow - NU] : 0.f);
-              v[jj] = s * (acc[i][4 * q + jj] + b);
-            }
-            *reinterpret_cast<floatx4*>(prow + r0) = v;
+            for (int jj = 0; jj < 4; ++jj) v[jj] = s * (acc[i][4 * q + jj] + b2[jj]);
+            *reinterpret_cast<floatx4*>(e) = v;
+          } else {
+#pragma unroll
+            for (int jj = 0; jj < 4; ++jj)
+              if (u0 + jj < NU) e[jj] = s * (acc[i][4 * q + jj] + b2[jj]);
           }
         }
       }
@@ -444,7 +473,7 @@ __global__ __launch_bounds__(kBlock, 4) void translate_staged_kernel(
     const floatx4* ap[PER];
 #pragma unroll
     for (int i = 0; i < PER; ++i) ap[i] = arow[i] + pass * (KP / 4) * 64;
-    rowblock_products<PER, KP / 4, 1>(acc, ap, reinterpret_cast<const floatx4*>(xs + r * XP + h * KP));
+    rowblock_products<PER, KP / 4>(acc, ap, reinterpret_cast<const floatx4*>(xs + r * XP + h * KP));
   }
   if (live) {
 #pragma unroll
@@ -465,7 +494,6 @@ __global__ __launch_bounds__(kBlock, 4) void translate_staged_kernel(
 // 16-bit matrix-core product on 8 values per lane (FP32 accumulation).
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 halfx8 __attribute__((ext_vector_type(8)));
-typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
 typedef unsigned uintx2 __attribute__((ext_vector_type(2)));
 template <bool F16>
 __device__ inline floatx16 mfma16(uintx4 a, uintx4 b, floatx16 c) {

@@ -97,6 +97,22 @@ def test_nd4_paper_shape(hidden):
         ff.close()
 
 
+@pytest.mark.parametrize("n_d,hidden", [(2, 32), (2, 61), (4, 5), (4, 32)])
+def test_image_shapes(n_d, hidden):
+    # both hidden-block counts where the output rows end inside a block (24)
+    # and where two row blocks fall to a wavefront's share of twelve (192)
+    boxes = W.grid_boxes(4, 4, 5)
+    nu = 3 * n_d ** 3
+    announce("cvfcnn image", "n_d", n_d, "hidden", hidden)
+    ff, nets = _field(boxes, 0.25, 2 * np.pi, n_d, "ilist", hidden, seed=17, max_nrhs=2)
+    x = W.complex_normal((2, len(boxes) * nu), seed=19)
+    y = to_host(ff(to_dev(x)))
+    P = x.reshape(2, len(boxes), nu).astype(np.complex128)
+    ref = C.translate_cvfcnn(P, boxes, nets, "ilist").reshape(2, -1)
+    parity(y, ref, TOL, boxes=nu, label=f"networks n_d={n_d} hidden {hidden}")
+    ff.close()
+
+
 @pytest.mark.parametrize("networks", [True, False])
 def test_nd4_degenerate_and_single_pair(networks):
     # 192 coefficients per box, networks or the operator table staged in
