@@ -214,99 +214,152 @@ __global__ __launch_bounds__(kBlock) void unpack_kernel(
 
 // ---------------------------------------------------------------- stage 1
 
-// One workgroup per (box, block of RB right-hand sides). Thread t owns row
-// u = t % nu of S_i and column group g = t / nu, so thread t reads S_i
-// element t + nu*G*it: the whole block streams S_i contiguously, once for
-// the RB vectors. The G column-group partial sums are reduced through LDS.
-template <int RB>
+// Two consecutive complex values of S, 8-byte aligned, read once per stage.
+typedef float floatx4u __attribute__((ext_vector_type(4), aligned(8)));
+template <bool NT>
+__device__ inline floatx4 load_pair(const float2* p) {
+  const floatx4u* q = reinterpret_cast<const floatx4u*>(p);
+  return NT ? __builtin_nontemporal_load(q) : *q;
+}
+
+// One workgroup per (box, block of RB right-hand sides). The block S_i
+// (N_u x nb values, column-major) is read as one stream of 16-byte pairs of
+// values, once for the RB vectors: NT threads take a pair each per step,
+// NT the largest multiple <= 256 for which a step is a whole number C of
+// columns, so that the two rows of a thread's pairs never change. The loads of
+// UN steps are in flight together, the first ones before x is staged in LDS
+// (XC columns at a time). The C columns' sums of a row are added through LDS,
+// the same way whatever RB is, and wavefront q finishes vector q. Bound by the
+// bytes of S_i: 3,338 boxes of 81 functions take 35 us (5.0 TB/s; 30 where S
+// passes the caches by, as a plain read of as many bytes does), four vectors
+// 47 us, 25,876 boxes 227 us (6.0 TB/s). Reading 8 bytes a lane, with x read
+// from memory beside them, took 44.5, 57.5 and 309 us.
+template <int RB, int UN, bool NT>
 __global__ __launch_bounds__(kBlock) void aggregate_kernel(
     const float2* __restrict__ x, const int64_t* __restrict__ nb_ptr,
     const float2* __restrict__ S, float* __restrict__ P, int64_t n_box,
     int64_t nb_total, int nu, int kh, int khb, int mode, float* __restrict__ box_scale,
     int nrhs) {
-  __shared__ float2 red[RB][kBlock];
-  __shared__ float wmax[kBlock / 64];
+  constexpr int XC = 256;  // columns of x in LDS
+  __shared__ float2 red[RB][2 * kBlock];
+  __shared__ float2 xs[RB][XC];
   const int64_t i = blockIdx.x;
   const int r0 = blockIdx.y * RB;
   const int nr = min(RB, nrhs - r0);  // >= 1
   const int t = threadIdx.x;
-  const int G = kBlock / nu;
-  const int u = t % nu, g = t / nu;
+  const int unit = (nu & 1) ? nu : nu / 2;  // pairs after which the rows repeat
+  const int nt = kBlock / unit * unit;
+  const int C = 2 * nt / nu;  // columns per step, <= 170
+  // this thread's pair of a step: rows ua, ub of columns ga, gb
+  const int ga = 2 * t / nu, gb = (2 * t + 1) / nu;
   const int64_t start = nb_ptr[i];
   const int64_t nb = nb_ptr[i + 1] - start;
   const float2* Sb = S + start * nu;
   const float2* xb = x + (int64_t)r0 * nb_total + start;
-  float ar[RB], ai[RB];
+  const int64_t np = nb * nu / 2;  // whole pairs
+  const int64_t steps = t < nt ? (np + nt - 1) / nt : 0;
+  const int64_t tile_steps = XC / C;  // >= 1
+  float ar[RB], ai[RB], br[RB], bi[RB];
 #pragma unroll
-  for (int q = 0; q < RB; ++q) ar[q] = ai[q] = 0.f;
-  if constexpr (RB == 1) {
-    if (g < G) {
-#pragma unroll 9
-      for (int64_t c = g; c < nb; c += G) {
-        const float2 s = Sb[c * nu + u];
-        const float2 xv = xb[c];
-        ar[0] = fmaf(s.x, xv.x, ar[0]);
-        ar[0] = fmaf(-s.y, xv.y, ar[0]);
-        ai[0] = fmaf(s.x, xv.y, ai[0]);
-        ai[0] = fmaf(s.y, xv.x, ai[0]);
-      }
-    }
-  } else {
-    // the block's x values go through LDS, 256 columns at a time, so that
-    // the loop's only global loads are those of S_i; vectors past the last
-    // one repeat it, and their sums are not stored
-    __shared__ float2 xs[RB][kBlock];
-    for (int64_t c0 = 0; c0 < nb; c0 += kBlock) {
-      const int64_t cn = min<int64_t>(kBlock, nb - c0);
-      if (c0 > 0) __syncthreads();  // every thread is done with the last tile
+  for (int q = 0; q < RB; ++q) ar[q] = ai[q] = br[q] = bi[q] = 0.f;
+  floatx4 v[UN];
+  auto load = [&](int64_t s0) {
 #pragma unroll
-      for (int q = 0; q < RB; ++q)
-        if (t < cn) xs[q][t] = xb[(int64_t)min(q, nr - 1) * nb_total + c0 + t];
-      __syncthreads();
-      if (g < G) {
-#pragma unroll 5
-        for (int c = g; c < cn; c += G) {
-          const float2 s = Sb[(c0 + c) * nu + u];
+    for (int k = 0; k < UN; ++k)
+      v[k] = load_pair<NT>(Sb + 2 * min((s0 + k) * nt + t, np - 1));
+  };
+  if (np > 0) load(0);  // uniform
+  for (int64_t c0 = 0, s0 = 0; c0 < nb; c0 += tile_steps * C) {
+    const int cn = (int)min(tile_steps * C, nb - c0);
+    if (c0 > 0) __syncthreads();  // every thread is done with the last columns
+#pragma unroll
+    for (int q = 0; q < RB; ++q)  // vectors past the last one repeat it (not stored)
+      if (t < cn) xs[q][t] = xb[(int64_t)min(q, nr - 1) * nb_total + c0 + t];
+    __syncthreads();
+    const int64_t s1 = min(s0 + tile_steps, steps);
+    int ca = ga, cb = gb;
+    for (; s0 < s1; s0 += UN) {
+#pragma unroll
+      for (int k = 0; k < UN; ++k) {
+        if (s0 + k < s1 && (s0 + k) * nt + t < np) {
 #pragma unroll
           for (int q = 0; q < RB; ++q) {
-            const float2 xv = xs[q][c];
-            ar[q] = fmaf(s.x, xv.x, ar[q]);
-            ar[q] = fmaf(-s.y, xv.y, ar[q]);
-            ai[q] = fmaf(s.x, xv.y, ai[q]);
-            ai[q] = fmaf(s.y, xv.x, ai[q]);
+            const float2 xa = xs[q][ca], xc = xs[q][cb];
+            ar[q] = fmaf(v[k].x, xa.x, ar[q]);
+            ar[q] = fmaf(-v[k].y, xa.y, ar[q]);
+            ai[q] = fmaf(v[k].x, xa.y, ai[q]);
+            ai[q] = fmaf(v[k].y, xa.x, ai[q]);
+            br[q] = fmaf(v[k].z, xc.x, br[q]);
+            br[q] = fmaf(-v[k].w, xc.y, br[q]);
+            bi[q] = fmaf(v[k].z, xc.y, bi[q]);
+            bi[q] = fmaf(v[k].w, xc.x, bi[q]);
           }
         }
+        ca += C;
+        cb += C;
       }
+      // the next steps, of the next columns where these are used up
+      if (min(s0 + UN, s1) < steps) load(min(s0 + UN, s1));
+    }
+    s0 = s1;
+  }
+  if (np * 2 < nb * nu && t == np % nt) {  // the last value of an odd block
+    const float2 s = Sb[2 * np];
+#pragma unroll
+    for (int q = 0; q < RB; ++q) {
+      const float2 xv = xb[(int64_t)min(q, nr - 1) * nb_total + nb - 1];
+      ar[q] = fmaf(s.x, xv.x, ar[q]);
+      ar[q] = fmaf(-s.y, xv.y, ar[q]);
+      ai[q] = fmaf(s.x, xv.y, ai[q]);
+      ai[q] = fmaf(s.y, xv.x, ai[q]);
     }
   }
 #pragma unroll
-  for (int q = 0; q < RB; ++q) red[q][t] = make_float2(ar[q], ai[q]);
+  for (int q = 0; q < RB; ++q)
+    *reinterpret_cast<float4*>(&red[q][2 * t]) = make_float4(ar[q], ai[q], br[q], bi[q]);
   __syncthreads();
-  const int len = mode ? khb : kh;  // <= kBlock: one coefficient per thread
-  for (int q = 0; q < nr; ++q) {
-    const int r = r0 + q;
-    float* Pb = P + ((int64_t)r * n_box + i) * (mode ? 2 * khb : 2 * kh);
-    float sr = 0.f, si = 0.f;
-    if (t < nu)
-      for (int gg = 0; gg < G; ++gg) {
-        sr += red[q][gg * nu + t].x;
-        si += red[q][gg * nu + t].y;
-      }
-    float inv = 1.f;
-    if (mode == 2) {  // FP16: the box vector's scale from its largest component
-      float m = fmaxf(fabsf(sr), fabsf(si));
+  // many columns per step (small N_u): halve them until a few are left
+  int G = C;
+  while (G > 16) {
+    const int half = (G + 1) / 2;
 #pragma unroll
-      for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
-      if ((t & 63) == 0) wmax[t >> 6] = m;
-      __syncthreads();
-      m = fmaxf(fmaxf(wmax[0], wmax[1]), fmaxf(wmax[2], wmax[3]));
-      if (q + 1 < nr) __syncthreads();  // wmax is reused by the next vector
-      const float sc = box_scale_for(m);
-      inv = 1.f / sc;
-      if (t == 0) box_scale[(int64_t)r * n_box + i] = sc;
-    }
-    if (t < len) put_coef(Pb, t, sr, si, kh, khb, mode, inv);
+    for (int q = 0; q < RB; ++q)
+      for (int e = t; e < (G - half) * nu; e += kBlock) {
+        red[q][e].x += red[q][e + half * nu].x;
+        red[q][e].y += red[q][e + half * nu].y;
+      }
+    __syncthreads();
+    G = half;
   }
+  // wavefront q finishes vector q
+  const int q = t >> 6, l = t & 63;
+  if (q >= nr) return;
+  const int r = r0 + q;
+  float* Pb = P + ((int64_t)r * n_box + i) * (mode ? 2 * khb : 2 * kh);
+  float sr[3], si[3], m = 0.f;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    const int u = l + 64 * k;
+    sr[k] = si[k] = 0.f;
+    if (u < nu)
+      for (int gg = 0; gg < G; ++gg) {
+        sr[k] += red[q][gg * nu + u].x;
+        si[k] += red[q][gg * nu + u].y;
+      }
+    m = fmaxf(m, fmaxf(fabsf(sr[k]), fabsf(si[k])));
+  }
+  float inv = 1.f;
+  if (mode == 2) {  // FP16: the box vector's scale from its largest component
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
+    const float sc = box_scale_for(m);
+    inv = 1.f / sc;
+    if (l == 0) box_scale[(int64_t)r * n_box + i] = sc;
+  }
+  const int len = mode ? khb : kh;  // <= 192
+#pragma unroll
+  for (int k = 0; k < 3; ++k)
+    if (l + 64 * k < len) put_coef(Pb, l + 64 * k, sr[k], si[k], kh, khb, mode, inv);
 }
 
 // ---------------------------------------------------------------- stage 2
@@ -1749,31 +1802,51 @@ __global__ __launch_bounds__(kBlock, EQ <= 21 ? 4 : 2) void disaggregate_explici
   }
 }
 
-// Stage 3 with one wavefront per box (E_j from the partial rows, N_u <= 84;
-// T_j = S_j^T, or y_j = E_j with IDENT): no workgroup barriers on the box's
-// path. The wavefront serves a block of up to RB right-hand sides. For each,
-// lane l < R4 sums float4 l of the box's partial rows (16 rows in flight);
-// the sums go to the wavefront's own LDS slot (672 bytes per vector) and
-// come back as this lane's rows of E_j; then four columns of S_j per pass,
-// 16 lanes per column, read from global memory once for the RB vectors and
-// reduced across the 16 lanes by shuffles. Same arithmetic as
-// disaggregate_kernel except the order of the sums.
-template <int EQ, bool IDENT, int RB>
+// Sum over a row of 16 lanes, in every lane (rotations by 8, 4, 2, 1).
+template <int N>
+__device__ inline float add_rotated(float v) {
+  const int w = __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x120 + N, 0xF, 0xF,
+                                            false);
+  return v + __builtin_bit_cast(float, w);
+}
+__device__ inline float row_sum(float v) {
+  return add_rotated<1>(add_rotated<2>(add_rotated<4>(add_rotated<8>(v))));
+}
+
+// Stage 3 with one wavefront per (box, right-hand side) (E_j from the partial
+// rows, N_u <= 84; T_j = S_j^T, or y_j = E_j with IDENT). Lane l < R4 sums
+// float4 l of the box's partial rows (16 rows in flight); the sums go to an
+// LDS slot (672 bytes per vector) and come back as this lane's rows of E_j;
+// then four columns of S_j per pass, 16 lanes per column, summed across the
+// 16 lanes. With RB = 1 a wavefront has a box to itself and no workgroup
+// barrier is on its path. With RB = 2 or 4 a workgroup of RB wavefronts takes
+// a box and a block of RB right-hand sides: each wavefront sums one's rows,
+// then takes every RB-th pass over the columns for all of them, so that S_j
+// is read once. Same arithmetic as disaggregate_kernel except the order of
+// the sums, and the same order for every RB. Bound by the bytes of the
+// partial rows and S_j: 3,338 boxes with 81 functions each take 40.8 us
+// (6.3 TB/s), 25,876 boxes 488 us (5.2 TB/s; 520 when S_j was read 8 bytes a
+// lane and through the caches). Four vectors of the 3,338 boxes take 80.6 us;
+// with one wavefront summing the rows of all four in turn they took 102.
+// Deeper prefetching of S_j gained nothing.
+template <int PQ, bool IDENT, int RB>
 __global__ __launch_bounds__(kBlock) void disaggregate_wave_kernel(
     const float* __restrict__ part, const int32_t* __restrict__ test_ptr, int64_t n_pairs,
     const int64_t* __restrict__ nb_ptr, const float2* __restrict__ S, float2* __restrict__ y,
     int64_t n_box, int64_t nb_total, int nu, int kh, int nrhs) {
   constexpr int RU = 16;  // partial rows in flight per lane
-  __shared__ float4 Es4[kBlock / 64][RB][42];
+  __shared__ float4 Es4[RB == 1 ? kBlock / 64 : RB][42];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int64_t j = (int64_t)blockIdx.x * (blockDim.x >> 6) + wave;
-  if (j >= n_box) return;  // whole wavefronts; no barriers below
+  const int64_t j = RB == 1 ? (int64_t)blockIdx.x * (blockDim.x >> 6) + wave : blockIdx.x;
+  if (j >= n_box) return;  // whole wavefronts (RB > 1: never); no barriers below
   const int r0 = blockIdx.y * RB;
   const int nr = min(RB, nrhs - r0);  // >= 1
   const int R4 = kh / 2;  // float4 per partial row (<= 42)
   const int p0 = test_ptr[j], p1 = test_ptr[j + 1];
-  for (int qr = 0; qr < nr; ++qr) {
-    const int r = r0 + qr;
+  const int64_t start = IDENT ? 0 : nb_ptr[j];
+  const int64_t nb = IDENT ? 0 : nb_ptr[j + 1] - start;
+  if (RB == 1 || wave < nr) {
+    const int r = RB == 1 ? r0 : r0 + wave;
     const float4* pr = reinterpret_cast<const float4*>(part) + (int64_t)r * n_pairs * R4;
     if (lane < R4) {
       float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -1791,63 +1864,77 @@ __global__ __launch_bounds__(kBlock) void disaggregate_wave_kernel(
             acc.w += v[i].w;
           }
       }
-      if (IDENT) {  // y_j = E_j: this lane's four positions of [Er | Ei]
-        float2* yj = y + (int64_t)r * nb_total + j * nu;
-        const float a4[4] = {acc.x, acc.y, acc.z, acc.w};
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const int pos = 4 * lane + k;
-          if (pos < nu) yj[pos].x = a4[k];
-          else if (pos < 2 * nu) yj[pos - nu].y = a4[k];
-        }
-      } else {
-        Es4[wave][qr][lane] = acc;
-      }
+      Es4[wave][lane] = acc;
     }
   }
-  if (IDENT) return;
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  if constexpr (RB == 1) {
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  } else {
+    __syncthreads();
+  }
+  if (IDENT) {  // y_j = E_j
+    const float* Es = reinterpret_cast<const float*>(Es4[wave]);
+    float2* yj = y + (int64_t)r0 * nb_total + j * nu;
+    for (int u = lane; u < nu; u += 64) yj[u] = make_float2(Es[u], Es[nu + u]);
+    return;
+  }
   // 16 lanes per column: lane group cs = lane / 16 takes column c0 + cs and
-  // lane q = lane % 16 rows q, q + 16, ...; each load instruction reads four
-  // whole 128-byte lines of S_j
-  constexpr int RQ = (EQ * 4 + 15) / 16;  // rows per lane (N_u <= 4 EQ)
+  // lane q = lane % 16 the row pairs q, q + 16, ... (16 bytes each); the next
+  // pass's columns are requested before this one's are used. The last pair of
+  // an odd N_u is read one row early (inside the column) and its first value
+  // dropped.
   const int q = lane & 15, cs = lane >> 4;
-  float er[RB][RQ], ei[RB][RQ];
+  const int np = (nu + 1) / 2;
+  const bool odd = nu & 1;
+  float er[RB][2 * PQ], ei[RB][2 * PQ];
 #pragma unroll
   for (int qr = 0; qr < RB; ++qr) {
     // vectors past the last one repeat it; their results are not stored
-    const float* Es = reinterpret_cast<const float*>(Es4[wave][min(qr, nr - 1)]);
+    const float* Es = reinterpret_cast<const float*>(Es4[RB == 1 ? wave : min(qr, nr - 1)]);
 #pragma unroll
-    for (int i = 0; i < RQ; ++i) {
-      const int u = min(q + 16 * i, nu - 1);
+    for (int i = 0; i < 2 * PQ; ++i) {
+      const int u = min(2 * (q + 16 * (i / 2)) + (i & 1), nu - 1);
       er[qr][i] = Es[u];
       ei[qr][i] = Es[nu + u];
     }
   }
-  const int64_t start = nb_ptr[j];
-  const int64_t nb = nb_ptr[j + 1] - start;
   const float2* Sb = S + start * nu;
-  for (int64_t c0 = 0; c0 < nb; c0 += 4) {
-    const int64_t c = c0 + cs;
-    const float2* col = Sb + min(c, nb - 1) * nu;
-    float2 sv[RQ];
+  const int64_t passes = (nb + 3) / 4;
+  floatx4 next[PQ];
+  auto load = [&](int64_t pass) {
+    const float2* col = Sb + min(4 * pass + cs, nb - 1) * nu;
 #pragma unroll
-    for (int i = 0; i < RQ; ++i) sv[i] = col[min(q + 16 * i, nu - 1)];
+    for (int i = 0; i < PQ; ++i) next[i] = load_pair<true>(col + min(2 * (q + 16 * i), nu - 2));
+  };
+  constexpr int W = RB;  // wavefronts on this machine's columns
+  const int first = RB == 1 ? 0 : wave;
+  if (first < passes) load(first);
+  for (int64_t pass = first; pass < passes; pass += W) {
+    const int64_t c = 4 * pass + cs;
+    floatx4 sv[PQ];
+#pragma unroll
+    for (int i = 0; i < PQ; ++i) sv[i] = next[i];
+    if (pass + W < passes) load(pass + W);
 #pragma unroll
     for (int qr = 0; qr < RB; ++qr) {
       float sr = 0.f, si = 0.f;
 #pragma unroll
-      for (int i = 0; i < RQ; ++i)
-        if (q + 16 * i < nu) {
-          sr = fmaf(sv[i].x, er[qr][i], fmaf(-sv[i].y, ei[qr][i], sr));
-          si = fmaf(sv[i].x, ei[qr][i], fmaf(sv[i].y, er[qr][i], si));
+      for (int i = 0; i < PQ; ++i) {
+        const int p = q + 16 * i;
+        if (p < np) {
+          const bool last = odd && p == np - 1;
+          const float ax = last ? sv[i].z : sv[i].x, ay = last ? sv[i].w : sv[i].y;
+          sr = fmaf(ax, er[qr][2 * i], fmaf(-ay, ei[qr][2 * i], sr));
+          si = fmaf(ax, ei[qr][2 * i], fmaf(ay, er[qr][2 * i], si));
+          if (!last) {
+            sr = fmaf(sv[i].z, er[qr][2 * i + 1], fmaf(-sv[i].w, ei[qr][2 * i + 1], sr));
+            si = fmaf(sv[i].z, ei[qr][2 * i + 1], fmaf(sv[i].w, er[qr][2 * i + 1], si));
+          }
         }
-#pragma unroll
-      for (int o = 8; o > 0; o >>= 1) {
-        sr += __shfl_xor(sr, o, 64);
-        si += __shfl_xor(si, o, 64);
       }
+      sr = row_sum(sr);
+      si = row_sum(si);
       if (qr < nr && c < nb && q == 0)
         y[(int64_t)(r0 + qr) * nb_total + start + c] = make_float2(sr, si);
     }
@@ -1938,13 +2025,27 @@ int launch_aggregate(const Plan& p, const void* x, float* P, int nrhs, void* str
   if (!p.has_basis) return launch_pack(p, x, P, nrhs, stream, ev);
   // S_i is read once per block of right-hand sides
   const int mode = p.fp16() ? 2 : (p.split() ? 1 : 0);
-#define UBF_AGG(RB)                                                                        \
-  UBF_LAUNCH(ev, aggregate_kernel<RB>, dim3((unsigned)p.n_box, (nrhs + RB - 1) / RB),      \
+  // Stage 3 reads S again. Where it can still find S in the 256 MB cache the
+  // loads keep it there (3,338 boxes, 175 MB: 35 us here and 41 there, against
+  // 30 and 53); a larger S passes by (25,876 boxes, 1.36 GB: 227 against 245).
+  const bool once = p.nb_total() * (int64_t)p.nu * 8 > 256000000;
+#define UBF_AGG_NT(RB, UN, NT)                                                             \
+  UBF_LAUNCH(ev, (aggregate_kernel<RB, UN, NT>), dim3((unsigned)p.n_box, (nrhs + RB - 1) / RB), \
              dim3(kBlock), (hipStream_t)stream, (const float2*)x, p.d_nb_ptr,              \
              (const float2*)p.d_S, P, p.n_box, p.nb_total(), p.nu, p.kh, p.khb, mode,       \
              p.d_box_scale, nrhs)
-  if (nrhs == 1) UBF_AGG(1); else if (nrhs == 2) UBF_AGG(2); else UBF_AGG(4);
+#define UBF_AGG(RB, UN)                                                                    \
+  do {                                                                                     \
+    if (once) UBF_AGG_NT(RB, UN, true); else UBF_AGG_NT(RB, UN, false);                    \
+  } while (0)
+  // seven steps in flight; one where a step is most of the 256 columns of x
+  if (p.nu == 3) {
+    if (nrhs == 1) UBF_AGG(1, 1); else if (nrhs == 2) UBF_AGG(2, 1); else UBF_AGG(4, 1);
+  } else {
+    if (nrhs == 1) UBF_AGG(1, 7); else if (nrhs == 2) UBF_AGG(2, 7); else UBF_AGG(4, 7);
+  }
 #undef UBF_AGG
+#undef UBF_AGG_NT
   return (int)hipGetLastError();
 }
 
@@ -2063,14 +2164,15 @@ int launch_disaggregate(const Plan& p, const Plan* rows, const float* part,
   // Larger launches keep four per workgroup: over many rounds the dynamic
   // dispatch balances by itself, and a million one-wavefront workgroups
   // cost a little more to dispatch (1% on the 314,171-box, 4-RHS batch).
-  // With T_j = S_j^T a wavefront serves up to four right-hand sides, so
-  // that S_j is read once for them; the identity basis has no S_j to share.
+  // With T_j = S_j^T a workgroup of rb wavefronts serves up to four right-hand
+  // sides, so that S_j is read once for them; the identity basis has no S_j to
+  // share.
   const int rb = (mode == 1 && nrhs > 1) ? (nrhs == 2 ? 2 : 4) : 1;
   const int64_t nrb = (nrhs + rb - 1) / rb;
-  const int wpg = (int64_t)p.n_box * nrb <= 8192 ? 1 : kBlock / 64;
-  const dim3 wgrid((unsigned)((p.n_box + wpg - 1) / wpg), (unsigned)nrb), wblock(64 * wpg);
-#define UBF_WAVE(IDENT, RB)                                                                \
-  UBF_LAUNCH(ev, (disaggregate_wave_kernel<21, IDENT, RB>), wgrid, wblock, s, part,        \
+  const int wpg = rb > 1 || (int64_t)p.n_box * nrb <= 8192 ? 1 : kBlock / 64;
+  const dim3 wgrid((unsigned)((p.n_box + wpg - 1) / wpg), (unsigned)nrb), wblock(64 * wpg * rb);
+#define UBF_WAVE(PQ, IDENT, RB)                                                                \
+  UBF_LAUNCH(ev, (disaggregate_wave_kernel<PQ, IDENT, RB>), wgrid, wblock, s, part,        \
              test_ptr, n_rows, p.d_nb_ptr, (const float2*)p.d_S, (float2*)y,     \
              p.n_box, nb_total, p.nu, p.kh, nrhs)
   if (mode == 2) {
@@ -2099,7 +2201,16 @@ int launch_disaggregate(const Plan& p, const Plan* rows, const float* part,
 #undef UBF_EXPLICIT_RHS
 #undef UBF_EXPLICIT
   } else if (from_parts && mode == 1 && small && few_rows) {
-    if (rb == 1) UBF_WAVE(false, 1); else if (rb == 2) UBF_WAVE(false, 2); else UBF_WAVE(false, 4);
+    // pairs of rows per lane: 16 lanes take a column
+    if (p.nu <= 32) {
+      if (rb == 1) UBF_WAVE(1, false, 1);
+      else if (rb == 2) UBF_WAVE(1, false, 2);
+      else UBF_WAVE(1, false, 4);
+    } else {
+      if (rb == 1) UBF_WAVE(3, false, 1);
+      else if (rb == 2) UBF_WAVE(3, false, 2);
+      else UBF_WAVE(3, false, 4);
+    }
   } else if (from_parts && mode == 0 &&
              (p.nu == 192 || (p.nu == 81 && few_rows && p.n_box * nrhs <= 2048))) {
     // a thread per value while the boxes are few (216 boxes of 83 rows: 7.0
@@ -2109,7 +2220,7 @@ int launch_disaggregate(const Plan& p, const Plan* rows, const float* part,
     UBF_LAUNCH(ev, sum_rows_kernel, grid, dim3((2 * p.nu + 63) / 64 * 64), s, part, test_ptr,
                n_rows, (float2*)y, p.n_box, p.nu, p.pstride());
   } else if (from_parts && mode == 0 && small && few_rows) {
-    UBF_WAVE(true, 1);
+    UBF_WAVE(1, true, 1);
   } else if (from_parts) {
     if (small) UBF_DISAGG(true, 21); else UBF_DISAGG(true, 49);
   } else {

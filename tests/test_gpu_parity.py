@@ -150,6 +150,46 @@ def test_explicit_T_ragged_blocks(n_d, nrhs):
     ff.close()
 
 
+@pytest.mark.parametrize("precision", ["fp32", "split-bf16", "split-fp16"])
+@pytest.mark.parametrize("n_d,nrhs", [(1, 3), (2, 1), (2, 5), (3, 2), (4, 4)])
+def test_streamed_blocks(n_d, nrhs, precision):
+    # stages 1 and 3 read S_i as pairs of values: odd and even block sizes,
+    # blocks that start at odd values, one and several column tiles (256) and
+    # every right-hand-side block width, each vector as when run alone
+    boxes = W.grid_boxes(4, 4, 3)
+    nu = 3 * n_d ** 3
+    nb = np.resize([1, 0, 3, 85, 86, 255, 256, 257, 4, 700], len(boxes))
+    announce("streamed blocks", "n_d", n_d, "nrhs", nrhs, precision)
+    nb_ptr, S = W.random_basis(nb, nu, 41)
+    ff = U.FarField(boxes, 0.25, 2 * np.pi, n_d, "ilist", max_nrhs=nrhs, precision=precision)
+    ff.set_basis(nb_ptr, to_dev(S))
+    x = W.complex_normal((nrhs, int(nb_ptr[-1])), 43)
+    y = to_host(ff(to_dev(x)))
+    ref = O.far_mvm(x.astype(np.complex128), boxes, 0.25, 2 * np.pi, n_d, nb_ptr,
+                    S.astype(np.complex128))
+    parity(y, ref, TOL, boxes=nb_ptr, label=f"streamed n_d {n_d} nrhs {nrhs}")
+    for r in range(nrhs):
+        assert np.array_equal(y[r:r + 1], to_host(ff(to_dev(x[r:r + 1])))), f"rhs {r}"
+    ff.close()
+
+
+def test_basis_larger_than_the_cache():
+    # S past 256 MB is read without keeping it in the caches
+    boxes = W.grid_boxes(4, 4, 2)
+    nb = np.resize([12500, 12501, 12640], len(boxes))
+    announce("large basis", int(nb.sum()), "functions")
+    nb_ptr, S = W.random_basis(nb, 81, 51)
+    assert S.nbytes > 256e6
+    ff = U.FarField(boxes, 0.25, 2 * np.pi, 3, "ilist")
+    ff.set_basis(nb_ptr, to_dev(S))
+    x = W.complex_normal((1, int(nb_ptr[-1])), 53)
+    y = to_host(ff(to_dev(x)))
+    ref = O.far_mvm(x.astype(np.complex128), boxes, 0.25, 2 * np.pi, 3, nb_ptr,
+                    S.astype(np.complex128))
+    parity(y, ref, TOL, boxes=nb_ptr, label="large basis")
+    ff.close()
+
+
 def test_stages_separately():
     w = W.config(1)
     announce("stages separately", w.name)
