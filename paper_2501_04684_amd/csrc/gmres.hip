@@ -7,6 +7,8 @@
 // and a fixed summation order, so results repeat bit for bit.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include <cstdint>
 
 #include "gmres.hpp"
@@ -16,7 +18,8 @@ namespace {
 
 constexpr int kThreads = 512;
 constexpr int kWaves = kThreads / 64;
-constexpr int kColTile = 8;    // Krylov columns per pass over w
+constexpr int kColTile = 4;    // Krylov columns per pass over w
+constexpr int kElems = 2;      // elements of a slice per thread and batch of loads (dots)
 constexpr int kSlice = 2048;   // elements of a block's slice (larger once kDotBlocks are out)
 
 __device__ inline double2 cmul(double2 a, double2 b) {
@@ -53,7 +56,7 @@ __device__ inline double2* partial_of(double2* partial, int r, int ldp, int c) {
 
 // hs[c] = sum over the blocks of column c's partials, c < ncol (ends with a
 // barrier).
-__device__ void gather_partials(const double2* __restrict__ partial, int r, int ldp, int ncol,
+__device__ __forceinline__ void gather_partials(const double2* __restrict__ partial, int r, int ldp, int ncol,
                                 double2* hs) {
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int nblk = gridDim.x;
@@ -77,9 +80,26 @@ __device__ inline void slice_of(int64_t n, int64_t& lo, int64_t& hi) {
   hi = min(lo + len, n);
 }
 
+// Calls f(integral_constant<NC>) for a tile of nc = 1..kColTile columns, so
+// that a tile's loads are one batch. Behind a test per column each load was
+// waited for before the next was issued, and the routine, not inlined, held
+// its kernels at one block per CU: at 428,328 elements and four vectors
+// orth_first took 44 us and orth_second 47 us a step (1 to 5 columns), now 24
+// and 27. Tiles of eight columns and four elements need 214 registers: 50, 53.
+template <class F>
+__device__ inline void with_columns(int nc, F f) {
+  static_assert(kColTile == 4, "cases");
+  switch (nc) {
+    case 1: f(std::integral_constant<int, 1>()); break;
+    case 2: f(std::integral_constant<int, 2>()); break;
+    case 3: f(std::integral_constant<int, 3>()); break;
+    default: f(std::integral_constant<int, 4>()); break;
+  }
+}
+
 // This block's partial sums of conj(V_c[i]) w[i] over its slice, columns
 // c < ncol; V and w at the right-hand side's first element.
-__device__ void slice_dots(const float2* __restrict__ V, int64_t vstride, int ncol,
+__device__ __forceinline__ void slice_dots(const float2* __restrict__ V, int64_t vstride, int ncol,
                            const float2* w, int64_t lo, int64_t hi, double2* partial, int r,
                            int ldp, double2 (*sh)[kColTile]) {
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -87,16 +107,29 @@ __device__ void slice_dots(const float2* __restrict__ V, int64_t vstride, int nc
     double2 acc[kColTile];
 #pragma unroll
     for (int t = 0; t < kColTile; ++t) acc[t] = make_double2(0.0, 0.0);
-    for (int64_t i = lo + threadIdx.x; i < hi; i += kThreads) {
-      const double2 wv = f2d(w[i]);
+    with_columns(min(ncol - c0, kColTile), [&](auto tag) {
+      constexpr int NC = decltype(tag)::value;
+      for (int64_t i = lo + threadIdx.x; i < hi; i += kElems * kThreads) {
+        float2 v[NC][kElems], wv[kElems];
 #pragma unroll
-      for (int t = 0; t < kColTile; ++t)
-        if (c0 + t < ncol) {
-          const double2 p = cmulc(f2d(V[(int64_t)(c0 + t) * vstride + i]), wv);
-          acc[t].x += p.x;
-          acc[t].y += p.y;
+        for (int e = 0; e < kElems; ++e) {  // clamped to the slice, left out below
+          const int64_t k = min(i + e * kThreads, hi - 1);
+          wv[e] = w[k];
+#pragma unroll
+          for (int t = 0; t < NC; ++t) v[t][e] = V[(int64_t)(c0 + t) * vstride + k];
         }
-    }
+#pragma unroll
+        for (int e = 0; e < kElems; ++e)
+          if (i + e * kThreads < hi) {
+#pragma unroll
+            for (int t = 0; t < NC; ++t) {
+              const double2 p = cmulc(f2d(v[t][e]), f2d(wv[e]));
+              acc[t].x += p.x;
+              acc[t].y += p.y;
+            }
+          }
+      }
+    });
 #pragma unroll
     for (int t = 0; t < kColTile; ++t)
       if (c0 + t < ncol) {  // uniform
@@ -144,7 +177,7 @@ __device__ inline double norm2(float2 v) {
 //                and the status row of the step (one block per right-hand side)
 // w is rounded to FP32 between the passes. Before, the same work took eleven
 // kernels and a copy (207 us of 320 us per step on the 762-box sphere).
-__global__ __launch_bounds__(kThreads) void orth_first_kernel(
+__global__ __launch_bounds__(kThreads, 4) void orth_first_kernel(
     const float2* __restrict__ V, int64_t vstride, int j, float2* __restrict__ w, double sr,
     double si, int64_t n, int R, double2* __restrict__ partial, int ldp) {
   __shared__ double2 sh[kWaves][kColTile];
@@ -163,17 +196,24 @@ __global__ __launch_bounds__(kThreads) void orth_first_kernel(
 
 // w -= V h over the slice (FP64 sum, one rounding to FP32); the thread's sum
 // of |w|^2 afterwards.
-__device__ double slice_update(const float2* __restrict__ V, int64_t vstride, int ncol,
+__device__ __forceinline__ double slice_update(const float2* __restrict__ V, int64_t vstride, int ncol,
                                const double2* hs, float2* w, int64_t lo, int64_t hi) {
   double nn = 0.0;
   for (int64_t i = lo + threadIdx.x; i < hi; i += kThreads) {
     double2 s = f2d(w[i]);
-#pragma unroll 8
-    for (int c = 0; c < ncol; ++c) {
-      const double2 p = cmul(f2d(V[(int64_t)c * vstride + i]), hs[c]);
-      s.x -= p.x;
-      s.y -= p.y;
-    }
+    for (int c0 = 0; c0 < ncol; c0 += kColTile)
+      with_columns(min(ncol - c0, kColTile), [&](auto tag) {
+        constexpr int NC = decltype(tag)::value;
+        float2 v[NC];
+#pragma unroll
+        for (int t = 0; t < NC; ++t) v[t] = V[(int64_t)(c0 + t) * vstride + i];
+#pragma unroll
+        for (int t = 0; t < NC; ++t) {
+          const double2 p = cmul(f2d(v[t]), hs[c0 + t]);
+          s.x -= p.x;
+          s.y -= p.y;
+        }
+      });
     const float2 o = make_float2((float)s.x, (float)s.y);
     w[i] = o;
     nn += norm2(o);
@@ -181,7 +221,7 @@ __device__ double slice_update(const float2* __restrict__ V, int64_t vstride, in
   return nn;
 }
 
-__global__ __launch_bounds__(kThreads) void orth_second_kernel(
+__global__ __launch_bounds__(kThreads, 4) void orth_second_kernel(
     const float2* __restrict__ V, int64_t vstride, int ncol, float2* __restrict__ w, int64_t n,
     int R, const double2* __restrict__ partial1, double2* __restrict__ partial2, int ldp,
     double2* __restrict__ h1, int ldh) {
@@ -199,7 +239,7 @@ __global__ __launch_bounds__(kThreads) void orth_second_kernel(
   slice_dots(Vr, vstride, ncol, wr, lo, hi, partial2, r, ldp, sh);
 }
 
-__global__ __launch_bounds__(kThreads) void orth_last_kernel(
+__global__ __launch_bounds__(kThreads, 4) void orth_last_kernel(
     const float2* __restrict__ V, int64_t vstride, int ncol, float2* __restrict__ w, int64_t n,
     int R, const double2* __restrict__ partial2, int ldp, double2* __restrict__ norm_partial,
     double2* __restrict__ h2, int ldh) {

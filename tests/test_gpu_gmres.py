@@ -256,13 +256,13 @@ def test_norm_estimate_rejects_explicit_T():
 
 @pytest.mark.parametrize("shape, n_d, restart, steps", [
     ((4, 4, 4), 2, 9, 12),       # one slice (1,536 elements); a ninth column, a restart
-    ((5, 5, 4), 2, 17, 18),      # 2,400 elements: two slices; three column tiles
+    ((5, 5, 4), 2, 17, 18),      # 2,400 elements: two slices; five column tiles
     ((29, 28, 28), 2, 3, 4),     # 545,664 elements: more than 256 slices of 2,048
 ])
 def test_history_over_slices_and_column_tiles(shape, n_d, restart, steps):
     """The residual estimates of every step against the FP64 oracle at the
     edges of the solver's slices (2,048 elements of a vector) and column
-    tiles (8), with a shift of five times the norm: a Krylov process that
+    tiles (4), with a shift of five times the norm: a Krylov process that
     FP32 vectors perturb by their own rounding only (1e-7 of ||b||)."""
     boxes = W.grid_boxes(*shape)
     announce("gmres slices", shape, "restart", restart)
