@@ -1826,10 +1826,10 @@ __device__ inline float row_sum(float v) {
 // the sums, and the same order for every RB. Bound by the bytes of the
 // partial rows and S_j: 3,338 boxes with 81 functions each take 40.8 us
 // (6.3 TB/s), 25,876 boxes 488 us (5.2 TB/s; 520 when S_j was read 8 bytes a
-// lane and through the caches). Four vectors of the 3,338 boxes take 80.6 us;
+// lane and through the caches, see reads_basis_once). Four vectors of the 3,338 boxes take 80.6 us;
 // with one wavefront summing the rows of all four in turn they took 102.
 // Deeper prefetching of S_j gained nothing.
-template <int PQ, bool IDENT, int RB>
+template <int PQ, bool IDENT, int RB, bool NT>
 __global__ __launch_bounds__(kBlock) void disaggregate_wave_kernel(
     const float* __restrict__ part, const int32_t* __restrict__ test_ptr, int64_t n_pairs,
     const int64_t* __restrict__ nb_ptr, const float2* __restrict__ S, float2* __restrict__ y,
@@ -1905,7 +1905,7 @@ __global__ __launch_bounds__(kBlock) void disaggregate_wave_kernel(
   auto load = [&](int64_t pass) {
     const float2* col = Sb + min(4 * pass + cs, nb - 1) * nu;
 #pragma unroll
-    for (int i = 0; i < PQ; ++i) next[i] = load_pair<true>(col + min(2 * (q + 16 * i), nu - 2));
+    for (int i = 0; i < PQ; ++i) next[i] = load_pair<NT>(col + min(2 * (q + 16 * i), nu - 2));
   };
   constexpr int W = RB;  // wavefronts on this machine's columns
   const int first = RB == 1 ? 0 : wave;
@@ -2020,15 +2020,20 @@ int launch_unpack(const Plan& p, const float* P, void* out, int nrhs, void* stre
   return (int)hipGetLastError();
 }
 
+// Whether stages 1 and 3 read S without keeping it in the caches. A stage
+// finds part of a smaller S in the 256 MB cache where the other stage, or the
+// last product, left it: 3,338 boxes, 175 MB, stages 1 and 3 take 35 and 42 us
+// against 30 and 53 with stage 1 passing the caches by. A larger S only drives
+// the rest out: 25,876 boxes, 1.36 GB, 227 and 489 us against 245 and 517.
+static bool reads_basis_once(const Plan& p) {
+  return p.has_basis && p.nb_total() * (int64_t)p.nu * 8 > 256000000;
+}
+
 int launch_aggregate(const Plan& p, const void* x, float* P, int nrhs, void* stream,
                      const StageEvents* ev) {
   if (!p.has_basis) return launch_pack(p, x, P, nrhs, stream, ev);
   // S_i is read once per block of right-hand sides
   const int mode = p.fp16() ? 2 : (p.split() ? 1 : 0);
-  // Stage 3 reads S again. Where it can still find S in the 256 MB cache the
-  // loads keep it there (3,338 boxes, 175 MB: 35 us here and 41 there, against
-  // 30 and 53); a larger S passes by (25,876 boxes, 1.36 GB: 227 against 245).
-  const bool once = p.nb_total() * (int64_t)p.nu * 8 > 256000000;
 #define UBF_AGG_NT(RB, UN, NT)                                                             \
   UBF_LAUNCH(ev, (aggregate_kernel<RB, UN, NT>), dim3((unsigned)p.n_box, (nrhs + RB - 1) / RB), \
              dim3(kBlock), (hipStream_t)stream, (const float2*)x, p.d_nb_ptr,              \
@@ -2036,7 +2041,7 @@ int launch_aggregate(const Plan& p, const void* x, float* P, int nrhs, void* str
              p.d_box_scale, nrhs)
 #define UBF_AGG(RB, UN)                                                                    \
   do {                                                                                     \
-    if (once) UBF_AGG_NT(RB, UN, true); else UBF_AGG_NT(RB, UN, false);                    \
+    if (reads_basis_once(p)) UBF_AGG_NT(RB, UN, true); else UBF_AGG_NT(RB, UN, false);                    \
   } while (0)
   // seven steps in flight; one where a step is most of the 256 columns of x
   if (p.nu == 3) {
@@ -2171,10 +2176,15 @@ int launch_disaggregate(const Plan& p, const Plan* rows, const float* part,
   const int64_t nrb = (nrhs + rb - 1) / rb;
   const int wpg = rb > 1 || (int64_t)p.n_box * nrb <= 8192 ? 1 : kBlock / 64;
   const dim3 wgrid((unsigned)((p.n_box + wpg - 1) / wpg), (unsigned)nrb), wblock(64 * wpg * rb);
-#define UBF_WAVE(PQ, IDENT, RB)                                                                \
-  UBF_LAUNCH(ev, (disaggregate_wave_kernel<PQ, IDENT, RB>), wgrid, wblock, s, part,        \
+#define UBF_WAVE_NT(PQ, IDENT, RB, NT)                                                                \
+  UBF_LAUNCH(ev, (disaggregate_wave_kernel<PQ, IDENT, RB, NT>), wgrid, wblock, s, part,        \
              test_ptr, n_rows, p.d_nb_ptr, (const float2*)p.d_S, (float2*)y,     \
              p.n_box, nb_total, p.nu, p.kh, nrhs)
+#define UBF_WAVE(PQ, IDENT, RB)                                                            \
+  do {                                                                                     \
+    if (reads_basis_once(p)) UBF_WAVE_NT(PQ, IDENT, RB, true);                             \
+    else UBF_WAVE_NT(PQ, IDENT, RB, false);                                                \
+  } while (0)
   if (mode == 2) {
     // T_j is read once for two or four right-hand sides
     const int nr = nrhs <= 2 ? nrhs : 4;
@@ -2220,13 +2230,14 @@ int launch_disaggregate(const Plan& p, const Plan* rows, const float* part,
     UBF_LAUNCH(ev, sum_rows_kernel, grid, dim3((2 * p.nu + 63) / 64 * 64), s, part, test_ptr,
                n_rows, (float2*)y, p.n_box, p.nu, p.pstride());
   } else if (from_parts && mode == 0 && small && few_rows) {
-    UBF_WAVE(1, true, 1);
+    UBF_WAVE_NT(1, true, 1, false);
   } else if (from_parts) {
     if (small) UBF_DISAGG(true, 21); else UBF_DISAGG(true, 49);
   } else {
     if (small) UBF_DISAGG(false, 21); else UBF_DISAGG(false, 49);
   }
 #undef UBF_WAVE
+#undef UBF_WAVE_NT
 #undef UBF_DISAGG
   return (int)hipGetLastError();
 }
