@@ -233,32 +233,37 @@ __device__ inline floatx4 load_pair(const float2* p) {
 // bytes of S_i: 3,338 boxes of 81 functions take 35 us (5.0 TB/s; 30 where S
 // passes the caches by, as a plain read of as many bytes does), four vectors
 // 47 us, 25,876 boxes 227 us (6.0 TB/s). Reading 8 bytes a lane, with x read
-// from memory beside them, took 44.5, 57.5 and 309 us.
-template <int RB, int UN, bool NT>
+// from memory beside them, took 44.5, 57.5 and 309 us. N_u is a constant for
+// the divisions: they set the time of small blocks (3,338 boxes at N_u = 24:
+// 7.8 us, 12.6 with a run-time N_u, 9.1 with 8-byte loads; N_u = 3: 8.9, 11.1
+// and 9.1).
+template <int RB, int NU, bool NT>
 __global__ __launch_bounds__(kBlock) void aggregate_kernel(
     const float2* __restrict__ x, const int64_t* __restrict__ nb_ptr,
     const float2* __restrict__ S, float* __restrict__ P, int64_t n_box,
-    int64_t nb_total, int nu, int kh, int khb, int mode, float* __restrict__ box_scale,
+    int64_t nb_total, int kh, int khb, int mode, float* __restrict__ box_scale,
     int nrhs) {
   constexpr int XC = 256;  // columns of x in LDS
+  constexpr int unit = NU % 2 ? NU : NU / 2;    // pairs after which the rows repeat
+  constexpr int nt = kBlock / unit * unit;      // threads that take a pair per step
+  constexpr int C = 2 * nt / NU;                // columns per step, <= 170
+  constexpr int tile_steps = XC / C;            // >= 1
+  // steps in flight (one where a step is most of the 256 columns of x)
+  constexpr int UN = tile_steps < 7 ? 1 : (NU < 81 ? 4 : 7);
   __shared__ float2 red[RB][2 * kBlock];
   __shared__ float2 xs[RB][XC];
   const int64_t i = blockIdx.x;
   const int r0 = blockIdx.y * RB;
   const int nr = min(RB, nrhs - r0);  // >= 1
   const int t = threadIdx.x;
-  const int unit = (nu & 1) ? nu : nu / 2;  // pairs after which the rows repeat
-  const int nt = kBlock / unit * unit;
-  const int C = 2 * nt / nu;  // columns per step, <= 170
   // this thread's pair of a step: rows ua, ub of columns ga, gb
-  const int ga = 2 * t / nu, gb = (2 * t + 1) / nu;
+  const int ga = 2 * t / NU, gb = (2 * t + 1) / NU;
   const int64_t start = nb_ptr[i];
   const int64_t nb = nb_ptr[i + 1] - start;
-  const float2* Sb = S + start * nu;
+  const float2* Sb = S + start * NU;
   const float2* xb = x + (int64_t)r0 * nb_total + start;
-  const int64_t np = nb * nu / 2;  // whole pairs
+  const int64_t np = nb * NU / 2;  // whole pairs
   const int64_t steps = t < nt ? (np + nt - 1) / nt : 0;
-  const int64_t tile_steps = XC / C;  // >= 1
   float ar[RB], ai[RB], br[RB], bi[RB];
 #pragma unroll
   for (int q = 0; q < RB; ++q) ar[q] = ai[q] = br[q] = bi[q] = 0.f;
@@ -270,7 +275,7 @@ __global__ __launch_bounds__(kBlock) void aggregate_kernel(
   };
   if (np > 0) load(0);  // uniform
   for (int64_t c0 = 0, s0 = 0; c0 < nb; c0 += tile_steps * C) {
-    const int cn = (int)min(tile_steps * C, nb - c0);
+    const int cn = (int)min<int64_t>(tile_steps * C, nb - c0);
     if (c0 > 0) __syncthreads();  // every thread is done with the last columns
 #pragma unroll
     for (int q = 0; q < RB; ++q)  // vectors past the last one repeat it (not stored)
@@ -303,7 +308,7 @@ __global__ __launch_bounds__(kBlock) void aggregate_kernel(
     }
     s0 = s1;
   }
-  if (np * 2 < nb * nu && t == np % nt) {  // the last value of an odd block
+  if (np * 2 < nb * NU && t == np % nt) {  // the last value of an odd block
     const float2 s = Sb[2 * np];
 #pragma unroll
     for (int q = 0; q < RB; ++q) {
@@ -324,9 +329,9 @@ __global__ __launch_bounds__(kBlock) void aggregate_kernel(
     const int half = (G + 1) / 2;
 #pragma unroll
     for (int q = 0; q < RB; ++q)
-      for (int e = t; e < (G - half) * nu; e += kBlock) {
-        red[q][e].x += red[q][e + half * nu].x;
-        red[q][e].y += red[q][e + half * nu].y;
+      for (int e = t; e < (G - half) * NU; e += kBlock) {
+        red[q][e].x += red[q][e + half * NU].x;
+        red[q][e].y += red[q][e + half * NU].y;
       }
     __syncthreads();
     G = half;
@@ -341,10 +346,10 @@ __global__ __launch_bounds__(kBlock) void aggregate_kernel(
   for (int k = 0; k < 3; ++k) {
     const int u = l + 64 * k;
     sr[k] = si[k] = 0.f;
-    if (u < nu)
+    if (u < NU)
       for (int gg = 0; gg < G; ++gg) {
-        sr[k] += red[q][gg * nu + u].x;
-        si[k] += red[q][gg * nu + u].y;
+        sr[k] += red[q][gg * NU + u].x;
+        si[k] += red[q][gg * NU + u].y;
       }
     m = fmaxf(m, fmaxf(fabsf(sr[k]), fabsf(si[k])));
   }
@@ -2034,20 +2039,28 @@ int launch_aggregate(const Plan& p, const void* x, float* P, int nrhs, void* str
   if (!p.has_basis) return launch_pack(p, x, P, nrhs, stream, ev);
   // S_i is read once per block of right-hand sides
   const int mode = p.fp16() ? 2 : (p.split() ? 1 : 0);
-#define UBF_AGG_NT(RB, UN, NT)                                                             \
-  UBF_LAUNCH(ev, (aggregate_kernel<RB, UN, NT>), dim3((unsigned)p.n_box, (nrhs + RB - 1) / RB), \
+#define UBF_AGG_NT(RB, NU, NT)                                                             \
+  UBF_LAUNCH(ev, (aggregate_kernel<RB, NU, NT>), dim3((unsigned)p.n_box, (nrhs + RB - 1) / RB), \
              dim3(kBlock), (hipStream_t)stream, (const float2*)x, p.d_nb_ptr,              \
-             (const float2*)p.d_S, P, p.n_box, p.nb_total(), p.nu, p.kh, p.khb, mode,       \
+             (const float2*)p.d_S, P, p.n_box, p.nb_total(), p.kh, p.khb, mode,             \
              p.d_box_scale, nrhs)
-#define UBF_AGG(RB, UN)                                                                    \
+#define UBF_AGG(NU)                                                                        \
   do {                                                                                     \
-    if (reads_basis_once(p)) UBF_AGG_NT(RB, UN, true); else UBF_AGG_NT(RB, UN, false);                    \
+    const bool once = reads_basis_once(p);                                                 \
+    if (nrhs == 1) {                                                                       \
+      if (once) UBF_AGG_NT(1, NU, true); else UBF_AGG_NT(1, NU, false);                    \
+    } else if (nrhs == 2) {                                                                \
+      if (once) UBF_AGG_NT(2, NU, true); else UBF_AGG_NT(2, NU, false);                    \
+    } else {                                                                               \
+      if (once) UBF_AGG_NT(4, NU, true); else UBF_AGG_NT(4, NU, false);                    \
+    }                                                                                      \
   } while (0)
-  // seven steps in flight; one where a step is most of the 256 columns of x
-  if (p.nu == 3) {
-    if (nrhs == 1) UBF_AGG(1, 1); else if (nrhs == 2) UBF_AGG(2, 1); else UBF_AGG(4, 1);
-  } else {
-    if (nrhs == 1) UBF_AGG(1, 7); else if (nrhs == 2) UBF_AGG(2, 7); else UBF_AGG(4, 7);
+  switch (p.nu) {
+    case 3: UBF_AGG(3); break;
+    case 24: UBF_AGG(24); break;
+    case 81: UBF_AGG(81); break;
+    case 192: UBF_AGG(192); break;
+    default: return (int)hipErrorInvalidValue;  // rejected at plan creation
   }
 #undef UBF_AGG
 #undef UBF_AGG_NT
