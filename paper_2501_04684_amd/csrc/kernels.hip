@@ -2213,11 +2213,13 @@ int launch_disaggregate(const Plan& p, const Plan* rows, const float* part,
     else UBF_EXPLICIT(PARTS, 4, EQ);                                                       \
   } while (0)
     if (from_parts) {
-      if (p.nu <= 24) UBF_EXPLICIT_RHS(true, 6);
+      if (p.nu == 3) UBF_EXPLICIT_RHS(true, 1);
+      else if (p.nu == 24) UBF_EXPLICIT_RHS(true, 6);
       else if (small) UBF_EXPLICIT_RHS(true, 21);
       else UBF_EXPLICIT_RHS(true, 48);
     } else {
-      if (p.nu <= 24) UBF_EXPLICIT_RHS(false, 6);
+      if (p.nu == 3) UBF_EXPLICIT_RHS(false, 1);
+      else if (p.nu == 24) UBF_EXPLICIT_RHS(false, 6);
       else if (small) UBF_EXPLICIT_RHS(false, 21);
       else UBF_EXPLICIT_RHS(false, 48);
     }
