@@ -912,9 +912,20 @@ def main():
     khb = (nu + 7) // 8 * 8
     issued = issued_16bit_flops(chosen, nu, n_pairs, nrhs) if split else flops
     dom = int(np.argmax(avg_us))
-    if dom == 1:
-        peak = PEAK_BF16_MFMA_TFLOPS if split else PEAK_FP32_MFMA_TFLOPS
-        ach = (issued if split else flops) / (avg_us[1] * 1e-6) / 1e12
+    peak = PEAK_BF16_MFMA_TFLOPS if split else PEAK_FP32_MFMA_TFLOPS
+    ach = (issued if split else flops) / (avg_us[1] * 1e-6) / 1e12
+    # a FULL far set whose pairs would need more than the peak rate ran as a
+    # convolution: its stage 2 has no flops per pair, only its input and output
+    convolution = w.far_mode == "full" and ach > peak
+    bytes_conv = 2 * nrhs * n_box * nu * 8
+    if convolution:
+        translate_kernel = "convolution"
+    if dom == 1 and convolution:
+        gbs = bytes_conv / (avg_us[1] * 1e-6) / 1e9
+        roof = {"kernel": translate_kernel, "bound": "hbm", "achieved": gbs,
+                "peak": PEAK_HBM_GBS, "unit": "GB/s", "frac": gbs / PEAK_HBM_GBS,
+                "traffic": None}
+    elif dom == 1:
         roof = {"kernel": translate_kernel, "bound": "mfma", "achieved": ach,
                 "peak": peak, "unit": "TFLOP/s", "frac": ach / peak,
                 "traffic": measured_traffic(translate_kernel, tkey)}
@@ -925,11 +936,14 @@ def main():
                 "peak": PEAK_HBM_GBS, "unit": "GB/s", "frac": ach / PEAK_HBM_GBS,
                 "traffic": measured_traffic(stage_names[dom], tkey)}
     stages = {name: {"avg_us": float(avg_us[i])} for i, name in enumerate(stage_names)}
-    stages["translate"].update(
-        kernel=translate_kernel, algorithmic_flops=flops,
-        tflops=trans_tflops, frac_fp32_mfma_peak=trans_tflops / PEAK_FP32_MFMA_TFLOPS,
-        traffic=measured_traffic(translate_kernel, tkey))
-    if split:
+    if convolution:
+        stages["translate"].update(kernel=translate_kernel, algorithmic_bytes=bytes_conv)
+    else:
+        stages["translate"].update(
+            kernel=translate_kernel, algorithmic_flops=flops,
+            tflops=trans_tflops, frac_fp32_mfma_peak=trans_tflops / PEAK_FP32_MFMA_TFLOPS,
+            traffic=measured_traffic(translate_kernel, tkey))
+    if split and not convolution:
         itf = issued / (avg_us[1] * 1e-6) / 1e12
         stages["translate"].update(issued_bf16_flops=issued, issued_tflops=itf,
                                    frac_bf16_mfma_peak=itf / PEAK_BF16_MFMA_TFLOPS)
