@@ -25,9 +25,10 @@
  * (the one-box-buffer interaction list of a two-level tree; its 316
  * distinct offsets are the translation vectors counted in Sec. 2.2).
  * The FULL product of a scatterer with many pairs runs as a convolution
- * over the lattice of its sites (FP32 FFTs) plus the pairs exactly two boxes
- * apart, except in the single FP16 form: its rounding errors are relative to
- * the scatterer's whole field, and a non-finite coefficient makes the whole
+ * over the lattice of its sites (FP64 FFTs) plus the pairs exactly two boxes
+ * apart, except in the single FP16 form. A box's error stays relative to what
+ * reaches it from its far boxes, as pair by pair, and a box whose far boxes
+ * are all zero gets exactly zero. A non-finite coefficient makes the whole
  * scatterer's result non-finite. Which way is taken depends on the
  * scatterer's boxes, n_d and precision alone.
  *

@@ -32,7 +32,7 @@ HIP_FLAGS = ["-O3", "-fPIC", "-std=c++17", f"--offload-arch={ARCH}",
 
 
 # Per file. fft.hip: sums with the zero padding (constant zeros) fold away.
-HIP_EXTRA = {"fft.hip": ["-fno-signed-zeros", "-ffinite-math-only"]}
+HIP_EXTRA = {"fft.hip": ["-fno-signed-zeros"]}
 
 
 def _run(cmd):

@@ -334,8 +334,9 @@ int ubf_plan_bind(ubf_plan* plan, void* d_workspace, size_t bytes,
   if (ubf::holds_own_pairs(p)) copy_pairs(p, L.own, offsets4[0]);
   if (p.rest) {
     copy_pairs(*p.rest, L.rest, offsets4[1]);
-    copies.push_back({L.fft_tw, p.fft_twiddles.data(), p.fft_twiddles.size() * sizeof(float)});
+    copies.push_back({L.fft_tw, p.fft_twiddles.data(), p.fft_twiddles.size() * sizeof(double)});
     copies.push_back({L.fft_map, p.fft_map.data(), p.fft_map.size() * sizeof(int32_t)});
+    copies.push_back({L.fft_cells, p.fft_cells.data(), p.fft_cells.size() * sizeof(int32_t)});
   }
   copies.push_back({L.nb_ptr, nb.data(), nb.size() * sizeof(int64_t)});
   hipError_t e = hipSuccess;
@@ -373,10 +374,11 @@ int ubf_plan_bind(ubf_plan* plan, void* d_workspace, size_t bytes,
   point(*p.rest, L.rest);
   p.rest->max_nrhs = max_nrhs;
   p.rest->d_box_scale = p.d_box_scale;
-  p.d_fft = (float*)(ws + L.fft);
-  p.d_fft_spec = (float*)(ws + L.fft_spec);
-  p.d_fft_tw = (float*)(ws + L.fft_tw);
+  p.d_fft = ws + L.fft;
+  p.d_fft_spec = (double*)(ws + L.fft_spec);
+  p.d_fft_tw = (double*)(ws + L.fft_tw);
   p.d_fft_map = (int32_t*)(ws + L.fft_map);
+  p.d_fft_cells = (int32_t*)(ws + L.fft_cells);
   int le = ubf::launch_fft_spectra(p, s);
   if (!le) le = (int)hipStreamSynchronize(s);
   if (le) return hip_fail(le, "spectra (bind)");

@@ -1,6 +1,7 @@
 // FULL far sets as a discrete convolution over the lattice of the sites
-// (FftGrid in plan.hpp). Per scatterer and right-hand side five kernels, each
-// transforming lines of the zero-padded lattice in LDS:
+// (FftGrid in plan.hpp), in FP64. Two kernels per product look at the box
+// vectors, then per scatterer and right-hand side five kernels each transform
+// lines of the zero-padded lattice in LDS:
 //   fft_z:    box vectors -> [x][y][kz][component]          (x, y < sites)
 //   fft_y:    -> [x][ky][kz][component]                     (x < sites)
 //   fft_x:    transform along x, product with the spectrum of D (a symmetric
@@ -8,12 +9,22 @@
 //   ifft_y:   -> [x][y][kz][component]
 //   ifft_z:   -> the first partial row of every box
 // Only lines that can hold a value are touched, so the zero padding of an
-// axis is never in memory before that axis is transformed. All are bound by
-// memory and by the transforms' own arithmetic: on the 3,338-box shell (105^3
-// sites, transforms of 216) 57 MB and 118 MB arrays, about 590 MB in all,
-// against 15 GB of partial rows that 11.1 million pairs write and read one
-// by one. Measured there: 27 + 50 + 131 + 55 + 22 us, and the whole product
-// 407 us against 6,335 with every pair's operator evaluated and applied.
+// axis is never in memory before that axis is transformed.
+//
+// A transform's rounding errors are relative to the whole scatterer's field,
+// those of a pair's own product to what reaches the test box, which may be
+// far less. So everything here is FP64, and the boxes that even so would see
+// mostly rounding errors are summed pair by pair: those that no strong box
+// is far from (strong: at least 2^-24 of the scatterer's largest coefficient;
+// Reach). The strong boxes are then within one of them on every axis, so
+// there are at most 27. One box 10^4 times stronger than the others left its
+// neighbours, which it does not reach, wrong by 5e-5 with FP32 transforms.
+//
+// The transforms are bound by memory (z, y) and by their own arithmetic and
+// LDS traffic (x). On the 3,338-box shell (105^3 sites, transforms of 216;
+// arrays of 114 and 235 MB, four passes each, and a spectrum of 124 MB): 42 +
+// 59 + 211 + 63 + 45 us, 14 us to look at the box vectors, and the whole
+// product 530 us against 6,290 pair by pair; 398 with FP32 transforms.
 #include <hip/hip_ext.h>
 #include <hip/hip_fp16.h>
 #include <hip/hip_runtime.h>
@@ -26,23 +37,22 @@ namespace ubf {
 namespace {
 
 constexpr int kThreads = 256;       // spectrum kernels
-constexpr int kMaxThreads = kMaxFftThreads;  // transform kernels: one butterfly per thread
 // LDS of one workgroup's lines: three workgroups share a compute unit (160 KB).
 constexpr size_t kLineBytes = 50 << 10;
 
-__device__ inline float2 cmul(float2 a, float2 b) {
-  return make_float2(fmaf(a.x, b.x, -a.y * b.y), fmaf(a.x, b.y, a.y * b.x));
+__device__ inline double2 cmul(double2 a, double2 b) {
+  return make_double2(fma(a.x, b.x, -a.y * b.y), fma(a.x, b.y, a.y * b.x));
 }
 // a * b + c
-__device__ inline float2 cfma(float2 a, float2 b, float2 c) {
-  return make_float2(fmaf(a.x, b.x, fmaf(-a.y, b.y, c.x)), fmaf(a.x, b.y, fmaf(a.y, b.x, c.y)));
+__device__ inline double2 cfma(double2 a, double2 b, double2 c) {
+  return make_double2(fma(a.x, b.x, fma(-a.y, b.y, c.x)), fma(a.x, b.y, fma(a.y, b.x, c.y)));
 }
-__device__ inline float2 cadd(float2 a, float2 b) { return make_float2(a.x + b.x, a.y + b.y); }
-__device__ inline float2 csub(float2 a, float2 b) { return make_float2(a.x - b.x, a.y - b.y); }
+__device__ inline double2 cadd(double2 a, double2 b) { return make_double2(a.x + b.x, a.y + b.y); }
+__device__ inline double2 csub(double2 a, double2 b) { return make_double2(a.x - b.x, a.y - b.y); }
 // a * (-i) forward, a * i backward
 template <bool INV>
-__device__ inline float2 mul_mi(float2 a) {
-  return INV ? make_float2(-a.y, a.x) : make_float2(a.y, -a.x);
+__device__ inline double2 mul_mi(double2 a) {
+  return INV ? make_double2(-a.y, a.x) : make_double2(a.y, -a.x);
 }
 
 // Discrete Fourier transform of R values in registers (in place, natural
@@ -51,28 +61,28 @@ template <int R, bool INV>
 struct Butterfly;
 template <bool INV>
 struct Butterfly<2, INV> {
-  static __device__ inline void run(float2 (&v)[2]) {
-    const float2 a = v[0], b = v[1];
+  static __device__ inline void run(double2 (&v)[2]) {
+    const double2 a = v[0], b = v[1];
     v[0] = cadd(a, b);
     v[1] = csub(a, b);
   }
 };
 template <bool INV>
 struct Butterfly<3, INV> {
-  static __device__ inline void run(float2 (&v)[3]) {
-    const float s = 0.866025403784438647f;
-    const float2 t = cadd(v[1], v[2]), d = mul_mi<INV>(csub(v[1], v[2]));
-    const float2 m = make_float2(fmaf(-0.5f, t.x, v[0].x), fmaf(-0.5f, t.y, v[0].y));
+  static __device__ inline void run(double2 (&v)[3]) {
+    const double s = 0.866025403784438647;
+    const double2 t = cadd(v[1], v[2]), d = mul_mi<INV>(csub(v[1], v[2]));
+    const double2 m = make_double2(fma(-0.5, t.x, v[0].x), fma(-0.5, t.y, v[0].y));
     v[0] = cadd(v[0], t);
-    v[1] = make_float2(fmaf(s, d.x, m.x), fmaf(s, d.y, m.y));
-    v[2] = make_float2(fmaf(-s, d.x, m.x), fmaf(-s, d.y, m.y));
+    v[1] = make_double2(fma(s, d.x, m.x), fma(s, d.y, m.y));
+    v[2] = make_double2(fma(-s, d.x, m.x), fma(-s, d.y, m.y));
   }
 };
 template <bool INV>
 struct Butterfly<4, INV> {
-  static __device__ inline void run(float2 (&v)[4]) {
-    const float2 a = cadd(v[0], v[2]), b = csub(v[0], v[2]);
-    const float2 c = cadd(v[1], v[3]), d = mul_mi<INV>(csub(v[1], v[3]));
+  static __device__ inline void run(double2 (&v)[4]) {
+    const double2 a = cadd(v[0], v[2]), b = csub(v[0], v[2]);
+    const double2 c = cadd(v[1], v[3]), d = mul_mi<INV>(csub(v[1], v[3]));
     v[0] = cadd(a, c);
     v[1] = cadd(b, d);
     v[2] = csub(a, c);
@@ -81,18 +91,18 @@ struct Butterfly<4, INV> {
 };
 template <bool INV>
 struct Butterfly<5, INV> {
-  static __device__ inline void run(float2 (&v)[5]) {
+  static __device__ inline void run(double2 (&v)[5]) {
     // cos and sin of 2 pi / 5 and 4 pi / 5
-    const float c1 = 0.309016994374947424f, c2 = -0.809016994374947424f;
-    const float s1 = 0.951056516295153572f, s2 = 0.587785252292473129f;
-    const float2 a = cadd(v[1], v[4]), b = cadd(v[2], v[3]);
-    const float2 d = mul_mi<INV>(csub(v[1], v[4])), e = mul_mi<INV>(csub(v[2], v[3]));
-    const float2 p = make_float2(fmaf(c1, a.x, fmaf(c2, b.x, v[0].x)),
-                                 fmaf(c1, a.y, fmaf(c2, b.y, v[0].y)));
-    const float2 q = make_float2(fmaf(c2, a.x, fmaf(c1, b.x, v[0].x)),
-                                 fmaf(c2, a.y, fmaf(c1, b.y, v[0].y)));
-    const float2 r = make_float2(fmaf(s1, d.x, s2 * e.x), fmaf(s1, d.y, s2 * e.y));
-    const float2 t = make_float2(fmaf(s2, d.x, -s1 * e.x), fmaf(s2, d.y, -s1 * e.y));
+    const double c1 = 0.309016994374947424, c2 = -0.809016994374947424;
+    const double s1 = 0.951056516295153572, s2 = 0.587785252292473129;
+    const double2 a = cadd(v[1], v[4]), b = cadd(v[2], v[3]);
+    const double2 d = mul_mi<INV>(csub(v[1], v[4])), e = mul_mi<INV>(csub(v[2], v[3]));
+    const double2 p = make_double2(fma(c1, a.x, fma(c2, b.x, v[0].x)),
+                                 fma(c1, a.y, fma(c2, b.y, v[0].y)));
+    const double2 q = make_double2(fma(c2, a.x, fma(c1, b.x, v[0].x)),
+                                 fma(c2, a.y, fma(c1, b.y, v[0].y)));
+    const double2 r = make_double2(fma(s1, d.x, s2 * e.x), fma(s1, d.y, s2 * e.y));
+    const double2 t = make_double2(fma(s2, d.x, -s1 * e.x), fma(s2, d.y, -s1 * e.y));
     v[0] = cadd(v[0], cadd(a, b));
     v[1] = cadd(p, r);
     v[4] = csub(p, r);
@@ -102,13 +112,13 @@ struct Butterfly<5, INV> {
 };
 template <bool INV>
 struct Butterfly<6, INV> {  // two of three, combined by twos
-  static __device__ inline void run(float2 (&v)[6]) {
-    float2 e[3] = {v[0], v[2], v[4]}, o[3] = {v[1], v[3], v[5]};
+  static __device__ inline void run(double2 (&v)[6]) {
+    double2 e[3] = {v[0], v[2], v[4]}, o[3] = {v[1], v[3], v[5]};
     Butterfly<3, INV>::run(e);
     Butterfly<3, INV>::run(o);
-    const float s = 0.866025403784438647f, sg = INV ? 1.f : -1.f;
-    o[1] = cmul(o[1], make_float2(0.5f, sg * s));
-    o[2] = cmul(o[2], make_float2(-0.5f, sg * s));
+    const double s = 0.866025403784438647, sg = INV ? 1.0 : -1.0;
+    o[1] = cmul(o[1], make_double2(0.5, sg * s));
+    o[2] = cmul(o[2], make_double2(-0.5, sg * s));
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
       v[k] = cadd(e[k], o[k]);
@@ -118,14 +128,14 @@ struct Butterfly<6, INV> {  // two of three, combined by twos
 };
 template <bool INV>
 struct Butterfly<8, INV> {
-  static __device__ inline void run(float2 (&v)[8]) {
-    float2 e[4] = {v[0], v[2], v[4], v[6]}, o[4] = {v[1], v[3], v[5], v[7]};
+  static __device__ inline void run(double2 (&v)[8]) {
+    double2 e[4] = {v[0], v[2], v[4], v[6]}, o[4] = {v[1], v[3], v[5], v[7]};
     Butterfly<4, INV>::run(e);
     Butterfly<4, INV>::run(o);
-    const float h = 0.707106781186547524f, sg = INV ? 1.f : -1.f;
-    o[1] = cmul(o[1], make_float2(h, sg * h));
+    const double h = 0.707106781186547524, sg = INV ? 1.0 : -1.0;
+    o[1] = cmul(o[1], make_double2(h, sg * h));
     o[2] = mul_mi<INV>(o[2]);
-    o[3] = cmul(o[3], make_float2(-h, sg * h));
+    o[3] = cmul(o[3], make_double2(-h, sg * h));
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       v[k] = cadd(e[k], o[k]);
@@ -138,39 +148,42 @@ struct Butterfly<8, INV> {
 // stays below half a unit of i.
 __device__ inline int fdiv(int i, float inv) { return (int)(((float)i + 0.5f) * inv); }
 
-// `w` neighbouring lines of length L in LDS, three components each: value
-// (position, line, component) at (position * w + line) * 3 + component. The
-// index of (position, line) times three is what load and store below take.
-//
-// One Stockham stage of radix R, one butterfly (of all three components) per
-// thread: butterfly j of a line reads positions j + r L / R, applies the
-// twiddle factors of k = j mod Ns and writes positions (j / Ns) Ns R + k +
-// r Ns. The components share the index arithmetic and the twiddle factors.
-// load(position, line, v) and store(position, line, v) go to LDS or, for a
-// transform's first and last stage, straight to memory; between the two every
-// thread waits, so that one buffer serves both.
+// A workgroup transforms `w` neighbouring lines of three components, taken as
+// 3 w lines of one: value (position, line) is at position * w3 + line in LDS,
+// line = 3 (line of sites) + component. Thread i has butterfly j = i / w3 of
+// line i mod w3 in every stage, so what depends on the line is computed once,
+// and neighbouring threads hold neighbouring values. (With the three
+// components in one thread the indices and twiddle factors are shared, but
+// the registers and the LDS leave two wavefronts to a SIMD: on 105^3 sites
+// 385 + 118 + 118 us along x, y and back.)
+struct Lane {
+  int j, line, w3;
+  __device__ Lane(int w) : w3(3 * w) {
+    j = fdiv(threadIdx.x, 1.f / (float)w3);
+    line = (int)threadIdx.x - j * w3;
+  }
+};
+
+// One Stockham stage of radix R: butterfly j reads positions j + r L / R,
+// applies the twiddle factors of k = j mod Ns and writes positions
+// (j / Ns) Ns R + k + r Ns. load(position) and store(position, value) go to
+// LDS or, for a transform's first and last stage, straight to memory; between
+// the two every thread waits, so that one buffer serves both.
 // A line of s sites is transformed at L >= 2 s - 1 positions: with an even
 // radix (L even, s <= L / 2) the upper R / 2 inputs of the forward
 // transform's first stage are the zero padding (HALF_IN), and the upper
 // R / 2 outputs of the backward transform's last stage are not wanted
 // (HALF_OUT).
 template <int R, bool INV, bool TW, bool HALF_IN, bool HALF_OUT, class Load, class Store>
-__device__ inline void stage(int L, int w, float inv_w, const float2* tw, int Ns, Load load,
-                             Store store) {
+__device__ inline void stage(int L, int j, const double2* tw, int Ns, Load load, Store store) {
   constexpr int RI = HALF_IN && R % 2 == 0 ? R / 2 : R;
   constexpr int RO = HALF_OUT && R % 2 == 0 ? R / 2 : R;
-  const int m = L / R, i = threadIdx.x;
-  const int j = fdiv(i, inv_w), line = i - j * w;
-  const bool on = i < m * w;
-  float2 v[R][3];
+  const int m = L / R;
+  const bool on = j < m;
+  double2 v[R];
   if (on) {
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-      if (r < RI)
-        load(j + r * m, line, v[r]);
-      else
-        v[r][0] = v[r][1] = v[r][2] = make_float2(0.f, 0.f);
-    }
+    for (int r = 0; r < R; ++r) v[r] = r < RI ? load(j + r * m) : make_double2(0.0, 0.0);
   }
   __syncthreads();
   if (on) {
@@ -181,95 +194,66 @@ __device__ inline void stage(int L, int w, float inv_w, const float2* tw, int Ns
       o = q * Ns * R + k;
 #pragma unroll
       for (int r = 1; r < R; ++r) {
-        float2 t = tw[r * step];
+        double2 t = tw[r * step];
         if (INV) t.y = -t.y;
-#pragma unroll
-        for (int al = 0; al < 3; ++al) v[r][al] = cmul(v[r][al], t);
+        v[r] = cmul(v[r], t);
       }
     }
+    Butterfly<R, INV>::run(v);
 #pragma unroll
-    for (int al = 0; al < 3; ++al) {
-      float2 x[R];
-#pragma unroll
-      for (int r = 0; r < R; ++r) x[r] = v[r][al];
-      Butterfly<R, INV>::run(x);
-#pragma unroll
-      for (int r = 0; r < R; ++r) v[r][al] = x[r];
-    }
-#pragma unroll
-    for (int r = 0; r < RO; ++r) store(o + r * Ns, line, v[r]);
+    for (int r = 0; r < RO; ++r) store(o + r * Ns, v[r]);
   }
   __syncthreads();
 }
 
 template <bool INV, bool TW, bool HALF_IN, bool HALF_OUT, class Load, class Store>
-__device__ inline void stage_of(int R, int L, int w, float inv_w, const float2* tw, int Ns,
-                                Load load, Store store) {
+__device__ inline void stage_of(int R, int L, int j, const double2* tw, int Ns, Load load,
+                                Store store) {
   switch (R) {  // uniform
-    case 2: stage<2, INV, TW, HALF_IN, HALF_OUT>(L, w, inv_w, tw, Ns, load, store); break;
-    case 3: stage<3, INV, TW, HALF_IN, HALF_OUT>(L, w, inv_w, tw, Ns, load, store); break;
-    case 4: stage<4, INV, TW, HALF_IN, HALF_OUT>(L, w, inv_w, tw, Ns, load, store); break;
-    case 5: stage<5, INV, TW, HALF_IN, HALF_OUT>(L, w, inv_w, tw, Ns, load, store); break;
-    case 6: stage<6, INV, TW, HALF_IN, HALF_OUT>(L, w, inv_w, tw, Ns, load, store); break;
-    default: stage<8, INV, TW, HALF_IN, HALF_OUT>(L, w, inv_w, tw, Ns, load, store); break;
+    case 2: stage<2, INV, TW, HALF_IN, HALF_OUT>(L, j, tw, Ns, load, store); break;
+    case 3: stage<3, INV, TW, HALF_IN, HALF_OUT>(L, j, tw, Ns, load, store); break;
+    case 4: stage<4, INV, TW, HALF_IN, HALF_OUT>(L, j, tw, Ns, load, store); break;
+    case 5: stage<5, INV, TW, HALF_IN, HALF_OUT>(L, j, tw, Ns, load, store); break;
+    case 6: stage<6, INV, TW, HALF_IN, HALF_OUT>(L, j, tw, Ns, load, store); break;
+    default: stage<8, INV, TW, HALF_IN, HALF_OUT>(L, j, tw, Ns, load, store); break;
   }
 }
-
-// Lines in LDS, as load and store of a stage.
-struct Buffer {
-  float2* b;
-  int w;
-  __device__ inline void operator()(int pos, int line, float2 (&v)[3]) const {  // load
-    const float2* p = b + 3 * (pos * w + line);
-#pragma unroll
-    for (int al = 0; al < 3; ++al) v[al] = p[al];
-  }
-};
-struct BufferStore {
-  float2* b;
-  int w;
-  __device__ inline void operator()(int pos, int line, const float2 (&v)[3]) const {
-    float2* p = b + 3 * (pos * w + line);
-#pragma unroll
-    for (int al = 0; al < 3; ++al) p[al] = v[al];
-  }
-};
 
 // A whole transform in the buffer `a`: the first stage takes its values from
 // load, the last one gives them to store (either may be the buffer). The
 // twiddle factors and the buffer may have been written just before; ends with
 // a barrier. An axis of length 1 passes its values through.
 template <bool INV, class Load, class Store>
-__device__ inline void transform(const FftAxis& ax, int w, const float2* tw, float2* a, Load load,
-                                 Store store) {
+__device__ inline void transform(const FftAxis& ax, const Lane& t, const double2* tw, double2* a,
+                                 Load load, Store store) {
   const int L = ax.L, n = ax.stages;
-  const float inv_w = 1.f / (float)w;
-  const Buffer get{a, w};
-  const BufferStore put{a, w};
+  double2* mine = a + t.line;
+  const int w3 = t.w3;
+  auto get = [mine, w3](int pos) { return mine[pos * w3]; };
+  auto put = [mine, w3](int pos, double2 v) { mine[pos * w3] = v; };
   __syncthreads();
   if (n == 0) {
-    if ((int)threadIdx.x < w) {
-      float2 v[3];
-      load(0, threadIdx.x, v);
-      store(0, threadIdx.x, v);
-    }
+    double2 v = make_double2(0.0, 0.0);
+    if (t.j == 0) v = load(0);
+    __syncthreads();
+    if (t.j == 0) store(0, v);
     __syncthreads();
     return;
   }
   if (n == 1) {
-    stage_of<INV, false, !INV, INV>(ax.radix[0], L, w, inv_w, tw, 1, load, store);
+    stage_of<INV, false, !INV, INV>(ax.radix[0], L, t.j, tw, 1, load, store);
     return;
   }
-  stage_of<INV, false, !INV, false>(ax.radix[0], L, w, inv_w, tw, 1, load, put);
+  stage_of<INV, false, !INV, false>(ax.radix[0], L, t.j, tw, 1, load, put);
   int Ns = ax.radix[0];
   for (int s = 1; s + 1 < n; ++s) {
-    stage_of<INV, true, false, false>(ax.radix[s], L, w, inv_w, tw, Ns, get, put);
+    stage_of<INV, true, false, false>(ax.radix[s], L, t.j, tw, Ns, get, put);
     Ns *= ax.radix[s];
   }
-  stage_of<INV, true, false, INV>(ax.radix[n - 1], L, w, inv_w, tw, Ns, get, store);
+  stage_of<INV, true, false, INV>(ax.radix[n - 1], L, t.j, tw, Ns, get, store);
 }
 
-__device__ inline void load_twiddles(float2* tw, const float2* __restrict__ all, const FftAxis& ax) {
+__device__ inline void load_twiddles(double2* tw, const double2* __restrict__ all, const FftAxis& ax) {
   for (int i = threadIdx.x; i < ax.L; i += blockDim.x) tw[i] = all[ax.tw + i];
 }
 
@@ -284,25 +268,25 @@ struct Source {
     P += rhs * stride;
     if (mode == 2) box_scale += rhs * n_box;
   }
-  __device__ inline float2 at(int box, int u) const {
+  __device__ inline double2 at(int box, int u) const {
     if (mode == 0) {
       const float* b = P + (int64_t)box * 2 * kh;
-      return make_float2(b[u], b[kh + u]);
+      return make_double2(b[u], b[kh + u]);
     }
     const int at = khb == 192 ? (u % 3) * 64 + u / 3 : u;  // pos16 of stage 1
     const unsigned short* q = reinterpret_cast<const unsigned short*>(P + (int64_t)box * 2 * khb) +
                               32 * (at >> 3) + (at & 7);
     if (mode == 1) {
-      auto f = [](unsigned short b) { return __uint_as_float((unsigned)b << 16); };
-      return make_float2(f(q[0]) + f(q[16]), f(q[8]) + f(q[24]));
+      auto f = [](unsigned short b) { return (double)__uint_as_float((unsigned)b << 16); };
+      return make_double2(f(q[0]) + f(q[16]), f(q[8]) + f(q[24]));
     }
-    auto f = [](unsigned short b) { return __half2float(__ushort_as_half(b)); };
-    const float sc = box_scale[box];  // a power of two
-    return make_float2((f(q[0]) + f(q[16])) * sc, (f(q[8]) + f(q[24])) * sc);
+    auto f = [](unsigned short b) { return (double)__half2float(__ushort_as_half(b)); };
+    const double sc = box_scale[box];  // a power of two
+    return make_double2((f(q[0]) + f(q[16])) * sc, (f(q[8]) + f(q[24])) * sc);
   }
 };
 
-extern __shared__ float2 lds[];
+extern __shared__ double2 lds[];
 
 // Workgroups are dealt round robin to the 8 XCDs: give each XCD a contiguous
 // range, so that workgroups sharing memory lines share an L2. The grid is a
@@ -311,288 +295,11 @@ __device__ inline int xcd_block() {
   return (int)(blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
 }
 
-// z transforms: one workgroup per column of boxes (x, y) and site plane mx
-// of it, n_d lines (site rows my).
-__global__ __launch_bounds__(kMaxThreads) void fft_z_kernel(
-    Source src, const int2* __restrict__ map, FftGrid g, const float2* __restrict__ twiddles,
-    float2* __restrict__ out, int64_t out_rhs) {
-  src.select(blockIdx.z);
-  out += blockIdx.z * out_rhs;
-  const int nd = src.nd, L = g.ax[2].L, row = 3 * nd * nd;
-  float2 *a = lds, *tw = a + 3 * L * nd;
-  const int by = blockIdx.y, bx = blockIdx.x / nd, mx = blockIdx.x - bx * nd;
-  const int2* col = map + ((int64_t)bx * g.n[1] + by) * g.n[2];
-  load_twiddles(tw, twiddles, g.ax[2]);
-  const float inv_row = 1.f / row, inv_line = 1.f / (3 * nd);
-  bool any = false;
-  for (int i = threadIdx.x; i < g.n[2] * row; i += blockDim.x) {
-    const int bz = fdiv(i, inv_row), v = i - bz * row;     // v = (my nd + mz) 3 + alpha
-    const int my = fdiv(v, inv_line), t = v - my * 3 * nd;  // t = 3 mz + alpha
-    const int mz = t / 3, al = t - 3 * mz;
-    const int box = col[bz].x;
-    float2 z = make_float2(0.f, 0.f);
-    if (box >= 0) {
-      z = src.at(box, mx * row + v);
-      any = true;
-    }
-    a[((bz * nd + mz) * nd + my) * 3 + al] = z;
-  }
-  const int X = bx * nd + mx, s = g.s[2];
-  float2* o = out + ((int64_t)X * g.s[1] + by * nd) * L * 3;
-  if (!__syncthreads_or(any)) {  // a column without boxes transforms to zeros
-    for (int i = threadIdx.x; i < 3 * L * nd; i += blockDim.x) o[i] = make_float2(0.f, 0.f);
-    return;
-  }
-  transform<false>(
-      g.ax[2], nd, tw, a,
-      [&](int pos, int line, float2 (&v)[3]) {
-#pragma unroll
-        for (int al = 0; al < 3; ++al)
-          v[al] = pos < s ? a[(pos * nd + line) * 3 + al] : make_float2(0.f, 0.f);
-      },
-      [&](int pos, int line, const float2 (&v)[3]) {
-        float2* q = o + 3 * (line * L + pos);
-#pragma unroll
-        for (int al = 0; al < 3; ++al) q[al] = v[al];
-      });
-}
+// ---------------------------------------------------- what reaches a box
 
-// y transforms of w neighbouring lines (x, kz with kz fastest); forward from
-// s to L positions, backward from L to s.
-template <bool INV>
-__global__ __launch_bounds__(kMaxThreads) void fft_y_kernel(
-    const float2* __restrict__ in, FftGrid g, const float2* __restrict__ twiddles,
-    float2* __restrict__ out, int w, int64_t in_rhs, int64_t out_rhs) {
-  in += blockIdx.y * in_rhs;
-  out += blockIdx.y * out_rhs;
-  const int L = g.ax[1].L, s = g.s[1], Lz = g.ax[2].L;
-  const int nin = INV ? L : s, nout = INV ? s : L;
-  float2 *a = lds, *tw = a + 3 * L * w;
-  const int all = g.s[0] * Lz, l0 = xcd_block() * w;
-  if (l0 >= all) return;
-  load_twiddles(tw, twiddles, g.ax[1]);
-  const float inv_lz = 1.f / Lz;
-  // line l = (x, kz): its first value in an array of n positions along y
-  auto first = [&](int l, int n) {
-    const int x = l / Lz;
-    return ((int64_t)x * n * Lz + (l - x * Lz)) * 3;
-  };
-  transform<INV>(
-      g.ax[1], w, tw, a,
-      [&](int pos, int line, float2 (&v)[3]) {
-        const int l = l0 + line;
-        const float2* p = in + first(l, nin) + 3 * pos * Lz;
-#pragma unroll
-        for (int al = 0; al < 3; ++al)
-          v[al] = pos < nin && l < all ? p[al] : make_float2(0.f, 0.f);
-      },
-      [&](int pos, int line, const float2 (&v)[3]) {
-        const int l = l0 + line;
-        float2* p = out + first(l, nout) + 3 * pos * Lz;
-        if (pos < nout && l < all) {
-#pragma unroll
-          for (int al = 0; al < 3; ++al) p[al] = v[al];
-        }
-      });
-}
-
-// The last forward stage along x, the product with the spectrum and the
-// first backward stage: butterfly j ends with the frequencies j + r L / R in
-// registers, which is what the backward transform's first butterfly of the
-// same radix starts from.
-template <int R, bool TW, class Load, class Store, class Spec>
-__device__ inline void middle_stage(int L, int w, float inv_w, const float2* tw, Load load,
-                                    Store store, Spec spectrum) {
-  const int m = L / R, i = threadIdx.x;
-  const int j = fdiv(i, inv_w), line = i - j * w;
-  const bool on = i < m * w;
-  float2 v[R][3];
-  if (on) {
-#pragma unroll
-    for (int r = 0; r < R; ++r) load(j + r * m, line, v[r]);
-    if (TW) {
-#pragma unroll
-      for (int r = 1; r < R; ++r) {
-        const float2 t = tw[r * j];  // Ns = m: k = j
-#pragma unroll
-        for (int al = 0; al < 3; ++al) v[r][al] = cmul(v[r][al], t);
-      }
-    }
-#pragma unroll
-    for (int al = 0; al < 3; ++al) {
-      float2 x[R];
-#pragma unroll
-      for (int r = 0; r < R; ++r) x[r] = v[r][al];
-      Butterfly<R, false>::run(x);
-#pragma unroll
-      for (int r = 0; r < R; ++r) v[r][al] = x[r];
-    }
-#pragma unroll
-    for (int r = 0; r < R; ++r) spectrum(j + r * m, line, v[r]);
-#pragma unroll
-    for (int al = 0; al < 3; ++al) {
-      float2 x[R];
-#pragma unroll
-      for (int r = 0; r < R; ++r) x[r] = v[r][al];
-      Butterfly<R, true>::run(x);
-#pragma unroll
-      for (int r = 0; r < R; ++r) v[r][al] = x[r];
-    }
-  }
-  __syncthreads();
-  if (on) {
-#pragma unroll
-    for (int r = 0; r < R; ++r) store(j * R + r, line, v[r]);
-  }
-  __syncthreads();
-}
-
-// Along x: transform, product with the spectrum, transform back, for w
-// neighbouring lines (ky, kz). The spectrum is stored for frequencies
-// 0 .. L/2 per axis; D is even along its two equal axes and odd along each
-// of two different ones, so a mirrored frequency changes the sign of the
-// components odd along that axis. The backward transform takes the radices
-// in the opposite order, so that the two stages around the product share
-// their butterflies.
-__global__ __launch_bounds__(kMaxThreads) void fft_x_kernel(
-    float2* __restrict__ data, FftGrid g, const float2* __restrict__ twiddles,
-    const float4* __restrict__ spec, int w, int64_t rhs) {
-  data += blockIdx.y * rhs;
-  const int L = g.ax[0].L, s = g.s[0], Ly = g.ax[1].L, Lz = g.ax[2].L;
-  const int hy = Ly / 2 + 1, hz = Lz / 2 + 1;
-  float2 *a = lds, *tw = a + 3 * L * w;
-  const int plane = Ly * Lz, l0 = xcd_block() * w;
-  if (l0 >= plane) return;
-  load_twiddles(tw, twiddles, g.ax[0]);
-  const float inv_w = 1.f / (float)w;
-  auto load = [&](int pos, int line, float2 (&v)[3]) {
-    const int l = l0 + line;
-    const float2* p = data + ((int64_t)pos * plane + l) * 3;
-#pragma unroll
-    for (int al = 0; al < 3; ++al) v[al] = pos < s && l < plane ? p[al] : make_float2(0.f, 0.f);
-  };
-  auto store = [&](int pos, int line, const float2 (&v)[3]) {
-    const int l = l0 + line;
-    float2* p = data + ((int64_t)pos * plane + l) * 3;
-    if (pos < s && l < plane) {
-#pragma unroll
-      for (int al = 0; al < 3; ++al) p[al] = v[al];
-    }
-  };
-  auto spectrum = [&](int kx, int line, float2 (&f)[3]) {
-    const int l = min(l0 + line, plane - 1);
-    const int ky = l / Lz, kz = l - ky * Lz;
-    const bool mx = 2 * kx > L, my = 2 * ky > Ly, mz = 2 * kz > Lz;
-    const float4* k = spec + 3 * (((int64_t)(mx ? L - kx : kx) * hy + (my ? Ly - ky : ky)) * hz +
-                                  (mz ? Lz - kz : kz));
-    const float4 k0 = k[0], k1 = k[1], k2 = k[2];  // xx, yy | zz, xy | xz, yz
-    const float sxy = mx == my ? 1.f : -1.f, sxz = mx == mz ? 1.f : -1.f,
-                syz = my == mz ? 1.f : -1.f;
-    const float2 xx = make_float2(k0.x, k0.y), yy = make_float2(k0.z, k0.w);
-    const float2 zz = make_float2(k1.x, k1.y), xy = make_float2(k1.z * sxy, k1.w * sxy);
-    const float2 xz = make_float2(k2.x * sxz, k2.y * sxz), yz = make_float2(k2.z * syz, k2.w * syz);
-    const float2 u = f[0], v = f[1], z = f[2];
-    f[0] = cfma(xx, u, cfma(xy, v, cmul(xz, z)));
-    f[1] = cfma(xy, u, cfma(yy, v, cmul(yz, z)));
-    f[2] = cfma(xz, u, cfma(yz, v, cmul(zz, z)));
-  };
-  const Buffer get{a, w};
-  const BufferStore put{a, w};
-  const FftAxis& ax = g.ax[0];
-  const int n = ax.stages;
-  __syncthreads();
-  if (n == 0) {
-    if ((int)threadIdx.x < w) {
-      float2 v[3];
-      load(0, threadIdx.x, v);
-      spectrum(0, threadIdx.x, v);
-      store(0, threadIdx.x, v);
-    }
-    return;
-  }
-  if (n == 1) {
-    switch (L) {  // uniform
-      case 2: middle_stage<2, false>(L, w, inv_w, tw, load, store, spectrum); break;
-      case 3: middle_stage<3, false>(L, w, inv_w, tw, load, store, spectrum); break;
-      case 4: middle_stage<4, false>(L, w, inv_w, tw, load, store, spectrum); break;
-      case 5: middle_stage<5, false>(L, w, inv_w, tw, load, store, spectrum); break;
-      default: middle_stage<6, false>(L, w, inv_w, tw, load, store, spectrum); break;
-    }
-    return;
-  }
-  stage_of<false, false, true, false>(ax.radix[0], L, w, inv_w, tw, 1, load, put);
-  int Ns = ax.radix[0];
-  for (int st = 1; st + 1 < n; ++st) {
-    stage_of<false, true, false, false>(ax.radix[st], L, w, inv_w, tw, Ns, get, put);
-    Ns *= ax.radix[st];
-  }
-  switch (ax.radix[n - 1]) {  // uniform; at most 6 (fft_axis)
-    case 2: middle_stage<2, true>(L, w, inv_w, tw, get, put, spectrum); break;
-    case 3: middle_stage<3, true>(L, w, inv_w, tw, get, put, spectrum); break;
-    case 4: middle_stage<4, true>(L, w, inv_w, tw, get, put, spectrum); break;
-    case 5: middle_stage<5, true>(L, w, inv_w, tw, get, put, spectrum); break;
-    default: middle_stage<6, true>(L, w, inv_w, tw, get, put, spectrum); break;
-  }
-  Ns = ax.radix[n - 1];
-  for (int st = n - 2; st > 0; --st) {
-    stage_of<true, true, false, false>(ax.radix[st], L, w, inv_w, tw, Ns, get, put);
-    Ns *= ax.radix[st];
-  }
-  stage_of<true, true, false, true>(ax.radix[0], L, w, inv_w, tw, Ns, get, store);
-}
-
-// Backward z transforms into the boxes' rows: the lines of fft_z_kernel.
-__global__ __launch_bounds__(kMaxThreads) void ifft_z_kernel(
-    const float2* __restrict__ in, const int2* __restrict__ map, FftGrid g,
-    const float2* __restrict__ twiddles, float* __restrict__ part, int nd, int kh,
-    int64_t in_rhs, int64_t part_rhs) {
-  in += blockIdx.z * in_rhs;
-  part += blockIdx.z * part_rhs;
-  const int L = g.ax[2].L, row = 3 * nd * nd, nu = row * nd, s = g.s[2];
-  float2 *a = lds, *tw = a + 3 * L * nd;
-  const int by = blockIdx.y, bx = blockIdx.x / nd, mx = blockIdx.x - bx * nd;
-  const int2* col = map + ((int64_t)bx * g.n[1] + by) * g.n[2];
-  bool any = false;
-  for (int i = threadIdx.x; i < g.n[2]; i += blockDim.x) any = any || col[i].y >= 0;
-  if (!__syncthreads_or(any)) return;  // a column without rows
-  load_twiddles(tw, twiddles, g.ax[2]);
-  const int X = bx * nd + mx;
-  const float2* p = in + ((int64_t)X * g.s[1] + by * nd) * L * 3;
-  transform<true>(
-      g.ax[2], nd, tw, a,
-      [&](int pos, int line, float2 (&v)[3]) {
-        const float2* q = p + 3 * (line * L + pos);
-#pragma unroll
-        for (int al = 0; al < 3; ++al) v[al] = q[al];
-      },
-      [&](int pos, int line, const float2 (&v)[3]) {
-        if (pos < s) {
-#pragma unroll
-          for (int al = 0; al < 3; ++al) a[(pos * nd + line) * 3 + al] = v[al];
-        }
-      });
-  const float inv_row = 1.f / row, inv_line = 1.f / (3 * nd);
-  for (int i = threadIdx.x; i < g.n[2] * row; i += blockDim.x) {
-    const int bz = fdiv(i, inv_row), v = i - bz * row;
-    const int my = fdiv(v, inv_line), t = v - my * 3 * nd;
-    const int mz = t / 3, al = t - 3 * mz;
-    const int at = col[bz].y;
-    if (at < 0) continue;
-    const float2 z = a[((bz * nd + mz) * nd + my) * 3 + al];
-    float* q = part + (int64_t)at * 2 * kh + mx * row + v;  // [Er | Ei] of N_u each
-    q[0] = z.x;
-    q[nu] = z.y;
-  }
-}
-
-// ---------------------------------------------------------------- spectrum
-
-// Component e (xx, yy, zz, xy, xz, yz) of D(R) in FP64, zero where the
-// convolution leaves the pair to the masked operators.
-__device__ double2 green_component(int e, int dx, int dy, int dz, double step, double k,
-                                   double eta, int nd) {
-  if (max(dx, max(dy, dz)) < 2 * nd) return make_double2(0.0, 0.0);
-  const int pa[6] = {0, 1, 2, 0, 0, 1}, pb[6] = {0, 1, 2, 1, 2, 2};
+// D(R), R = step (dx, dy, dz), in FP64: xx, yy, zz, xy, xz, yz.
+__device__ void green(int dx, int dy, int dz, double step, double k, double eta,
+                      double2 (&D)[6]) {
   const double R[3] = {step * dx, step * dy, step * dz};
   const double r2 = R[0] * R[0] + R[1] * R[1] + R[2] * R[2];
   const double r = sqrt(r2), kr = k * r, ik = 1.0 / kr;
@@ -601,11 +308,335 @@ __device__ double2 green_component(int e, int dx, int dy, int dz, double step, d
   // psi = -j k eta e^{-j kr} / (4 pi r)
   const double f = k * eta / (4.0 * 3.14159265358979323846 * r);
   const double pr = -f * sn, pi = -f * cs;
-  const double rr = R[pa[e]] * R[pb[e]] / r2, iso = pa[e] == pb[e] ? 1.0 : 0.0;
-  const double tr = iso * (1.0 - ik * ik) - rr * (1.0 - 3.0 * ik * ik);
-  const double ti = -iso * ik + rr * 3.0 * ik;
-  return make_double2(pr * tr - pi * ti, pr * ti + pi * tr);
+  const int pa[6] = {0, 1, 2, 0, 0, 1}, pb[6] = {0, 1, 2, 1, 2, 2};
+#pragma unroll
+  for (int e = 0; e < 6; ++e) {
+    const double rr = R[pa[e]] * R[pb[e]] / r2, iso = e < 3 ? 1.0 : 0.0;
+    const double tr = iso * (1.0 - ik * ik) - rr * (1.0 - 3.0 * ik * ik);
+    const double ti = -iso * ik + rr * 3.0 * ik;
+    D[e] = make_double2(pr * tr - pi * ti, pr * ti + pi * tr);
+  }
 }
+
+// Largest real or imaginary part of every box vector of a lattice; a
+// wavefront per box.
+__global__ __launch_bounds__(kThreads) void norm_kernel(Source src, const int4* __restrict__ cells,
+                                                        int nu, float* __restrict__ norm) {
+  src.select(blockIdx.y);
+  const int64_t box = (int64_t)blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
+  if (box >= src.n_box || cells[box].w < 0) return;
+  const int lane = threadIdx.x & 63;
+  double m = 0.0;
+  for (int u = lane; u < nu; u += 64) {
+    const double2 v = src.at((int)box, u);
+    m = fmax(m, fmax(fabs(v.x), fabs(v.y)));
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) m = fmax(m, __shfl_xor(m, o, 64));
+  if (lane == 0) norm[blockIdx.y * src.n_box + box] = (float)fmin(m, 3.4028234663852886e38);
+}
+
+// Bounding grid of the strong boxes of one lattice and right-hand side.
+struct Reach {
+  int lo[3], hi[3];
+  __device__ inline bool empty() const { return lo[0] > hi[0]; }
+  // No strong box is far from (x, y, z): all are within one of it on every
+  // axis (true without strong boxes).
+  __device__ inline bool near(int x, int y, int z) const {
+    return lo[0] >= x - 1 && hi[0] <= x + 1 && lo[1] >= y - 1 && hi[1] <= y + 1 &&
+           lo[2] >= z - 1 && hi[2] <= z + 1;
+  }
+};
+
+static_assert(sizeof(Reach) == kReachBytes && alignof(Reach) <= 4, "fft_scratch_bytes");
+
+// Per lattice and right-hand side 27 workgroups, one for each box that may be
+// near all strong ones. Each finds the strong boxes (the first one also
+// leaves them for ifft_z); where its box exists and is near all, it sums the
+// site pairs that the convolution stands for, from the boxes that are not
+// zero: a thread per test site and every (512 / sites)-th source site, D
+// evaluated in FP64 for each. Reads 4 bytes per box in the ordinary case,
+// about 1 us of latency; a box that sees 3,338 weak ones would take about
+// 5 ms, as many as all pairs did.
+constexpr int kReachThreads = 512;
+__global__ __launch_bounds__(kReachThreads) void reach_kernel(
+    Source src, const int2* __restrict__ map, const int4* __restrict__ cells,
+    const int4* __restrict__ grids, const float* __restrict__ norm, double step, double k,
+    double eta, int nu, Reach* __restrict__ reach, float* __restrict__ part, int64_t part_rhs) {
+  __shared__ float wave_max[kReachThreads / 64];
+  __shared__ Reach strong;
+  __shared__ double2 sums[kReachThreads][3];
+  const int rhs = blockIdx.z, t = threadIdx.x;
+  src.select(rhs);
+  norm += rhs * src.n_box;
+  const int4 ga = grids[2 * blockIdx.y], gb = grids[2 * blockIdx.y + 1];
+  const int first = ga.x, count = ga.y;           // its boxes
+  const int nx = gb.x, ny = gb.y, nz = gb.z;
+  const int64_t cell0 = ((int64_t)ga.w << 32) | (unsigned)ga.z;
+  float m = 0.f;
+#pragma unroll 8
+  for (int i = t; i < count; i += kReachThreads) m = fmaxf(m, norm[first + i]);
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
+  if ((t & 63) == 0) wave_max[t >> 6] = m;
+  if (t < 3) {
+    strong.lo[t] = 0x7fffffff;
+    strong.hi[t] = -1;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < kReachThreads / 64; ++w) m = fmaxf(m, wave_max[w]);
+  const float bar = m * 0x1p-24f;
+  int lo[3] = {0x7fffffff, 0x7fffffff, 0x7fffffff}, hi[3] = {-1, -1, -1};
+#pragma unroll 4
+  for (int i = t; i < count; i += kReachThreads) {
+    const float v = norm[first + i];
+    const int4 c = cells[first + i];
+    if (v > 0.f && v >= bar) {
+      lo[0] = min(lo[0], c.x);
+      lo[1] = min(lo[1], c.y);
+      lo[2] = min(lo[2], c.z);
+      hi[0] = max(hi[0], c.x);
+      hi[1] = max(hi[1], c.y);
+      hi[2] = max(hi[2], c.z);
+    }
+  }
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      lo[d] = min(lo[d], __shfl_xor(lo[d], o, 64));
+      hi[d] = max(hi[d], __shfl_xor(hi[d], o, 64));
+    }
+    if ((t & 63) == 0) {
+      atomicMin(&strong.lo[d], lo[d]);
+      atomicMax(&strong.hi[d], hi[d]);
+    }
+  }
+  __syncthreads();
+  if (blockIdx.x == 0 && t == 0) reach[rhs * gridDim.y + blockIdx.y] = strong;
+  if (strong.empty()) return;
+  const int x = strong.hi[0] - 1 + (int)blockIdx.x / 9, y = strong.hi[1] - 1 + (int)blockIdx.x / 3 % 3,
+            z = strong.hi[2] - 1 + (int)blockIdx.x % 3;
+  if (x < 0 || y < 0 || z < 0 || x >= nx || y >= ny || z >= nz || !strong.near(x, y, z)) return;
+  const int at = map[cell0 + ((int64_t)x * ny + y) * nz + z].y;
+  if (at < 0) return;
+  // site l of the test box, source sites chunk, chunk + chunks, ...
+  const int nd = src.nd, nd2 = nd * nd, nd3 = nd2 * nd;
+  const int chunks = kReachThreads / nd3, l = t % nd3, chunk = t / nd3;
+  const int lx = x * nd + l / nd2, ly = y * nd + l / nd % nd, lz = z * nd + l % nd;
+  double2 E[3];
+#pragma unroll
+  for (int al = 0; al < 3; ++al) E[al] = make_double2(0.0, 0.0);
+  if (chunk < chunks)
+    for (int q = chunk; q < count * nd3; q += chunks) {
+      const int i = q / nd3, s = q - i * nd3;
+      if (!(norm[first + i] > 0.f)) continue;
+      const int4 c = cells[first + i];
+      const int dx = lx - (c.x * nd + s / nd2), dy = ly - (c.y * nd + s / nd % nd),
+                dz = lz - (c.z * nd + s % nd);
+      if (max(abs(dx), max(abs(dy), abs(dz))) < 2 * nd) continue;
+      double2 D[6];
+      green(dx, dy, dz, step, k, eta, D);
+      const double2 px = src.at(first + i, 3 * s), py = src.at(first + i, 3 * s + 1),
+                    pz = src.at(first + i, 3 * s + 2);
+      E[0] = cfma(D[0], px, cfma(D[3], py, cfma(D[4], pz, E[0])));
+      E[1] = cfma(D[3], px, cfma(D[1], py, cfma(D[5], pz, E[1])));
+      E[2] = cfma(D[4], px, cfma(D[5], py, cfma(D[2], pz, E[2])));
+    }
+#pragma unroll
+  for (int al = 0; al < 3; ++al) sums[t][al] = E[al];
+  __syncthreads();
+  for (int left = chunks; left > 1;) {
+    const int half = (left + 1) / 2;
+    if (chunk < left - half)
+#pragma unroll
+      for (int al = 0; al < 3; ++al) sums[t][al] = cadd(sums[t][al], sums[t + half * nd3][al]);
+    __syncthreads();
+    left = half;
+  }
+  if (t < nd3) {
+    float* row = part + rhs * part_rhs + (int64_t)at * 2 * src.kh + 3 * t;  // [Er | Ei]
+#pragma unroll
+    for (int al = 0; al < 3; ++al) {
+      row[al] = (float)sums[t][al].x;
+      row[nu + al] = (float)sums[t][al].y;
+    }
+  }
+}
+
+// z transforms: `groups` workgroups per column of boxes (x, y) and site plane
+// mx of it, which has n_d lines (site rows my).
+__global__ __launch_bounds__(kMaxFftThreads) void fft_z_kernel(
+    Source src, const int2* __restrict__ map, FftGrid g, const double2* __restrict__ twiddles,
+    double2* __restrict__ out, int64_t out_rhs, int groups) {
+  src.select(blockIdx.z);
+  out += blockIdx.z * out_rhs;
+  const int nd = src.nd, w = nd / groups, L = g.ax[2].L, row = 3 * nd * nd;
+  double2 *a = lds, *tw = a + 3 * L * w;
+  const int by = blockIdx.y, X = blockIdx.x / groups, my0 = (blockIdx.x - X * groups) * w;
+  const int bx = X / nd, mx = X - bx * nd;
+  const int2* col = map + ((int64_t)bx * g.n[1] + by) * g.n[2];
+  load_twiddles(tw, twiddles, g.ax[2]);
+  const int part = 3 * nd * w;  // a box's values here
+  const float inv_part = 1.f / part, inv_line = 1.f / (3 * nd);
+  bool any = false;
+  for (int i = threadIdx.x; i < g.n[2] * part; i += blockDim.x) {
+    const int bz = fdiv(i, inv_part), v = i - bz * part;   // v = (line nd + mz) 3 + alpha
+    const int line = fdiv(v, inv_line), t = v - line * 3 * nd;  // t = 3 mz + alpha
+    const int mz = t / 3, al = t - 3 * mz;
+    const int box = col[bz].x;
+    double2 z = make_double2(0.0, 0.0);
+    if (box >= 0) {
+      z = src.at(box, mx * row + my0 * 3 * nd + v);
+      any = true;
+    }
+    a[((bz * nd + mz) * w + line) * 3 + al] = z;
+  }
+  const int s = g.s[2];
+  double2* o = out + ((int64_t)X * g.s[1] + by * nd + my0) * L * 3;
+  if (!__syncthreads_or(any)) {  // a column without boxes transforms to zeros
+    for (int i = threadIdx.x; i < 3 * L * w; i += blockDim.x) o[i] = make_double2(0.0, 0.0);
+    return;
+  }
+  const Lane t(w);
+  const int line = t.line / 3, al = t.line - 3 * line;
+  o += 3 * line * L + al;
+  transform<false>(
+      g.ax[2], t, tw, a,
+      [&](int pos) { return pos < s ? a[pos * t.w3 + t.line] : make_double2(0.0, 0.0); },
+      [&](int pos, double2 v) { o[3 * pos] = v; });
+}
+
+// y transforms of w neighbouring lines (x, kz with kz fastest); forward from
+// s to L positions, backward from L to s.
+template <bool INV>
+__global__ __launch_bounds__(kMaxFftThreads) void fft_y_kernel(
+    const double2* __restrict__ in, FftGrid g, const double2* __restrict__ twiddles,
+    double2* __restrict__ out, int w, int64_t in_rhs, int64_t out_rhs) {
+  const int L = g.ax[1].L, s = g.s[1], Lz = g.ax[2].L;
+  const int nin = INV ? L : s, nout = INV ? s : L;
+  double2 *a = lds, *tw = a + 3 * L * w;
+  const int all = g.s[0] * Lz, l0 = xcd_block() * w;
+  if (l0 >= all) return;
+  load_twiddles(tw, twiddles, g.ax[1]);
+  const Lane t(w);
+  const int l = l0 + t.line / 3;
+  const bool live = l < all;  // line l = (x, kz)
+  const int x = l / Lz, kz = l - x * Lz, at = 3 * kz + t.line % 3;
+  const double2* p = in + blockIdx.y * in_rhs + (int64_t)x * nin * Lz * 3 + at;
+  double2* o = out + blockIdx.y * out_rhs + (int64_t)x * nout * Lz * 3 + at;
+  transform<INV>(
+      g.ax[1], t, tw, a,
+      [&](int pos) { return live && pos < nin ? p[3 * pos * Lz] : make_double2(0.0, 0.0); },
+      [&](int pos, double2 v) {
+        if (live && pos < nout) o[3 * pos * Lz] = v;
+      });
+}
+
+// Along x: transform, product with the spectrum, transform back, for w (a
+// power of two) neighbouring lines (ky, kz). The spectrum is stored for
+// frequencies 0 .. L/2 per axis; D is even along its two equal axes and odd
+// along each of two different ones, so a frequency mirrored along some axes
+// (s = -1) has component (alpha, beta) times s_alpha s_beta. For the product a
+// thread takes the three components of every (blockDim / w)-th position of a
+// line.
+__global__ __launch_bounds__(kMaxFftThreads) void fft_x_kernel(
+    double2* __restrict__ data, FftGrid g, const double2* __restrict__ twiddles,
+    const double2* __restrict__ spec, int w, int64_t rhs) {
+  data += blockIdx.y * rhs;
+  const FftAxis& ax = g.ax[0];
+  const int L = ax.L, s = g.s[0], Ly = g.ax[1].L, Lz = g.ax[2].L;
+  double2 *a = lds, *tw = a + 3 * L * w;
+  const int plane = Ly * Lz, l0 = xcd_block() * w;
+  if (l0 >= plane) return;
+  load_twiddles(tw, twiddles, ax);
+  const Lane t(w);
+  const bool live = l0 + t.line / 3 < plane;
+  double2* p = data + (int64_t)l0 * 3 + t.line;
+  const int64_t step = 3LL * plane;
+  transform<false>(
+      ax, t, tw, a,
+      [&](int pos) { return live && pos < s ? p[pos * step] : make_double2(0.0, 0.0); },
+      [&](int pos, double2 v) { a[pos * t.w3 + t.line] = v; });
+  {
+    const int line = threadIdx.x & (w - 1);
+    const int l = min(l0 + line, plane - 1), ky = l / Lz, kz = l - ky * Lz;
+    const int hy = Ly / 2 + 1, hz = Lz / 2 + 1;
+    const bool my = 2 * ky > Ly, mz = 2 * kz > Lz;
+    const double2* kyz = spec + 6 * ((int64_t)(my ? Ly - ky : ky) * hz + (mz ? Lz - kz : kz));
+    const int64_t kstep = 6LL * hy * hz;
+    const double syz = my == mz ? 1.0 : -1.0;
+    for (int pos = threadIdx.x / w; pos < L; pos += blockDim.x / w) {
+      const bool mx = 2 * pos > L;
+      const double2* k = kyz + (mx ? L - pos : pos) * kstep;
+      const double sxy = mx == my ? 1.0 : -1.0, sxz = mx == mz ? 1.0 : -1.0;
+      const double2 xx = k[0], yy = k[1], zz = k[2];
+      const double2 xy = make_double2(k[3].x * sxy, k[3].y * sxy);
+      const double2 xz = make_double2(k[4].x * sxz, k[4].y * sxz);
+      const double2 yz = make_double2(k[5].x * syz, k[5].y * syz);
+      double2* f = a + 3 * (pos * w + line);
+      const double2 u = f[0], v = f[1], z = f[2];
+      f[0] = cfma(xx, u, cfma(xy, v, cmul(xz, z)));
+      f[1] = cfma(xy, u, cfma(yy, v, cmul(yz, z)));
+      f[2] = cfma(xz, u, cfma(yz, v, cmul(zz, z)));
+    }
+  }
+  transform<true>(
+      ax, t, tw, a, [&](int pos) { return a[pos * t.w3 + t.line]; },
+      [&](int pos, double2 v) {
+        if (live && pos < s) p[pos * step] = v;
+      });
+}
+
+// Backward z transforms into the boxes' rows: the lines of fft_z_kernel. The
+// rows of boxes that no strong box is far from are reach_kernel's, or zero
+// where no box is strong.
+__global__ __launch_bounds__(kMaxFftThreads) void ifft_z_kernel(
+    const double2* __restrict__ in, const int2* __restrict__ map, FftGrid g,
+    const double2* __restrict__ twiddles, float* __restrict__ part, int nd, int kh,
+    int64_t in_rhs, int64_t part_rhs, const Reach* __restrict__ reach, int n_grid, int groups) {
+  in += blockIdx.z * in_rhs;
+  part += blockIdx.z * part_rhs;
+  const Reach strong = reach[blockIdx.z * n_grid];
+  const int L = g.ax[2].L, w = nd / groups, row = 3 * nd * nd, nu = row * nd, s = g.s[2];
+  double2 *a = lds, *tw = a + 3 * L * w;
+  const int by = blockIdx.y, X = blockIdx.x / groups, my0 = (blockIdx.x - X * groups) * w;
+  const int bx = X / nd, mx = X - bx * nd;
+  const int2* col = map + ((int64_t)bx * g.n[1] + by) * g.n[2];
+  bool any = false;
+  for (int i = threadIdx.x; i < g.n[2]; i += blockDim.x) any = any || col[i].y >= 0;
+  if (!__syncthreads_or(any)) return;  // a column without rows
+  load_twiddles(tw, twiddles, g.ax[2]);
+  const Lane t(w);
+  const int line = t.line / 3;
+  const double2* p =
+      in + ((int64_t)X * g.s[1] + by * nd + my0 + line) * L * 3 + (t.line - 3 * line);
+  transform<true>(
+      g.ax[2], t, tw, a, [&](int pos) { return p[3 * pos]; },
+      [&](int pos, double2 v) {
+        if (pos < s) a[pos * t.w3 + t.line] = v;
+      });
+  const int values = 3 * nd * w;  // a box's values here
+  const float inv_values = 1.f / values, inv_line = 1.f / (3 * nd);
+  for (int i = threadIdx.x; i < g.n[2] * values; i += blockDim.x) {
+    const int bz = fdiv(i, inv_values), v = i - bz * values;
+    const int ln = fdiv(v, inv_line), q = v - ln * 3 * nd;
+    const int mz = q / 3, al = q - 3 * mz;
+    const int at = col[bz].y;
+    if (at < 0) continue;
+    double2 z = a[((bz * nd + mz) * w + ln) * 3 + al];
+    if (strong.near(bx, by, bz)) {
+      if (!strong.empty()) continue;
+      z = make_double2(0.0, 0.0);
+    }
+    float* e = part + (int64_t)at * 2 * kh + mx * row + my0 * 3 * nd + v;  // [Er | Ei]
+    e[0] = (float)z.x;
+    e[nu] = (float)z.y;
+  }
+}
+
+// ---------------------------------------------------------------- spectrum
 
 // Weight of the value at distance d for frequency kf of one axis of a real
 // even (cosine) or odd (sine) sequence of period L.
@@ -625,7 +656,12 @@ __global__ __launch_bounds__(kThreads) void spectrum_z_kernel(FftGrid g, int e, 
   __shared__ double2 D[kMaxFftLength];
   const int x = blockIdx.x, y = blockIdx.y, L = g.ax[2].L, h = L / 2 + 1;
   for (int z = threadIdx.x; z < g.s[2]; z += kThreads)
-    D[z] = green_component(e, x, y, z, step, k, eta, nd);
+  {
+    double2 v[6];
+    const bool kept = max(x, max(y, z)) >= 2 * nd;  // the rest: masked operators
+    if (kept) green(x, y, z, step, k, eta, v);
+    D[z] = kept ? v[e] : make_double2(0.0, 0.0);
+  }
   __syncthreads();
   for (int kz = threadIdx.x; kz < h; kz += kThreads) {
     double2 s = make_double2(0.0, 0.0);
@@ -662,7 +698,7 @@ __global__ __launch_bounds__(kThreads) void spectrum_y_kernel(FftGrid g, int e,
 // transforms; a pair of odd axes carries (-j)^2 = -1.
 __global__ __launch_bounds__(kThreads) void spectrum_x_kernel(FftGrid g, int e,
                                                               const double2* __restrict__ U,
-                                                              float2* __restrict__ spec) {
+                                                              double2* __restrict__ spec) {
   __shared__ double w[kMaxFftLength];
   const int kx = blockIdx.x, ky = blockIdx.y, L = g.ax[0].L;
   const int hy = g.ax[1].L / 2 + 1, hz = g.ax[2].L / 2 + 1;
@@ -677,24 +713,36 @@ __global__ __launch_bounds__(kThreads) void spectrum_x_kernel(FftGrid g, int e,
       s.y = fma(w[x], t.y, s.y);
     }
     // six components side by side: xx, yy, zz, xy, xz, yz
-    spec[6 * (((int64_t)kx * hy + ky) * hz + kz) + e] =
-        make_float2((float)(s.x * f), (float)(s.y * f));
+    spec[6 * (((int64_t)kx * hy + ky) * hz + kz) + e] = make_double2(s.x * f, s.y * f);
   }
 }
 
-// Lines of a workgroup, of `all`: as many as the LDS budget and about 320
-// threads take, but no fewer than 1,024 workgroups (four per compute unit)
-// while a workgroup keeps a wavefront busy.
+// Lines of a workgroup, of `all`: as many as the LDS budget and 512 threads
+// take, but no fewer than 1,024 workgroups (four per compute unit) while a
+// workgroup keeps a wavefront busy.
 int fit_lines(const FftAxis& ax, int all) {
   int w = 64;
-  while (w > 1 && (3 * (size_t)ax.L * w * sizeof(float2) > kLineBytes ||
-                   ax.butterflies() * w > 320 ||
-                   (all < 1024 * w && ax.butterflies() * w >= 128)))
+  while (w > 1 && (3 * (size_t)ax.L * w * sizeof(double2) > kLineBytes ||
+                   3 * ax.butterflies() * w > 512 ||
+                   (all < 1024 * w && 3 * ax.butterflies() * w >= 128)))
     w /= 2;
   return w;
 }
-size_t line_bytes(const FftAxis& ax, int w) { return (3 * (size_t)ax.L * w + ax.L) * sizeof(float2); }
-dim3 line_threads(const FftAxis& ax, int w) { return dim3((ax.butterflies() * w + 63) / 64 * 64); }
+// Workgroups that share the n_d z lines of a plane of boxes.
+int z_groups(const FftAxis& ax, int nd) {
+  int groups = 1;
+  while (nd % groups || 3 * ax.butterflies() * (nd / groups) > 512) {
+    if (groups == nd) break;
+    ++groups;
+  }
+  return groups;
+}
+size_t line_bytes(const FftAxis& ax, int w) {
+  return (3 * (size_t)ax.L * w + ax.L) * sizeof(double2);
+}
+dim3 line_threads(const FftAxis& ax, int w) {
+  return dim3((3 * ax.butterflies() * w + 63) / 64 * 64);
+}
 
 // Workgroups of `lines` lines each, a multiple of 8 (xcd_block).
 unsigned blocks_of(int all, int lines) {
@@ -723,7 +771,7 @@ int launch_fft_spectra(const Plan& p, hipStream_t s) {
     double2* T = reinterpret_cast<double2*>(p.d_fft);
     const int hx = g.ax[0].L / 2 + 1, hy = g.ax[1].L / 2 + 1, hz = g.ax[2].L / 2 + 1;
     double2* U = T + (int64_t)g.s[0] * g.s[1] * hz;
-    float2* spec = reinterpret_cast<float2*>(p.d_fft_spec) + g.spec;
+    double2* spec = reinterpret_cast<double2*>(p.d_fft_spec) + g.spec;
     for (int e = 0; e < 6; ++e) {
       hipLaunchKernelGGL(spectrum_z_kernel, dim3(g.s[0], g.s[1]), dim3(kThreads), 0, s, g, e,
                          step, p.k, p.eta, p.n_d, T);
@@ -736,7 +784,7 @@ int launch_fft_spectra(const Plan& p, hipStream_t s) {
 
 int launch_fft(const Plan& p, const float* P, float* part, int nrhs, hipStream_t s,
                hipEvent_t start, hipEvent_t stop) {
-  const float2* tw = reinterpret_cast<const float2*>(p.d_fft_tw);
+  const double2* tw = reinterpret_cast<const double2*>(p.d_fft_tw);
   const int64_t part_rhs = p.rest->n_pairs() * p.pstride();
   int64_t zmax = 0, ymax = 0;
   for (const FftGrid& g : p.fft) {
@@ -744,41 +792,54 @@ int launch_fft(const Plan& p, const float* P, float* part, int nrhs, hipStream_t
     ymax = std::max(ymax, g.yzlen());
   }
   // right-hand sides go through the scratch in blocks (fft_block)
-  const int block = (int)fft_block(p, p.max_nrhs);
-  float2* bz = reinterpret_cast<float2*>(p.d_fft);
-  float2* by = bz + block * zmax;
-  for (size_t i = 0; i < p.fft.size(); ++i) {
+  const int block = (int)fft_block(p, p.max_nrhs), n_grid = (int)p.fft.size();
+  double2* bz = reinterpret_cast<double2*>(p.d_fft);
+  double2* by = bz + block * zmax;
+  float* norm = reinterpret_cast<float*>(by + block * ymax);
+  Reach* reach = reinterpret_cast<Reach*>(norm + p.n_box * p.max_nrhs);
+  const int2* maps = reinterpret_cast<const int2*>(p.d_fft_map);
+  const int4* cells = reinterpret_cast<const int4*>(p.d_fft_cells);
+  const Source all{P,
+                   p.d_box_scale,
+                   p.fp16() ? 2 : (p.split() ? 1 : 0),
+                   p.kh,
+                   p.khb,
+                   p.n_d,
+                   p.n_box * p.vstride(),
+                   p.n_box};
+  launch(norm_kernel, dim3((unsigned)((p.n_box + kThreads / 64 - 1) / (kThreads / 64)), nrhs),
+         dim3(kThreads), 0, s, start, nullptr, all, cells, p.nu, norm);
+  launch(reach_kernel, dim3(27, n_grid, nrhs), dim3(kReachThreads), 0, s, nullptr, nullptr, all,
+         maps, cells, cells + p.n_box, (const float*)norm, p.a / p.n_d, p.k, p.eta, p.nu, reach,
+         part, part_rhs);
+  for (int i = 0; i < n_grid; ++i) {
     const FftGrid& g = p.fft[i];
-    const int2* map = reinterpret_cast<const int2*>(p.d_fft_map) + g.map;
-    const float4* spec = reinterpret_cast<const float4*>(p.d_fft_spec) + g.spec / 2;
+    const int2* map = maps + g.map;
+    const double2* spec = reinterpret_cast<const double2*>(p.d_fft_spec) + g.spec;
     const int ny = g.s[0] * g.ax[2].L, nx = g.ax[1].L * g.ax[2].L;
     const int yw = fit_lines(g.ax[1], ny), xw = fit_lines(g.ax[0], nx);
-    const dim3 zblock = line_threads(g.ax[2], p.n_d), yblock = line_threads(g.ax[1], yw),
+    const int zg = z_groups(g.ax[2], p.n_d), zw = p.n_d / zg;
+    const dim3 zblock = line_threads(g.ax[2], zw), yblock = line_threads(g.ax[1], yw),
                xblock = line_threads(g.ax[0], xw);
-    const size_t zb = line_bytes(g.ax[2], p.n_d), yb = line_bytes(g.ax[1], yw),
+    const size_t zb = line_bytes(g.ax[2], zw), yb = line_bytes(g.ax[1], yw),
                  xb = line_bytes(g.ax[0], xw);
     for (int r0 = 0; r0 < nrhs; r0 += block) {
       const int nr = std::min(block, nrhs - r0);
-      const bool first = i == 0 && r0 == 0, last = i + 1 == p.fft.size() && r0 + nr == nrhs;
-      const dim3 zgrid(g.n[0] * p.n_d, g.n[1], nr), ygrid(blocks_of(ny, yw), nr),
+      const bool last = i + 1 == n_grid && r0 + nr == nrhs;
+      const dim3 zgrid(g.n[0] * p.n_d * zg, g.n[1], nr), ygrid(blocks_of(ny, yw), nr),
           xgrid(blocks_of(nx, xw), nr);
-      const Source src{P + (int64_t)r0 * p.n_box * p.vstride(),
-                       p.d_box_scale + (int64_t)r0 * p.n_box,
-                       p.fp16() ? 2 : (p.split() ? 1 : 0),
-                       p.kh,
-                       p.khb,
-                       p.n_d,
-                       p.n_box * p.vstride(),
-                       p.n_box};
-      launch(fft_z_kernel, zgrid, zblock, zb, s, first ? start : nullptr, nullptr, src, map, g, tw,
-             bz, zmax);
-      launch(fft_y_kernel<false>, ygrid, yblock, yb, s, nullptr, nullptr, (const float2*)bz, g, tw,
-             by, yw, zmax, ymax);
+      Source src = all;
+      src.P += (int64_t)r0 * p.n_box * p.vstride();
+      src.box_scale += (int64_t)r0 * p.n_box;
+      launch(fft_z_kernel, zgrid, zblock, zb, s, nullptr, nullptr, src, map, g, tw, bz, zmax, zg);
+      launch(fft_y_kernel<false>, ygrid, yblock, yb, s, nullptr, nullptr, (const double2*)bz, g,
+             tw, by, yw, zmax, ymax);
       launch(fft_x_kernel, xgrid, xblock, xb, s, nullptr, nullptr, by, g, tw, spec, xw, ymax);
-      launch(fft_y_kernel<true>, ygrid, yblock, yb, s, nullptr, nullptr, (const float2*)by, g, tw,
+      launch(fft_y_kernel<true>, ygrid, yblock, yb, s, nullptr, nullptr, (const double2*)by, g, tw,
              bz, yw, ymax, zmax);
       launch(ifft_z_kernel, zgrid, zblock, zb, s, nullptr, last ? stop : nullptr,
-             (const float2*)bz, map, g, tw, part + r0 * part_rhs, p.n_d, p.kh, zmax, part_rhs);
+             (const double2*)bz, map, g, tw, part + r0 * part_rhs, p.n_d, p.kh, zmax, part_rhs,
+             (const Reach*)(reach + (int64_t)r0 * n_grid + i), n_grid, zg);
     }
   }
   return (int)hipGetLastError();

@@ -83,14 +83,14 @@ int ubf_far_mvm_noalloc(ubf_plan* plan, const void* d_x, void* d_y, int32_t nrhs
   float* const keep_P = p.d_P;
   float* const keep_part = p.d_part;
   float* const keep_box_scale = p.d_box_scale;
-  float* const keep_fft = p.d_fft;
+  char* const keep_fft = p.d_fft;
   const int32_t keep_max_nrhs = p.max_nrhs;
   p.d_P = reinterpret_cast<float*>(b + L.P);
   p.d_part = reinterpret_cast<float*>(b + L.part);
   p.d_box_scale = reinterpret_cast<float*>(b + L.box_scale);
   p.max_nrhs = nrhs;
   if (p.rest) {
-    p.d_fft = reinterpret_cast<float*>(b + L.fft);
+    p.d_fft = b + L.fft;
     p.rest->d_box_scale = p.d_box_scale;
     p.rest->max_nrhs = nrhs;
   }

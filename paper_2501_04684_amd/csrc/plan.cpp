@@ -424,8 +424,13 @@ size_t row_bytes(const Plan& p, int32_t nrhs) {
 }  // namespace
 
 int64_t fft_block(const Plan& p, int32_t max_nrhs) {
-  const int64_t one = std::max<int64_t>(8 * p.fft_scratch_len(), 1);
+  const int64_t one = std::max<int64_t>(16 * p.fft_scratch_len(), 1);
   return std::max<int64_t>(1, std::min<int64_t>(max_nrhs, (64ll << 20) / one));
+}
+
+size_t fft_scratch_bytes(const Plan& p, int32_t nrhs) {
+  return (size_t)fft_block(p, nrhs) * p.fft_scratch_len() * 16 +
+         (size_t)nrhs * (p.n_box * sizeof(float) + p.fft.size() * kReachBytes);
 }
 
 Layout workspace_layout(const Plan& p, int32_t max_nrhs) {
@@ -456,10 +461,11 @@ Layout workspace_layout(const Plan& p, int32_t max_nrhs) {
   L.part = take(rows);
   L.box_scale = take((size_t)max_nrhs * p.n_box * sizeof(float));
   if (p.rest) {
-    L.fft = take((size_t)fft_block(p, max_nrhs) * p.fft_scratch_len() * 8);
-    L.fft_spec = take((size_t)p.fft_spec_len * 8);
-    L.fft_tw = take(p.fft_twiddles.size() * sizeof(float));
+    L.fft = take(fft_scratch_bytes(p, max_nrhs));
+    L.fft_spec = take((size_t)p.fft_spec_len * 16);
+    L.fft_tw = take(p.fft_twiddles.size() * sizeof(double));
     L.fft_map = take(p.fft_map.size() * sizeof(int32_t));
+    L.fft_cells = take(p.fft_cells.size() * sizeof(int32_t));
   }
   L.total = take.at;
   return L;
@@ -472,7 +478,7 @@ ScratchLayout scratch_layout(const Plan& p, int32_t nrhs) {
     L.P = take((size_t)nrhs * p.n_box * p.vstride() * sizeof(float));
     L.part = take(row_bytes(direct ? p : p.pairs_plan(), nrhs));
     L.box_scale = take((size_t)nrhs * p.n_box * sizeof(float));
-    L.fft = take(direct ? 0 : (size_t)fft_block(p, nrhs) * p.fft_scratch_len() * 8);
+    L.fft = take(direct ? 0 : fft_scratch_bytes(p, nrhs));
     return take.at;
   };
   L.direct = lay(true);
@@ -551,9 +557,9 @@ void build_table(Plan& P) {
 }
 
 // Smallest 5-smooth length >= n, split into radices of 2..8, the largest
-// first and the last at most 6 (the x kernel keeps the last stage's three
-// components in registers): as few as possible, and among those the split
-// whose smallest radix is largest (L / radix butterflies run side by side).
+// first: as few as possible, and among those the split whose smallest radix
+// is largest (L / radix butterflies run side by side: at most 256 up to
+// kMaxFftLength, so the 3 components of a line fit a workgroup).
 // False above kMaxFftLength.
 bool fft_axis(int64_t n, FftAxis& ax) {
   for (int64_t L = std::max<int64_t>(n, 1); L <= kMaxFftLength; ++L) {
@@ -568,7 +574,7 @@ bool fft_axis(int64_t n, FftAxis& ax) {
       for (const auto& f : level) {
         int64_t q = L;
         for (int r : f) q /= r;
-        if (q == 1 && (f.empty() || f.back() <= 6)) {
+        if (q == 1) {
           if (!best || (!f.empty() && f.back() > best->back())) best = &f;
         }
         for (int r : {8, 6, 5, 4, 3, 2})
@@ -590,29 +596,35 @@ bool fft_axis(int64_t n, FftAxis& ax) {
 }
 
 // Whether a scatterer's FULL product runs as a convolution: by estimates of
-// both ways' microseconds, fitted to both measured side by side on grids,
-// plates, shells, cubes and masks of 16 to 2,000 boxes, n_d 1..4.
-// Direct: 10 + 1.5 ns per chunk (of a tuned schedule) + the operators and the
-// partial rows, out and in, at 3.3 TB/s. Convolution: 30 (its launches) + 12
-// if pairs are left + the lattices, each transform in and out, and the
-// spectrum at 1.8 TB/s + the rows of the pairs left. Measured, direct and as
-// a convolution: n_d = 1, shells of 314 boxes 16 and 32 us, of 762 100 and
-// 35; n_d = 2, 762 boxes 148 and 56; n_d = 3, 5^3 boxes 45 and 55, 6^3 67 and
-// 57, 762 boxes (19,408 offsets) 525 and 108.
-bool convolution_pays(const Plan& P, const FftGrid& g, int64_t n_box, int64_t n_pairs,
-                      int64_t n_rest, int64_t n_off) {
+// both ways' microseconds for stages 2 and 3, fitted to both measured side by
+// side on 90 plans: cubes, plates, lines, shells, hollow cubes and masks of 64
+// to 2,000 boxes, n_d 1..4, FP32 and 16-bit forms (rms errors 15% and 7%).
+// Measured, pairs against convolution: 4^3 boxes, n_d = 3 FP32 31 and 44,
+// n_d = 4 59 and 75; 6^3, n_d = 3 16-bit 50 and 53, FP32 100 and 62; shells of
+// 314 boxes, n_d = 1 17 and 37, n_d = 3 16-bit 119 and 76, of 762, n_d = 1 45
+// and 38; a 40 x 23 plate, n_d = 1 39 and 38.
+bool convolution_pays(const Plan& P, const FftGrid& g, double n_box, double n_pairs,
+                      double n_rest, double n_off) {
   const double row = 4.0 * P.pstride();
-  // the scratch has to fit where the rows of the pairs would be (a caller
+  // the lattices have to fit where the rows of the pairs would be (a caller
   // without allocation has room for those)
-  if (8.0 * (g.zlen() + g.yzlen()) + row * (double)(n_rest + 2 * n_box) >
-      0.9 * row * (double)n_pairs)
+  if (16.0 * (g.zlen() + g.yzlen()) + row * (n_rest + 2.0 * n_box) > 0.9 * row * n_pairs)
     return false;
-  const double direct = 10.0 + 1.5e-3 * ((double)n_off + (double)n_pairs / kChunk) +
-                        ((double)n_off * image_bytes(P) + 2.0 * row * (double)n_pairs) / 3.3e6;
-  const double lattices = 8.0 * (4.0 * g.zlen() + 4.0 * g.yzlen() + g.spec_len());
-  const double conv =
-      30.0 + (n_rest ? 12.0 : 0.0) + lattices / 1.8e6 + 2.0 * row * (double)n_rest / 3.3e6;
-  return conv < 0.9 * direct;
+  // of the pair kernels: per chunk (N_u = 192: item) of pairs of one offset,
+  // and with few of them
+  const double fp32[] = {0.56e-3, 2.3e-3, 30e-3, 51e-3}, half[] = {1.1e-3, 2.3e-3, 8.2e-3, 27e-3};
+  const double unit = (P.split() ? half : fp32)[P.n_d - 1];
+  const double start = P.split() || P.n_d < 3 ? 0.0 : (P.n_d == 3 ? 10.0 : 25.0);
+  const double per_unit = P.nu == 192 ? 32 : kChunk;
+  const double direct = 8.5 + start + unit * (n_off + n_pairs / per_unit) +
+                        n_off * image_bytes(P) / 13e6 + 2.0 * row * n_pairs / 4.3e6;
+  // the lattices, each transform in and out, and the spectrum; the pairs left
+  const double lattices = 16.0 * (4.0 * g.zlen() + 4.0 * g.yzlen() + g.spec_len());
+  const double conv = 30.0 + lattices / 2.35e6 +
+                      (n_rest > 0 ? 10.6 + start + unit * n_rest / per_unit +
+                                        2.0 * row * n_rest / 4.3e6
+                                  : 0.0);
+  return conv < direct;
 }
 
 // Lattices of the scatterers whose FULL product runs as a convolution, and
@@ -663,18 +675,22 @@ void build_convolution(Plan& P) {
       g.n[d] = (int32_t)std::min<int64_t>(n, kMaxFftLength);
       g.s[d] = g.n[d] * P.n_d;
     }
-    // z lines run n_d to a workgroup, one butterfly per thread
-    fits = fits && g.ax[2].butterflies() * P.n_d <= kMaxFftThreads;
-    if (!fits || !convolution_pays(P, g, P.scat_ptr[s + 1] - P.scat_ptr[s], n_pairs[s],
-                                   n_rest[s], n_off[s])) continue;
+    if (!fits || !convolution_pays(P, g, (double)(P.scat_ptr[s + 1] - P.scat_ptr[s]),
+                                   (double)n_pairs[s], (double)n_rest[s], (double)n_off[s]))
+      continue;
     grid_of[s] = (int32_t)P.fft.size();
+    g.box = P.scat_ptr[s];
+    g.count = P.scat_ptr[s + 1] - g.box;
     g.map = (int64_t)P.fft_map.size() / 2;
+    P.fft_cells.resize(4 * (size_t)P.n_box, -1);
     P.fft_map.resize(P.fft_map.size() + 2 * (size_t)g.n[0] * g.n[1] * g.n[2], -1);
     for (int64_t i = P.scat_ptr[s]; i < P.scat_ptr[s + 1]; ++i) {
       const int32_t* c = &P.boxes[3 * i];
       const int64_t cell =
           g.map + ((c[0] - lo[0]) * g.n[1] + (c[1] - lo[1])) * g.n[2] + (c[2] - lo[2]);
       P.fft_map[2 * cell] = (int32_t)i;
+      for (int d = 0; d < 3; ++d) P.fft_cells[4 * i + d] = (int32_t)(c[d] - lo[d]);
+      P.fft_cells[4 * i + 3] = grid_of[s];
     }
     // a spectrum depends on the lattice alone: equal lattices share one
     g.spec = -1;
@@ -687,6 +703,10 @@ void build_convolution(Plan& P) {
     P.fft.push_back(g);
   }
   if (P.fft.empty()) return;
+  for (const FftGrid& g : P.fft)
+    P.fft_cells.insert(P.fft_cells.end(),
+                       {(int32_t)g.box, (int32_t)g.count, (int32_t)(g.map & 0xffffffff),
+                        (int32_t)(g.map >> 32), g.n[0], g.n[1], g.n[2], 0});
   for (FftGrid& g : P.fft)
     for (FftAxis& ax : g.ax) {
       ax.tw = (int32_t)P.fft_twiddles.size() / 2;
@@ -695,8 +715,8 @@ void build_convolution(Plan& P) {
           if (&b < &ax && b.L == ax.L) ax.tw = b.tw;
       if (ax.tw < (int32_t)P.fft_twiddles.size() / 2) continue;
       for (int32_t k = 0; k < ax.L; ++k) {
-        P.fft_twiddles.push_back((float)std::cos(2.0 * kPi * k / ax.L));
-        P.fft_twiddles.push_back((float)-std::sin(2.0 * kPi * k / ax.L));
+        P.fft_twiddles.push_back(std::cos(2.0 * kPi * k / ax.L));
+        P.fft_twiddles.push_back(-std::sin(2.0 * kPi * k / ax.L));
       }
     }
 

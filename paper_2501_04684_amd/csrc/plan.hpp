@@ -114,7 +114,7 @@ void operator_fp64(const int32_t w[3], double a, double k, double eta, int n_d,
 // lattice of step a / n_d, and D depends on the site difference d alone, so
 // the part of the FULL product with max |d_i| >= 2 n_d sites (which only
 // pairs of boxes two or more apart have) is a discrete convolution over the
-// lattice, done with FFTs of the zero-padded lattice. What is left are the
+// lattice, done with FP64 FFTs of the zero-padded lattice. What is left are the
 // pairs of boxes exactly two apart, with the site pairs max |d_i| < 2 n_d:
 // a far set of at most 98 offsets with masked operators, which the
 // translation kernels take (Plan::rest). Everything summed is far field:
@@ -122,6 +122,7 @@ void operator_fp64(const int32_t w[3], double a, double k, double eta, int n_d,
 constexpr int kMaxFftLength = 768;
 constexpr int kMaxFftStages = 6;
 constexpr int kMaxFftThreads = 1024;  // threads of a transform's workgroup
+constexpr size_t kReachBytes = 24;    // the convolution's record of a lattice's strong boxes
 // Transform along one axis: length (5-smooth), its radices, and where its
 // twiddle factors exp(-2 pi i k / L) start in Plan::fft_twiddles.
 struct FftAxis {
@@ -136,6 +137,7 @@ struct FftGrid {
   int32_t n[3];   // boxes per axis of the bounding grid
   int32_t s[3];   // sites per axis, n * n_d
   FftAxis ax[3];  // L >= 2 s - 1
+  int64_t box, count;  // its boxes
   int64_t map;    // first cell in Plan::fft_map ((x n_y + y) n_z + z)
   int64_t spec;   // first value of its spectrum (complex values)
   int64_t spec_len() const {
@@ -264,7 +266,10 @@ struct Plan {
   // pair_src / pair_dst are padded to the number of rows.
   std::vector<FftGrid> fft;
   std::vector<int32_t> fft_map;
-  std::vector<float> fft_twiddles;
+  // 4 per box: its cell (x, y, z) and lattice (-1: none); then 8 per lattice:
+  // first box, boxes, first cell (64 bits), boxes per axis, 0
+  std::vector<int32_t> fft_cells;
+  std::vector<double> fft_twiddles;
   int64_t fft_spec_len = 0;     // complex values of all spectra
   std::unique_ptr<Plan> rest;
   std::vector<uint8_t> op_masked;  // per offset; empty: none
@@ -300,10 +305,11 @@ struct Plan {
   float* d_part = nullptr;
   float* d_off_scale = nullptr;  // [n_off] (FP16 forms)
   int32_t* d_offsets = nullptr;  // [n_off][4] offset, masked (generated operators)
-  float* d_fft = nullptr;          // scratch of the convolution
-  float* d_fft_spec = nullptr;
-  float* d_fft_tw = nullptr;
+  char* d_fft = nullptr;           // scratch of the convolution (fft_scratch_bytes)
+  double* d_fft_spec = nullptr;
+  double* d_fft_tw = nullptr;
   int32_t* d_fft_map = nullptr;
+  int32_t* d_fft_cells = nullptr;
   float* d_box_scale = nullptr;  // [max_nrhs][n_box] box-vector scales (FP16 forms)
 
   // Networks standing in for the operators (Sec. 3): hidden width (0 = none,
@@ -330,7 +336,7 @@ struct Layout {
         off_scale, offsets;
   };
   Pairs own, rest;
-  size_t nb_ptr, P, part, box_scale, fft, fft_spec, fft_tw, fft_map, total;
+  size_t nb_ptr, P, part, box_scale, fft, fft_spec, fft_tw, fft_map, fft_cells, total;
 };
 Layout workspace_layout(const Plan& p, int32_t max_nrhs);
 // Whether a bound plan holds its own far set's arrays and rows: without a
@@ -341,6 +347,10 @@ inline bool holds_own_pairs(const Plan& p) { return !p.rest || p.precision == 0;
 // many as 64 MB hold (small lattices are bound by their launches, large ones
 // by memory, where one at a time keeps more in the caches).
 int64_t fft_block(const Plan& p, int32_t max_nrhs);
+// Scratch of the convolution for nrhs right-hand sides: the lattices of a
+// block of them, then per right-hand side a float for each box and a
+// kReachBytes record for each lattice.
+size_t fft_scratch_bytes(const Plan& p, int32_t nrhs);
 
 // The per-call intermediates of one product of nrhs right-hand sides (box
 // vectors, partial rows with their spare row, FP16 box scales), laid out

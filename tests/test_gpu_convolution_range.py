@@ -1,0 +1,106 @@
+"""FULL products whose box vectors differ by many orders of magnitude (needs a
+GPU): every box keeps the error that its own far pairs give it, whatever the
+boxes it does not see hold.
+
+The bar per box: a pair's product sums 162 FP32 terms and a box some 900
+rows, so rounding walks of 2^-24 (sqrt(162) + sqrt(900)) ~ 2.6e-6 at most,
+and the split FP16 inputs carry 2^-22; the split BF16 inputs 2^-16 per term.
+"""
+import numpy as np
+import pytest
+
+import oracle as O
+import workloads as W
+from gpu_util import announce, parity, to_dev, to_host
+
+pytestmark = pytest.mark.gpu
+TWO_PI = 2 * np.pi
+TOL = {"fp32": 3e-6, "split-fp16": 3e-6, "split-bf16": 1e-4}
+
+torch = pytest.importorskip("torch")
+U = pytest.importorskip("paper_2501_04684_amd")
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _need_gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    U.lib()
+
+
+def _vectors(boxes, n_u, strong, seed):
+    """One right-hand side per entry of ``strong``: (cells, factor of these
+    boxes, factor of the others)."""
+    at = {tuple(c): i for i, c in enumerate(boxes)}
+    P = W.complex_normal((len(strong), len(boxes), n_u), seed)
+    for r, (cells, factor, rest) in enumerate(strong):
+        picked = [at[c] for c in cells]
+        keep = P[r, picked].copy()
+        P[r] *= np.float32(rest)
+        P[r, picked] = keep * np.float32(factor)
+    return P
+
+
+@pytest.mark.parametrize("n_d, precision, operators", [
+    (1, "split-fp16", "table"), (2, "fp32", "table"), (3, "fp32", "table"),
+    (3, "split-fp16", "generated"), (3, "split-bf16", "table"), (4, "split-fp16", "table")])
+def test_boxes_keep_their_own_error(n_d, precision, operators):
+    boxes = W.grid_boxes(13, 9, 8)
+    announce("range", n_d, precision, operators)
+    n_u, c = 3 * n_d ** 3, (6, 4, 4)
+    strong = [
+        ([c], 1e4, 1), ([c], 1e6, 1),
+        ([c], 1e9, 1),                               # its neighbours see weak boxes only
+        ([c, (7, 4, 4), (7, 5, 5)], 1e9, 1),         # fewer boxes do
+        ([(5, 3, 3), c, (7, 5, 5)], 1e9, 1),         # the middle one alone does
+        ([c, (6, 4, 7)], 1e9, 1),                    # none does
+        ([(0, 0, 0)], 1e9, 1),                       # at a corner
+        ([c], 1, 0), ([], 1, 0),                     # nothing else, nothing at all
+        ([c], 1e-30, 0), ([c], 1e30, 1e30)]
+    P = _vectors(boxes, n_u, strong, 11 + n_d)
+    ff = U.FarField(boxes, 0.25, TWO_PI, n_d, "full", max_nrhs=len(P), precision=precision,
+                    operators=operators)
+    E = torch.full(P.shape, float("nan"), dtype=torch.complex64, device="cuda")
+    U.translate(ff.plan, to_dev(P), E, len(P))
+    E = to_host(E)
+    d = np.abs(boxes - np.array(c)).max(axis=1)
+    d0 = boxes.max(axis=1)
+    sample = np.nonzero((d <= 1) | (d0 <= 1))[0]
+    sample = np.union1d(sample, np.random.default_rng(3).choice(len(boxes), 8, replace=False))
+    ref = O.translate(P.astype(np.complex128), boxes, 0.25, TWO_PI, n_d, mode="full",
+                      test_boxes=sample)
+    parity(E[:, sample], ref[:, sample], TOL[precision], boxes=n_u,
+           label=f"range n_d={n_d} {precision}")
+    ff.close()
+
+
+def test_ranges_of_neighbouring_scatterers_are_their_own():
+    """A strong scatterer beside a weak one, and a zero one, in one plan: each
+    gives what it gives alone."""
+    parts = [W.grid_boxes(9, 8, 7), W.hollow_cube_boxes(9), W.grid_boxes(9, 8, 7)]
+    n_u = 81
+    ff = U.FarField(None, 0.25, TWO_PI, 3, "full", max_nrhs=2, precision="split-fp16",
+                    scatterers=parts)
+    starts = np.cumsum([0] + [len(p) for p in parts])
+    P = W.complex_normal((2, int(starts[-1]), n_u), 5)
+    P[0, :starts[1]] *= np.float32(1e12)
+    P[0, starts[2]:] = 0
+    P[1, starts[1] + 3] *= np.float32(1e10)
+    announce("range, batch", starts)
+    E = torch.full(P.shape, float("nan"), dtype=torch.complex64, device="cuda")
+    U.translate(ff.plan, to_dev(P), E, 2)
+    E = to_host(E)
+    assert not np.any(E[0, starts[2]:])
+    for i, p in enumerate(parts):
+        solo = U.FarField(p, 0.25, TWO_PI, 3, "full", max_nrhs=2, precision="split-fp16")
+        Q = np.ascontiguousarray(P[:, starts[i]:starts[i + 1]])
+        alone = torch.full(Q.shape, float("nan"), dtype=torch.complex64, device="cuda")
+        U.translate(solo.plan, to_dev(Q), alone, 2)
+        sample = np.arange(0, len(p), 37)
+        ref = O.translate(Q.astype(np.complex128), p, 0.25, TWO_PI, 3, mode="full",
+                          test_boxes=sample)
+        parity(E[:, starts[i]:starts[i + 1]][:, sample], ref[:, sample], 3e-6, boxes=n_u,
+               label=f"scatterer {i} of three")
+        assert np.array_equal(to_host(alone), E[:, starts[i]:starts[i + 1]])
+        solo.close()
+    ff.close()
