@@ -28,8 +28,9 @@
  * over the lattice of its sites (FP64 FFTs) plus the pairs exactly two boxes
  * apart, except in the single FP16 form. A box's error stays relative to what
  * reaches it from its far boxes, as pair by pair, and a box whose far boxes
- * are all zero gets exactly zero. A non-finite coefficient makes the whole
- * scatterer's result non-finite. Which way is taken depends on the
+ * are all zero gets exactly zero. A non-finite coefficient makes the results
+ * of the boxes far from its own non-finite, and those alone, as pair by pair
+ * (NaN, where a pair may give an infinity). Which way is taken depends on the
  * scatterer's boxes, n_d and precision alone.
  *
  * Operators: G_w[(l,alpha),(s,beta)] = D(a*w + r_l - r_s)[alpha][beta],

@@ -30,6 +30,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cfloat>
 
 #include "fft.hpp"
 
@@ -318,8 +319,8 @@ __device__ void green(int dx, int dy, int dz, double step, double k, double eta,
   }
 }
 
-// Largest real or imaginary part of every box vector of a lattice; a
-// wavefront per box.
+// Largest real or imaginary part of every box vector of a lattice, infinity
+// where one is not finite; a wavefront per box.
 __global__ __launch_bounds__(kThreads) void norm_kernel(Source src, const int4* __restrict__ cells,
                                                         int nu, float* __restrict__ norm) {
   src.select(blockIdx.y);
@@ -327,25 +328,52 @@ __global__ __launch_bounds__(kThreads) void norm_kernel(Source src, const int4* 
   if (box >= src.n_box || cells[box].w < 0) return;
   const int lane = threadIdx.x & 63;
   double m = 0.0;
+  bool finite = true;
   for (int u = lane; u < nu; u += 64) {
     const double2 v = src.at((int)box, u);
+    finite = finite && isfinite(v.x) && isfinite(v.y);
     m = fmax(m, fmax(fabs(v.x), fabs(v.y)));
   }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) m = fmax(m, __shfl_xor(m, o, 64));
-  if (lane == 0) norm[blockIdx.y * src.n_box + box] = (float)fmin(m, 3.4028234663852886e38);
+  finite = __all(finite);
+  if (lane == 0)
+    norm[blockIdx.y * src.n_box + box] =
+        finite ? (float)fmin(m, (double)FLT_MAX) : __builtin_inff();
 }
 
-// Bounding grid of the strong boxes of one lattice and right-hand side.
-struct Reach {
+// Bounding grid of some boxes.
+struct Bounds {
   int lo[3], hi[3];
+  __device__ inline void clear() {
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      lo[d] = 0x7fffffff;
+      hi[d] = -1;
+    }
+  }
+  __device__ inline void add(int x, int y, int z) {
+    lo[0] = min(lo[0], x);
+    lo[1] = min(lo[1], y);
+    lo[2] = min(lo[2], z);
+    hi[0] = max(hi[0], x);
+    hi[1] = max(hi[1], y);
+    hi[2] = max(hi[2], z);
+  }
   __device__ inline bool empty() const { return lo[0] > hi[0]; }
-  // No strong box is far from (x, y, z): all are within one of it on every
-  // axis (true without strong boxes).
+  // None of them is far from (x, y, z): all are within one of it on every
+  // axis (true where there are none).
   __device__ inline bool near(int x, int y, int z) const {
     return lo[0] >= x - 1 && hi[0] <= x + 1 && lo[1] >= y - 1 && hi[1] <= y + 1 &&
            lo[2] >= z - 1 && hi[2] <= z + 1;
   }
+};
+
+// The strong boxes of one lattice and right-hand side, and those whose
+// coefficients are not all finite. The latter are left out of the transforms,
+// and the boxes that one of them is far from get NaN, as from its pairs.
+struct Reach {
+  Bounds strong, bad;
 };
 
 static_assert(sizeof(Reach) == kReachBytes && alignof(Reach) <= 4, "fft_scratch_bytes");
@@ -364,7 +392,7 @@ __global__ __launch_bounds__(kReachThreads) void reach_kernel(
     const int4* __restrict__ grids, const float* __restrict__ norm, double step, double k,
     double eta, int nu, Reach* __restrict__ reach, float* __restrict__ part, int64_t part_rhs) {
   __shared__ float wave_max[kReachThreads / 64];
-  __shared__ Reach strong;
+  __shared__ Reach all;
   __shared__ double2 sums[kReachThreads][3];
   const int rhs = blockIdx.z, t = threadIdx.x;
   src.select(rhs);
@@ -375,50 +403,58 @@ __global__ __launch_bounds__(kReachThreads) void reach_kernel(
   const int64_t cell0 = ((int64_t)ga.w << 32) | (unsigned)ga.z;
   float m = 0.f;
 #pragma unroll 8
-  for (int i = t; i < count; i += kReachThreads) m = fmaxf(m, norm[first + i]);
+  for (int i = t; i < count; i += kReachThreads) {
+    const float v = norm[first + i];
+    if (v <= FLT_MAX) m = fmaxf(m, v);
+  }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
   if ((t & 63) == 0) wave_max[t >> 6] = m;
-  if (t < 3) {
-    strong.lo[t] = 0x7fffffff;
-    strong.hi[t] = -1;
+  if (t == 0) {
+    all.strong.clear();
+    all.bad.clear();
   }
   __syncthreads();
 #pragma unroll
   for (int w = 0; w < kReachThreads / 64; ++w) m = fmaxf(m, wave_max[w]);
   const float bar = m * 0x1p-24f;
-  int lo[3] = {0x7fffffff, 0x7fffffff, 0x7fffffff}, hi[3] = {-1, -1, -1};
+  Reach mine;
+  mine.strong.clear();
+  mine.bad.clear();
 #pragma unroll 4
   for (int i = t; i < count; i += kReachThreads) {
     const float v = norm[first + i];
     const int4 c = cells[first + i];
-    if (v > 0.f && v >= bar) {
-      lo[0] = min(lo[0], c.x);
-      lo[1] = min(lo[1], c.y);
-      lo[2] = min(lo[2], c.z);
-      hi[0] = max(hi[0], c.x);
-      hi[1] = max(hi[1], c.y);
-      hi[2] = max(hi[2], c.z);
-    }
+    if (!(v <= FLT_MAX))
+      mine.bad.add(c.x, c.y, c.z);
+    else if (v > 0.f && v >= bar)
+      mine.strong.add(c.x, c.y, c.z);
   }
+  auto join = [t](Bounds& to, Bounds& b) {
 #pragma unroll
-  for (int d = 0; d < 3; ++d) {
+    for (int d = 0; d < 3; ++d) {
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-      lo[d] = min(lo[d], __shfl_xor(lo[d], o, 64));
-      hi[d] = max(hi[d], __shfl_xor(hi[d], o, 64));
+      for (int o = 32; o > 0; o >>= 1) {
+        b.lo[d] = min(b.lo[d], __shfl_xor(b.lo[d], o, 64));
+        b.hi[d] = max(b.hi[d], __shfl_xor(b.hi[d], o, 64));
+      }
+      if ((t & 63) == 0) {
+        atomicMin(&to.lo[d], b.lo[d]);
+        atomicMax(&to.hi[d], b.hi[d]);
+      }
     }
-    if ((t & 63) == 0) {
-      atomicMin(&strong.lo[d], lo[d]);
-      atomicMax(&strong.hi[d], hi[d]);
-    }
-  }
+  };
+  join(all.strong, mine.strong);
+  if (__any(!mine.bad.empty())) join(all.bad, mine.bad);
   __syncthreads();
-  if (blockIdx.x == 0 && t == 0) reach[rhs * gridDim.y + blockIdx.y] = strong;
+  if (blockIdx.x == 0 && t == 0) reach[rhs * gridDim.y + blockIdx.y] = all;
+  const Bounds strong = all.strong;
   if (strong.empty()) return;
   const int x = strong.hi[0] - 1 + (int)blockIdx.x / 9, y = strong.hi[1] - 1 + (int)blockIdx.x / 3 % 3,
             z = strong.hi[2] - 1 + (int)blockIdx.x % 3;
-  if (x < 0 || y < 0 || z < 0 || x >= nx || y >= ny || z >= nz || !strong.near(x, y, z)) return;
+  if (x < 0 || y < 0 || z < 0 || x >= nx || y >= ny || z >= nz || !strong.near(x, y, z) ||
+      !all.bad.near(x, y, z))
+    return;
   const int at = map[cell0 + ((int64_t)x * ny + y) * nz + z].y;
   if (at < 0) return;
   // site l of the test box, source sites chunk, chunk + chunks, ...
@@ -431,7 +467,7 @@ __global__ __launch_bounds__(kReachThreads) void reach_kernel(
   if (chunk < chunks)
     for (int q = chunk; q < count * nd3; q += chunks) {
       const int i = q / nd3, s = q - i * nd3;
-      if (!(norm[first + i] > 0.f)) continue;
+      if (!(norm[first + i] > 0.f && norm[first + i] <= FLT_MAX)) continue;
       const int4 c = cells[first + i];
       const int dx = lx - (c.x * nd + s / nd2), dy = ly - (c.y * nd + s / nd % nd),
                 dz = lz - (c.z * nd + s % nd);
@@ -469,8 +505,9 @@ __global__ __launch_bounds__(kReachThreads) void reach_kernel(
 // mx of it, which has n_d lines (site rows my).
 __global__ __launch_bounds__(kMaxFftThreads) void fft_z_kernel(
     Source src, const int2* __restrict__ map, FftGrid g, const double2* __restrict__ twiddles,
-    double2* __restrict__ out, int64_t out_rhs, int groups) {
+    double2* __restrict__ out, int64_t out_rhs, int groups, const float* __restrict__ norm) {
   src.select(blockIdx.z);
+  norm += blockIdx.z * src.n_box;
   out += blockIdx.z * out_rhs;
   const int nd = src.nd, w = nd / groups, L = g.ax[2].L, row = 3 * nd * nd;
   double2 *a = lds, *tw = a + 3 * L * w;
@@ -488,7 +525,7 @@ __global__ __launch_bounds__(kMaxFftThreads) void fft_z_kernel(
     const int box = col[bz].x;
     double2 z = make_double2(0.0, 0.0);
     if (box >= 0) {
-      z = src.at(box, mx * row + my0 * 3 * nd + v);
+      if (norm[box] <= FLT_MAX) z = src.at(box, mx * row + my0 * 3 * nd + v);
       any = true;
     }
     a[((bz * nd + mz) * w + line) * 3 + al] = z;
@@ -591,14 +628,15 @@ __global__ __launch_bounds__(kMaxFftThreads) void fft_x_kernel(
 
 // Backward z transforms into the boxes' rows: the lines of fft_z_kernel. The
 // rows of boxes that no strong box is far from are reach_kernel's, or zero
-// where no box is strong.
+// where no box is strong; those that a box without finite coefficients is far
+// from are NaN.
 __global__ __launch_bounds__(kMaxFftThreads) void ifft_z_kernel(
     const double2* __restrict__ in, const int2* __restrict__ map, FftGrid g,
     const double2* __restrict__ twiddles, float* __restrict__ part, int nd, int kh,
     int64_t in_rhs, int64_t part_rhs, const Reach* __restrict__ reach, int n_grid, int groups) {
   in += blockIdx.z * in_rhs;
   part += blockIdx.z * part_rhs;
-  const Reach strong = reach[blockIdx.z * n_grid];
+  const Reach of = reach[blockIdx.z * n_grid];
   const int L = g.ax[2].L, w = nd / groups, row = 3 * nd * nd, nu = row * nd, s = g.s[2];
   double2 *a = lds, *tw = a + 3 * L * w;
   const int by = blockIdx.y, X = blockIdx.x / groups, my0 = (blockIdx.x - X * groups) * w;
@@ -626,8 +664,10 @@ __global__ __launch_bounds__(kMaxFftThreads) void ifft_z_kernel(
     const int at = col[bz].y;
     if (at < 0) continue;
     double2 z = a[((bz * nd + mz) * w + ln) * 3 + al];
-    if (strong.near(bx, by, bz)) {
-      if (!strong.empty()) continue;
+    if (!of.bad.near(bx, by, bz)) {
+      z.x = z.y = __builtin_nan("");
+    } else if (of.strong.near(bx, by, bz)) {
+      if (!of.strong.empty()) continue;
       z = make_double2(0.0, 0.0);
     }
     float* e = part + (int64_t)at * 2 * kh + mx * row + my0 * 3 * nd + v;  // [Er | Ei]
@@ -831,7 +871,8 @@ int launch_fft(const Plan& p, const float* P, float* part, int nrhs, hipStream_t
       Source src = all;
       src.P += (int64_t)r0 * p.n_box * p.vstride();
       src.box_scale += (int64_t)r0 * p.n_box;
-      launch(fft_z_kernel, zgrid, zblock, zb, s, nullptr, nullptr, src, map, g, tw, bz, zmax, zg);
+      launch(fft_z_kernel, zgrid, zblock, zb, s, nullptr, nullptr, src, map, g, tw, bz, zmax, zg,
+             (const float*)(norm + (int64_t)r0 * p.n_box));
       launch(fft_y_kernel<false>, ygrid, yblock, yb, s, nullptr, nullptr, (const double2*)bz, g,
              tw, by, yw, zmax, ymax);
       launch(fft_x_kernel, xgrid, xblock, xb, s, nullptr, nullptr, by, g, tw, spec, xw, ymax);

@@ -122,7 +122,7 @@ void operator_fp64(const int32_t w[3], double a, double k, double eta, int n_d,
 constexpr int kMaxFftLength = 768;
 constexpr int kMaxFftStages = 6;
 constexpr int kMaxFftThreads = 1024;  // threads of a transform's workgroup
-constexpr size_t kReachBytes = 24;    // the convolution's record of a lattice's strong boxes
+constexpr size_t kReachBytes = 48;    // the convolution's record of a lattice's boxes (Reach)
 // Transform along one axis: length (5-smooth), its radices, and where its
 // twiddle factors exp(-2 pi i k / L) start in Plan::fft_twiddles.
 struct FftAxis {

@@ -104,3 +104,47 @@ def test_ranges_of_neighbouring_scatterers_are_their_own():
         assert np.array_equal(to_host(alone), E[:, starts[i]:starts[i + 1]])
         solo.close()
     ff.close()
+
+
+@pytest.mark.parametrize("n_d, precision, operators", [
+    (1, "split-fp16", "table"), (2, "fp32", "table"), (3, "split-fp16", "generated"),
+    (3, "split-bf16", "table"), (4, "fp32", "table")])
+def test_non_finite_coefficients_stay_with_their_pairs(n_d, precision, operators):
+    """A NaN or an infinity reaches the boxes far from its own and no others,
+    in its right-hand side and scatterer alone."""
+    parts = [W.grid_boxes(13, 9, 8), W.grid_boxes(13, 9, 8)[:-1]]
+    n_u, n = 3 * n_d ** 3, len(parts[0])
+    at = {tuple(c): i for i, c in enumerate(parts[0])}
+    bad = [[], [((6, 4, 4), np.nan)], [((0, 0, 0), np.inf)],
+           [((6, 4, 4), -np.inf), ((7, 5, 4), np.nan)],         # their common neighbours stay
+           [((6, 4, 4), np.inf), ((6, 4, 7), np.inf)],          # no box has both near
+           [(c, np.nan) for c in at]]
+    P = W.complex_normal((len(bad), n + len(parts[1]), n_u), 17 + n_d)
+    P[1, :n] *= np.float32(1e-9)
+    P[1, at[(6, 4, 4)]] = 1                      # the strongest box is the bad one
+    clean = P.astype(np.complex128)
+    for r, boxes in enumerate(bad):
+        for i, (c, v) in enumerate(boxes):
+            P[r, at[c], i % n_u] = complex(v, 1.0) if i % 2 else complex(1.0, v)
+            clean[r, at[c]] = 0
+    announce("non-finite", n_d, precision, operators)
+    ff = U.FarField(None, 0.25, TWO_PI, n_d, "full", max_nrhs=len(P), precision=precision,
+                    operators=operators, scatterers=parts)
+    E = torch.zeros(P.shape, dtype=torch.complex64, device="cuda")
+    U.translate(ff.plan, to_dev(P), E, len(P))
+    E = to_host(E)
+    assert np.isfinite(E[:, n:]).all() and np.isfinite(E[0]).all()
+    for r, boxes in enumerate(bad):
+        hit = np.zeros(n, dtype=bool)
+        for c, _ in boxes:
+            hit |= np.abs(parts[0] - np.array(c)).max(axis=1) >= 2
+        finite = np.isfinite(E[r, :n].real) & np.isfinite(E[r, :n].imag)
+        assert not finite[hit].any(), r
+        assert finite[~hit].all(), r
+        keep = np.nonzero(~hit)[0][:40]
+        if len(keep):
+            ref = O.translate(clean[r:r + 1, :n], parts[0], 0.25, TWO_PI, n_d, mode="full",
+                              test_boxes=keep)
+            parity(E[r:r + 1, keep], ref[:, keep], TOL[precision], boxes=n_u,
+                   label=f"beside non-finite boxes {r}, n_d={n_d} {precision}")
+    ff.close()
