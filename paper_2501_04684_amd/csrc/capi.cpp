@@ -337,6 +337,7 @@ int ubf_plan_bind(ubf_plan* plan, void* d_workspace, size_t bytes,
     copies.push_back({L.fft_tw, p.fft_twiddles.data(), p.fft_twiddles.size() * sizeof(double)});
     copies.push_back({L.fft_map, p.fft_map.data(), p.fft_map.size() * sizeof(int32_t)});
     copies.push_back({L.fft_cells, p.fft_cells.data(), p.fft_cells.size() * sizeof(int32_t)});
+    copies.push_back({L.fft_tasks, p.fft_tasks.data(), p.fft_tasks.size() * sizeof(ubf::FftTask)});
   }
   copies.push_back({L.nb_ptr, nb.data(), nb.size() * sizeof(int64_t)});
   hipError_t e = hipSuccess;
@@ -379,6 +380,7 @@ int ubf_plan_bind(ubf_plan* plan, void* d_workspace, size_t bytes,
   p.d_fft_tw = (double*)(ws + L.fft_tw);
   p.d_fft_map = (int32_t*)(ws + L.fft_map);
   p.d_fft_cells = (int32_t*)(ws + L.fft_cells);
+  p.d_fft_tasks = (ubf::FftTask*)(ws + L.fft_tasks);
   int le = ubf::launch_fft_spectra(p, s);
   if (!le) le = (int)hipStreamSynchronize(s);
   if (le) return hip_fail(le, "spectra (bind)");

@@ -1,7 +1,7 @@
-// FULL far sets as a discrete convolution over the lattice of the sites
+// FULL far sets as a discrete convolution over the lattices of the sites
 // (FftGrid in plan.hpp), in FP64. Two kernels per product look at the box
-// vectors, then per scatterer and right-hand side five kernels each transform
-// lines of the zero-padded lattice in LDS:
+// vectors, then five kernels each transform lines of the zero-padded lattices
+// in LDS, for a group of scatterers and right-hand sides at a time (FftGroup):
 //   fft_z:    box vectors -> [x][y][kz][component]          (x, y < sites)
 //   fft_y:    -> [x][ky][kz][component]                     (x < sites)
 //   fft_x:    transform along x, product with the spectrum of D (a symmetric
@@ -25,6 +25,9 @@
 // arrays of 114 and 235 MB, four passes each, and a spectrum of 124 MB): 42 +
 // 59 + 211 + 63 + 45 us, 14 us to look at the box vectors, and the whole
 // product 530 us against 6,290 pair by pair; 398 with FP32 transforms.
+// Small lattices are bound by the launches, which a group shares: 8 shells of
+// 762 boxes at n_d = 1 take 54 us (234 with five launches for each, 174 pair
+// by pair), 16 masks of 200 at n_d = 3 in FP32 264 (613, 575).
 #include <hip/hip_ext.h>
 #include <hip/hip_fp16.h>
 #include <hip/hip_runtime.h>
@@ -38,9 +41,6 @@ namespace ubf {
 namespace {
 
 constexpr int kThreads = 256;       // spectrum kernels
-// LDS of one workgroup's lines: three workgroups share a compute unit (160 KB).
-constexpr size_t kLineBytes = 50 << 10;
-
 __device__ inline double2 cmul(double2 a, double2 b) {
   return make_double2(fma(a.x, b.x, -a.y * b.y), fma(a.x, b.y, a.y * b.x));
 }
@@ -296,6 +296,18 @@ __device__ inline int xcd_block() {
   return (int)(blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
 }
 
+// The task whose part of launch `kind` holds workgroup `block`, of n.
+__device__ inline const FftTask& task_of(const FftTask* __restrict__ tasks, int n, int kind,
+                                         int block) {
+  int lo = 0;
+  while (n > 1) {  // uniform
+    const int half = n / 2;
+    if (tasks[lo + half].first[kind] <= block) lo += half;
+    n -= half;
+  }
+  return tasks[lo];
+}
+
 // ---------------------------------------------------- what reaches a box
 
 // D(R), R = step (dx, dy, dz), in FP64: xx, yy, zz, xy, xz, yz.
@@ -501,19 +513,35 @@ __global__ __launch_bounds__(kReachThreads) void reach_kernel(
   }
 }
 
-// z transforms: `groups` workgroups per column of boxes (x, y) and site plane
-// mx of it, which has n_d lines (site rows my).
+// A workgroup of the z transforms: w of the n_d lines (site rows my) of a
+// column of boxes (x, y) and a site plane mx of it.
+struct ZBlock {
+  int w, bx, by, mx, my0, X;  // X: sites along x
+  __device__ ZBlock(const FftTask& t, int nd) : w(t.lines[0]) {
+    const int groups = nd / w, row = t.g.n[0] * nd * groups;
+    const int b = (int)blockIdx.x - t.first[0];
+    by = b / row;
+    X = (b - by * row) / groups;
+    my0 = (b - by * row - X * groups) * w;
+    bx = X / nd;
+    mx = X - bx * nd;
+  }
+};
+
 __global__ __launch_bounds__(kMaxFftThreads) void fft_z_kernel(
-    Source src, const int2* __restrict__ map, FftGrid g, const double2* __restrict__ twiddles,
-    double2* __restrict__ out, int64_t out_rhs, int groups, const float* __restrict__ norm) {
-  src.select(blockIdx.z);
-  norm += blockIdx.z * src.n_box;
-  out += blockIdx.z * out_rhs;
-  const int nd = src.nd, w = nd / groups, L = g.ax[2].L, row = 3 * nd * nd;
+    Source src, const int2* __restrict__ maps, const FftTask* __restrict__ tasks, int n_tasks,
+    const double2* __restrict__ twiddles, double2* __restrict__ scratch, int64_t scratch_rhs,
+    const float* __restrict__ norm) {
+  src.select(blockIdx.y);
+  norm += blockIdx.y * src.n_box;
+  const FftTask& task = task_of(tasks, n_tasks, 0, blockIdx.x);
+  const FftGrid& g = task.g;
+  const ZBlock blk(task, src.nd);
+  double2* out = scratch + blockIdx.y * scratch_rhs + task.z;
+  const int nd = src.nd, w = blk.w, L = g.ax[2].L, row = 3 * nd * nd;
   double2 *a = lds, *tw = a + 3 * L * w;
-  const int by = blockIdx.y, X = blockIdx.x / groups, my0 = (blockIdx.x - X * groups) * w;
-  const int bx = X / nd, mx = X - bx * nd;
-  const int2* col = map + ((int64_t)bx * g.n[1] + by) * g.n[2];
+  const int by = blk.by, X = blk.X, my0 = blk.my0, bx = blk.bx, mx = blk.mx;
+  const int2* col = maps + g.map + ((int64_t)bx * g.n[1] + by) * g.n[2];
   load_twiddles(tw, twiddles, g.ax[2]);
   const int part = 3 * nd * w;  // a box's values here
   const float inv_part = 1.f / part, inv_line = 1.f / (3 * nd);
@@ -549,20 +577,24 @@ __global__ __launch_bounds__(kMaxFftThreads) void fft_z_kernel(
 // s to L positions, backward from L to s.
 template <bool INV>
 __global__ __launch_bounds__(kMaxFftThreads) void fft_y_kernel(
-    const double2* __restrict__ in, FftGrid g, const double2* __restrict__ twiddles,
-    double2* __restrict__ out, int w, int64_t in_rhs, int64_t out_rhs) {
-  const int L = g.ax[1].L, s = g.s[1], Lz = g.ax[2].L;
+    const FftTask* __restrict__ tasks, int n_tasks, int blocks,
+    const double2* __restrict__ twiddles, double2* __restrict__ scratch, int64_t scratch_rhs) {
+  const int block = xcd_block();
+  if (block >= blocks) return;
+  const FftTask& task = task_of(tasks, n_tasks, 1, block);
+  const FftGrid& g = task.g;
+  scratch += blockIdx.y * scratch_rhs;
+  const int w = task.lines[1], L = g.ax[1].L, s = g.s[1], Lz = g.ax[2].L;
   const int nin = INV ? L : s, nout = INV ? s : L;
   double2 *a = lds, *tw = a + 3 * L * w;
-  const int all = g.s[0] * Lz, l0 = xcd_block() * w;
-  if (l0 >= all) return;
+  const int all = g.s[0] * Lz, l0 = (block - task.first[1]) * w;
   load_twiddles(tw, twiddles, g.ax[1]);
   const Lane t(w);
   const int l = l0 + t.line / 3;
   const bool live = l < all;  // line l = (x, kz)
   const int x = l / Lz, kz = l - x * Lz, at = 3 * kz + t.line % 3;
-  const double2* p = in + blockIdx.y * in_rhs + (int64_t)x * nin * Lz * 3 + at;
-  double2* o = out + blockIdx.y * out_rhs + (int64_t)x * nout * Lz * 3 + at;
+  const double2* p = scratch + (INV ? task.yz : task.z) + (int64_t)x * nin * Lz * 3 + at;
+  double2* o = scratch + (INV ? task.z : task.yz) + (int64_t)x * nout * Lz * 3 + at;
   transform<INV>(
       g.ax[1], t, tw, a,
       [&](int pos) { return live && pos < nin ? p[3 * pos * Lz] : make_double2(0.0, 0.0); },
@@ -579,14 +611,19 @@ __global__ __launch_bounds__(kMaxFftThreads) void fft_y_kernel(
 // thread takes the three components of every (blockDim / w)-th position of a
 // line.
 __global__ __launch_bounds__(kMaxFftThreads) void fft_x_kernel(
-    double2* __restrict__ data, FftGrid g, const double2* __restrict__ twiddles,
-    const double2* __restrict__ spec, int w, int64_t rhs) {
-  data += blockIdx.y * rhs;
+    const FftTask* __restrict__ tasks, int n_tasks, int blocks,
+    const double2* __restrict__ twiddles, const double2* __restrict__ spectra,
+    double2* __restrict__ scratch, int64_t scratch_rhs) {
+  const int block = xcd_block();
+  if (block >= blocks) return;
+  const FftTask& task = task_of(tasks, n_tasks, 2, block);
+  const FftGrid& g = task.g;
   const FftAxis& ax = g.ax[0];
-  const int L = ax.L, s = g.s[0], Ly = g.ax[1].L, Lz = g.ax[2].L;
+  double2* data = scratch + blockIdx.y * scratch_rhs + task.yz;
+  const double2* spec = spectra + g.spec;
+  const int w = task.lines[2], L = ax.L, s = g.s[0], Ly = g.ax[1].L, Lz = g.ax[2].L;
   double2 *a = lds, *tw = a + 3 * L * w;
-  const int plane = Ly * Lz, l0 = xcd_block() * w;
-  if (l0 >= plane) return;
+  const int plane = Ly * Lz, l0 = (block - task.first[2]) * w;
   load_twiddles(tw, twiddles, ax);
   const Lane t(w);
   const bool live = l0 + t.line / 3 < plane;
@@ -631,17 +668,20 @@ __global__ __launch_bounds__(kMaxFftThreads) void fft_x_kernel(
 // where no box is strong; those that a box without finite coefficients is far
 // from are NaN.
 __global__ __launch_bounds__(kMaxFftThreads) void ifft_z_kernel(
-    const double2* __restrict__ in, const int2* __restrict__ map, FftGrid g,
-    const double2* __restrict__ twiddles, float* __restrict__ part, int nd, int kh,
-    int64_t in_rhs, int64_t part_rhs, const Reach* __restrict__ reach, int n_grid, int groups) {
-  in += blockIdx.z * in_rhs;
-  part += blockIdx.z * part_rhs;
-  const Reach of = reach[blockIdx.z * n_grid];
-  const int L = g.ax[2].L, w = nd / groups, row = 3 * nd * nd, nu = row * nd, s = g.s[2];
+    const int2* __restrict__ maps, const FftTask* __restrict__ tasks, int n_tasks,
+    const double2* __restrict__ twiddles, const double2* __restrict__ scratch,
+    int64_t scratch_rhs, float* __restrict__ part, int nd, int kh, int64_t part_rhs,
+    const Reach* __restrict__ reach, int n_grid) {
+  const FftTask& task = task_of(tasks, n_tasks, 0, blockIdx.x);
+  const FftGrid& g = task.g;
+  const ZBlock blk(task, nd);
+  const double2* in = scratch + blockIdx.y * scratch_rhs + task.z;
+  part += blockIdx.y * part_rhs;
+  const Reach of = reach[blockIdx.y * n_grid + task.index];
+  const int L = g.ax[2].L, w = blk.w, row = 3 * nd * nd, nu = row * nd, s = g.s[2];
   double2 *a = lds, *tw = a + 3 * L * w;
-  const int by = blockIdx.y, X = blockIdx.x / groups, my0 = (blockIdx.x - X * groups) * w;
-  const int bx = X / nd, mx = X - bx * nd;
-  const int2* col = map + ((int64_t)bx * g.n[1] + by) * g.n[2];
+  const int by = blk.by, X = blk.X, my0 = blk.my0, bx = blk.bx, mx = blk.mx;
+  const int2* col = maps + g.map + ((int64_t)bx * g.n[1] + by) * g.n[2];
   bool any = false;
   for (int i = threadIdx.x; i < g.n[2]; i += blockDim.x) any = any || col[i].y >= 0;
   if (!__syncthreads_or(any)) return;  // a column without rows
@@ -757,38 +797,6 @@ __global__ __launch_bounds__(kThreads) void spectrum_x_kernel(FftGrid g, int e,
   }
 }
 
-// Lines of a workgroup, of `all`: as many as the LDS budget and 512 threads
-// take, but no fewer than 1,024 workgroups (four per compute unit) while a
-// workgroup keeps a wavefront busy.
-int fit_lines(const FftAxis& ax, int all) {
-  int w = 64;
-  while (w > 1 && (3 * (size_t)ax.L * w * sizeof(double2) > kLineBytes ||
-                   3 * ax.butterflies() * w > 512 ||
-                   (all < 1024 * w && 3 * ax.butterflies() * w >= 128)))
-    w /= 2;
-  return w;
-}
-// Workgroups that share the n_d z lines of a plane of boxes.
-int z_groups(const FftAxis& ax, int nd) {
-  int groups = 1;
-  while (nd % groups || 3 * ax.butterflies() * (nd / groups) > 512) {
-    if (groups == nd) break;
-    ++groups;
-  }
-  return groups;
-}
-size_t line_bytes(const FftAxis& ax, int w) {
-  return (3 * (size_t)ax.L * w + ax.L) * sizeof(double2);
-}
-dim3 line_threads(const FftAxis& ax, int w) {
-  return dim3((3 * ax.butterflies() * w + 63) / 64 * 64);
-}
-
-// Workgroups of `lines` lines each, a multiple of 8 (xcd_block).
-unsigned blocks_of(int all, int lines) {
-  return (unsigned)((all + lines - 1) / lines + 7) / 8 * 8;
-}
-
 // Kernel launch with optional events at its start and end.
 template <typename... Args>
 void launch(void (*kernel)(Args...), dim3 grid, dim3 block, size_t shared, hipStream_t s,
@@ -825,17 +833,11 @@ int launch_fft_spectra(const Plan& p, hipStream_t s) {
 int launch_fft(const Plan& p, const float* P, float* part, int nrhs, hipStream_t s,
                hipEvent_t start, hipEvent_t stop) {
   const double2* tw = reinterpret_cast<const double2*>(p.d_fft_tw);
+  const double2* spectra = reinterpret_cast<const double2*>(p.d_fft_spec);
   const int64_t part_rhs = p.rest->n_pairs() * p.pstride();
-  int64_t zmax = 0, ymax = 0;
-  for (const FftGrid& g : p.fft) {
-    zmax = std::max(zmax, g.zlen());
-    ymax = std::max(ymax, g.yzlen());
-  }
-  // right-hand sides go through the scratch in blocks (fft_block)
-  const int block = (int)fft_block(p, p.max_nrhs), n_grid = (int)p.fft.size();
-  double2* bz = reinterpret_cast<double2*>(p.d_fft);
-  double2* by = bz + block * zmax;
-  float* norm = reinterpret_cast<float*>(by + block * ymax);
+  const int n_grid = (int)p.fft.size();
+  double2* lattices = reinterpret_cast<double2*>(p.d_fft);
+  float* norm = reinterpret_cast<float*>(lattices + fft_scratch_len(p, p.max_nrhs));
   Reach* reach = reinterpret_cast<Reach*>(norm + p.n_box * p.max_nrhs);
   const int2* maps = reinterpret_cast<const int2*>(p.d_fft_map);
   const int4* cells = reinterpret_cast<const int4*>(p.d_fft_cells);
@@ -852,35 +854,29 @@ int launch_fft(const Plan& p, const float* P, float* part, int nrhs, hipStream_t
   launch(reach_kernel, dim3(27, n_grid, nrhs), dim3(kReachThreads), 0, s, nullptr, nullptr, all,
          maps, cells, cells + p.n_box, (const float*)norm, p.a / p.n_d, p.k, p.eta, p.nu, reach,
          part, part_rhs);
-  for (int i = 0; i < n_grid; ++i) {
-    const FftGrid& g = p.fft[i];
-    const int2* map = maps + g.map;
-    const double2* spec = reinterpret_cast<const double2*>(p.d_fft_spec) + g.spec;
-    const int ny = g.s[0] * g.ax[2].L, nx = g.ax[1].L * g.ax[2].L;
-    const int yw = fit_lines(g.ax[1], ny), xw = fit_lines(g.ax[0], nx);
-    const int zg = z_groups(g.ax[2], p.n_d), zw = p.n_d / zg;
-    const dim3 zblock = line_threads(g.ax[2], zw), yblock = line_threads(g.ax[1], yw),
-               xblock = line_threads(g.ax[0], xw);
-    const size_t zb = line_bytes(g.ax[2], zw), yb = line_bytes(g.ax[1], yw),
-                 xb = line_bytes(g.ax[0], xw);
+  for (const FftGroup& g : p.fft_groups) {
+    const FftTask* tasks = p.d_fft_tasks + g.first;
+    const int n = g.count, block = (int)fft_block(g, p.max_nrhs);
+    const unsigned zb = (unsigned)g.blocks[0], yb = (unsigned)(g.blocks[1] + 7) / 8 * 8,
+                   xb = (unsigned)(g.blocks[2] + 7) / 8 * 8;  // multiples of 8: xcd_block
     for (int r0 = 0; r0 < nrhs; r0 += block) {
-      const int nr = std::min(block, nrhs - r0);
-      const bool last = i + 1 == n_grid && r0 + nr == nrhs;
-      const dim3 zgrid(g.n[0] * p.n_d * zg, g.n[1], nr), ygrid(blocks_of(ny, yw), nr),
-          xgrid(blocks_of(nx, xw), nr);
+      const unsigned nr = (unsigned)std::min(block, nrhs - r0);
+      const bool last = &g == &p.fft_groups.back() && r0 + block >= nrhs;
       Source src = all;
       src.P += (int64_t)r0 * p.n_box * p.vstride();
       src.box_scale += (int64_t)r0 * p.n_box;
-      launch(fft_z_kernel, zgrid, zblock, zb, s, nullptr, nullptr, src, map, g, tw, bz, zmax, zg,
-             (const float*)(norm + (int64_t)r0 * p.n_box));
-      launch(fft_y_kernel<false>, ygrid, yblock, yb, s, nullptr, nullptr, (const double2*)bz, g,
-             tw, by, yw, zmax, ymax);
-      launch(fft_x_kernel, xgrid, xblock, xb, s, nullptr, nullptr, by, g, tw, spec, xw, ymax);
-      launch(fft_y_kernel<true>, ygrid, yblock, yb, s, nullptr, nullptr, (const double2*)by, g, tw,
-             bz, yw, ymax, zmax);
-      launch(ifft_z_kernel, zgrid, zblock, zb, s, nullptr, last ? stop : nullptr,
-             (const double2*)bz, map, g, tw, part + r0 * part_rhs, p.n_d, p.kh, zmax, part_rhs,
-             (const Reach*)(reach + (int64_t)r0 * n_grid + i), n_grid, zg);
+      launch(fft_z_kernel, dim3(zb, nr), dim3(g.threads[0]), g.lds[0], s, nullptr, nullptr, src,
+             maps, tasks, n, tw, lattices, g.len, (const float*)(norm + (int64_t)r0 * p.n_box));
+      launch(fft_y_kernel<false>, dim3(yb, nr), dim3(g.threads[1]), g.lds[1], s, nullptr, nullptr,
+             tasks, n, g.blocks[1], tw, lattices, g.len);
+      launch(fft_x_kernel, dim3(xb, nr), dim3(g.threads[2]), g.lds[2], s, nullptr, nullptr, tasks,
+             n, g.blocks[2], tw, spectra, lattices, g.len);
+      launch(fft_y_kernel<true>, dim3(yb, nr), dim3(g.threads[1]), g.lds[1], s, nullptr, nullptr,
+             tasks, n, g.blocks[1], tw, lattices, g.len);
+      launch(ifft_z_kernel, dim3(zb, nr), dim3(g.threads[0]), g.lds[0], s, nullptr,
+             last ? stop : nullptr, maps, tasks, n, tw, (const double2*)lattices, g.len,
+             part + r0 * part_rhs, p.n_d, p.kh, part_rhs,
+             (const Reach*)(reach + (int64_t)r0 * n_grid), n_grid);
     }
   }
   return (int)hipGetLastError();

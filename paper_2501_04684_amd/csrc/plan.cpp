@@ -423,13 +423,18 @@ size_t row_bytes(const Plan& p, int32_t nrhs) {
 
 }  // namespace
 
-int64_t fft_block(const Plan& p, int32_t max_nrhs) {
-  const int64_t one = std::max<int64_t>(16 * p.fft_scratch_len(), 1);
-  return std::max<int64_t>(1, std::min<int64_t>(max_nrhs, (64ll << 20) / one));
+int64_t fft_block(const FftGroup& g, int32_t nrhs) {
+  return std::max<int64_t>(1, std::min<int64_t>(nrhs, kFftScratch / std::max<int64_t>(g.len, 1)));
+}
+
+int64_t fft_scratch_len(const Plan& p, int32_t nrhs) {
+  int64_t len = 0;
+  for (const FftGroup& g : p.fft_groups) len = std::max(len, fft_block(g, nrhs) * g.len);
+  return len;
 }
 
 size_t fft_scratch_bytes(const Plan& p, int32_t nrhs) {
-  return (size_t)fft_block(p, nrhs) * p.fft_scratch_len() * 16 +
+  return (size_t)fft_scratch_len(p, nrhs) * 16 +
          (size_t)nrhs * (p.n_box * sizeof(float) + p.fft.size() * kReachBytes);
 }
 
@@ -466,6 +471,7 @@ Layout workspace_layout(const Plan& p, int32_t max_nrhs) {
     L.fft_tw = take(p.fft_twiddles.size() * sizeof(double));
     L.fft_map = take(p.fft_map.size() * sizeof(int32_t));
     L.fft_cells = take(p.fft_cells.size() * sizeof(int32_t));
+    L.fft_tasks = take(p.fft_tasks.size() * sizeof(FftTask));
   }
   L.total = take.at;
   return L;
@@ -595,6 +601,64 @@ bool fft_axis(int64_t n, FftAxis& ax) {
   return false;
 }
 
+// LDS of one workgroup's lines: three workgroups share a compute unit (160 KB).
+constexpr size_t kLineBytes = 50 << 10;
+
+// Lines of a workgroup, of `all`: as many as the LDS budget and 512 threads
+// take, but no fewer than 1,024 workgroups (four per compute unit) while a
+// workgroup keeps a wavefront busy.
+int fit_lines(const FftAxis& ax, int64_t all) {
+  int w = 64;
+  while (w > 1 && (48 * (size_t)ax.L * w > kLineBytes || 3 * ax.butterflies() * w > 512 ||
+                   (all < 1024 * w && 3 * ax.butterflies() * w >= 128)))
+    w /= 2;
+  return w;
+}
+// Workgroups that share the n_d z lines of a plane of boxes.
+int z_groups(const FftAxis& ax, int nd) {
+  int groups = 1;
+  while (groups < nd && (nd % groups || 3 * ax.butterflies() * (nd / groups) > 512)) ++groups;
+  return groups;
+}
+
+// Tasks and groups of the plan's lattices: consecutive ones share launches
+// while a right-hand side of them fits the scratch.
+void build_fft_tasks(Plan& P) {
+  for (size_t i = 0; i < P.fft.size(); ++i) {
+    FftTask t{};
+    t.g = P.fft[i];
+    const FftGrid& g = t.g;
+    t.index = (int32_t)i;
+    const int64_t ny = (int64_t)g.s[0] * g.ax[2].L, nx = (int64_t)g.ax[1].L * g.ax[2].L;
+    const int zg = z_groups(g.ax[2], P.n_d), yw = fit_lines(g.ax[1], ny),
+              xw = fit_lines(g.ax[0], nx);
+    const int32_t lines[3] = {P.n_d / zg, yw, xw};
+    const int64_t blocks[3] = {(int64_t)g.n[0] * P.n_d * zg * g.n[1], (ny + yw - 1) / yw,
+                               (nx + xw - 1) / xw};
+    const int64_t len = g.zlen() + g.yzlen();
+    if (P.fft_groups.empty() || P.fft_groups.back().len + len > kFftScratch) {
+      P.fft_groups.emplace_back();
+      P.fft_groups.back().first = (int32_t)i;
+      P.fft_groups.back().count = 0;
+    }
+    FftGroup& G = P.fft_groups.back();
+    t.z = G.len;
+    t.yz = G.len + g.zlen();
+    G.len += len;
+    G.count += 1;
+    for (int k = 0; k < 3; ++k) {
+      const FftAxis& ax = g.ax[2 - k];
+      t.lines[k] = lines[k];
+      t.blocks[k] = (int32_t)blocks[k];
+      t.first[k] = G.blocks[k];
+      G.blocks[k] += t.blocks[k];
+      G.threads[k] = std::max(G.threads[k], (3 * ax.butterflies() * lines[k] + 63) / 64 * 64);
+      G.lds[k] = std::max(G.lds[k], (size_t)(3 * lines[k] + 1) * ax.L * 16);
+    }
+    P.fft_tasks.push_back(t);
+  }
+}
+
 // Whether a scatterer's FULL product runs as a convolution: by estimates of
 // both ways' microseconds for stages 2 and 3, fitted to both measured side by
 // side on 90 plans: cubes, plates, lines, shells, hollow cubes and masks of 64
@@ -719,6 +783,8 @@ void build_convolution(Plan& P) {
         P.fft_twiddles.push_back(-std::sin(2.0 * kPi * k / ax.L));
       }
     }
+
+  build_fft_tasks(P);
 
   // The pairs left: all of a scatterer without a lattice, the masked ones of
   // the others; grouped by (offset, masked), in P's order within a group.

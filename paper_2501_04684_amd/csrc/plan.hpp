@@ -149,6 +149,23 @@ struct FftGrid {
   int64_t yzlen() const { return 3LL * s[0] * ax[1].L * ax[2].L; }
 };
 
+// A scatterer's part of the three kinds of transform launches (z, y, x), which
+// take the lattices of a group together.
+struct FftTask {
+  FftGrid g;
+  int64_t z, yz;      // its lattices in the group's scratch of a right-hand side (complex values)
+  int32_t lines[3];   // lines of a workgroup
+  int32_t blocks[3];  // workgroups; z: that of a column of boxes' site planes, n[0] n_d splits
+  int32_t first[3];   // first workgroup in the launch
+  int32_t index;      // among the plan's lattices
+};
+struct FftGroup {
+  int32_t first, count;           // tasks
+  int64_t len = 0;                // scratch of a right-hand side (complex values)
+  int32_t blocks[3] = {}, threads[3] = {};
+  size_t lds[3] = {};
+};
+
 struct Plan {
   // Problem.
   int64_t n_box = 0;
@@ -265,6 +282,8 @@ struct Plan {
   // one partial row more (its first, written by the convolution), and
   // pair_src / pair_dst are padded to the number of rows.
   std::vector<FftGrid> fft;
+  std::vector<FftTask> fft_tasks;
+  std::vector<FftGroup> fft_groups;
   std::vector<int32_t> fft_map;
   // 4 per box: its cell (x, y, z) and lattice (-1: none); then 8 per lattice:
   // first box, boxes, first cell (64 bits), boxes per axis, 0
@@ -274,14 +293,6 @@ struct Plan {
   std::unique_ptr<Plan> rest;
   std::vector<uint8_t> op_masked;  // per offset; empty: none
   bool masked(int32_t o) const { return !op_masked.empty() && op_masked[o]; }
-  int64_t fft_scratch_len() const {
-    int64_t z = 0, yz = 0;
-    for (const FftGrid& g : fft) {
-      z = z > g.zlen() ? z : g.zlen();
-      yz = yz > g.yzlen() ? yz : g.yzlen();
-    }
-    return z + yz;
-  }
   // The plan whose pairs, rows and schedule stage 2 with operators uses.
   const Plan& pairs_plan() const { return rest ? *rest : *this; }
   Plan& pairs_plan() { return rest ? *rest : *this; }
@@ -310,6 +321,7 @@ struct Plan {
   double* d_fft_tw = nullptr;
   int32_t* d_fft_map = nullptr;
   int32_t* d_fft_cells = nullptr;
+  FftTask* d_fft_tasks = nullptr;
   float* d_box_scale = nullptr;  // [max_nrhs][n_box] box-vector scales (FP16 forms)
 
   // Networks standing in for the operators (Sec. 3): hidden width (0 = none,
@@ -336,20 +348,24 @@ struct Layout {
         off_scale, offsets;
   };
   Pairs own, rest;
-  size_t nb_ptr, P, part, box_scale, fft, fft_spec, fft_tw, fft_map, fft_cells, total;
+  size_t nb_ptr, P, part, box_scale, fft, fft_spec, fft_tw, fft_map, fft_cells, fft_tasks, total;
 };
 Layout workspace_layout(const Plan& p, int32_t max_nrhs);
 // Whether a bound plan holds its own far set's arrays and rows: without a
 // convolution, or where networks may be set (the FP32 form).
 inline bool holds_own_pairs(const Plan& p) { return !p.rest || p.precision == 0; }
 
-// Right-hand sides that pass through the convolution's scratch together: as
-// many as 64 MB hold (small lattices are bound by their launches, large ones
-// by memory, where one at a time keeps more in the caches).
-int64_t fft_block(const Plan& p, int32_t max_nrhs);
+// The convolution's scratch holds the lattices of as many scatterers and
+// right-hand sides as this takes (at least one): small lattices are bound by
+// their launches, which they share, large ones by memory, where one at a time
+// keeps more in the caches.
+constexpr int64_t kFftScratch = (64 << 20) / 16;  // complex values
+// Right-hand sides of a group that pass through the scratch together.
+int64_t fft_block(const FftGroup& g, int32_t nrhs);
 // Scratch of the convolution for nrhs right-hand sides: the lattices of a
 // block of them, then per right-hand side a float for each box and a
 // kReachBytes record for each lattice.
+int64_t fft_scratch_len(const Plan& p, int32_t nrhs);  // lattices, complex values
 size_t fft_scratch_bytes(const Plan& p, int32_t nrhs);
 
 // The per-call intermediates of one product of nrhs right-hand sides (box

@@ -148,3 +148,35 @@ def test_non_finite_coefficients_stay_with_their_pairs(n_d, precision, operators
             parity(E[r:r + 1, keep], ref[:, keep], TOL[precision], boxes=n_u,
                    label=f"beside non-finite boxes {r}, n_d={n_d} {precision}")
     ff.close()
+
+
+@pytest.mark.parametrize("n_d, precision", [(3, "split-fp16"), (3, "fp32")])
+def test_lattices_of_a_batch_share_launches(n_d, precision):
+    """Lattices of several lengths in one plan, some filling the scratch by
+    themselves (n_d = 3: 64 MB hold no two of the masks), some sharing it: each
+    scatterer gives the same bits as in a plan of its own."""
+    mask = W.mask_boxes(600, 0.05, 2)
+    parts = [mask, W.grid_boxes(9, 8, 7), W.mask_boxes(600, 0.05, 3), W.grid_boxes(9, 8, 7),
+             W.grid_boxes(3, 3, 3), W.hollow_cube_boxes(9), W.grid_boxes(40, 23, 1)]
+    starts = np.cumsum([0] + [len(p) for p in parts])
+    P = W.complex_normal((3, int(starts[-1]), 3 * n_d ** 3), 21)
+    announce("batch of lattices", n_d, precision, starts)
+
+    def product(scatterers, x):
+        ff = U.FarField(None, 0.25, TWO_PI, n_d, "full", max_nrhs=3, precision=precision,
+                        scatterers=scatterers)
+        E = torch.full(x.shape, float("nan"), dtype=torch.complex64, device="cuda")
+        U.translate(ff.plan, to_dev(x), E, len(x))
+        E = to_host(E)
+        ff.close()
+        return E
+
+    E = product(parts, P)
+    for i, p in enumerate(parts):
+        s = slice(starts[i], starts[i + 1])
+        assert np.array_equal(product([p], P[:, s]), E[:, s]), i
+    sample = np.arange(0, len(mask), 61)
+    ref = O.translate(P[:, :len(mask)].astype(np.complex128), mask, 0.25, TWO_PI, n_d, mode="full",
+                      test_boxes=sample)
+    parity(E[:, sample], ref[:, sample], TOL[precision], boxes=3 * n_d ** 3,
+           label=f"batch of lattices n_d={n_d} {precision}")
