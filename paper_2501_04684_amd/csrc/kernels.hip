@@ -2173,8 +2173,11 @@ int launch_disaggregate(const Plan& p, const Plan* rows, const float* part,
              (const float2*)p.d_S, mode, (float2*)y, p.n_box, nb_total, p.nu, p.kh)
   // One wavefront per box while a box has up to a few hundred partial rows
   // on average (interaction lists: tens); with thousands per box (FULL far
-  // sets) the row sums want a whole workgroup per box.
-  const bool few_rows = n_rows <= 256 * p.n_box;
+  // sets) the row sums want a whole workgroup per box. Beside a convolution
+  // the rows left are few only where no box has many: by their average, one
+  // wavefront summed the 592 rows of each box of a plate in a batch with three
+  // scatterers of one row per box (51 us, 25 with a workgroup per box).
+  const bool few_rows = p.n_pairs() <= 256 * p.n_box || (rows && rows->max_rows <= 256);
   // When the boxes fill about two rounds of the chip (up to 16 resident
   // wavefronts per CU), one wavefront per workgroup lets the dispatcher
   // spread them evenly (with four per workgroup a quarter of the CUs of the

@@ -833,6 +833,7 @@ void build_convolution(Plan& P) {
   const int64_t n_rows = R->test_ptr.back();
   R->pair_dst.resize(nr);
   for (int64_t q = 0; q < nr; ++q) R->pair_dst[q] = fill[R->pair_test[q]]++;
+  R->count_rows();
   build_units(*R);
   R->pair_src.resize(n_rows, 0);
   R->pair_dst.resize(n_rows, 0);
@@ -1001,6 +1002,7 @@ std::string build_plan(const int32_t* box_ijk, int64_t n_box, double a,
   P.pair_dst.resize(np);
   for (int64_t q = 0; q < np; ++q) P.pair_dst[P.test_pos[q]] = (int32_t)q;
 
+  P.count_rows();
   build_units(P);
 
   // Orbits under the 48 signed permutations: key = sorted |w|.

@@ -183,6 +183,7 @@ struct Plan {
   std::vector<int32_t> pair_src;   // n_pairs
   std::vector<int32_t> pair_off;   // n_pairs
   std::vector<int32_t> test_ptr;   // n_box + 1: pairs of each test box ...
+  int32_t max_rows = 0;            // most of a box
   std::vector<int32_t> test_pos;   // ... as positions in the grouped order
   std::vector<int32_t> pair_dst;   // grouped position -> test-major position
   std::vector<int32_t> chunks;     // 4 per chunk: offset, begin, count, 0
@@ -292,6 +293,13 @@ struct Plan {
   int64_t fft_spec_len = 0;     // complex values of all spectra
   std::unique_ptr<Plan> rest;
   std::vector<uint8_t> op_masked;  // per offset; empty: none
+  void count_rows() {
+    max_rows = 0;
+    for (int64_t j = 0; j < n_box; ++j) {
+      const int32_t n = test_ptr[j + 1] - test_ptr[j];
+      max_rows = n > max_rows ? n : max_rows;
+    }
+  }
   bool masked(int32_t o) const { return !op_masked.empty() && op_masked[o]; }
   // The plan whose pairs, rows and schedule stage 2 with operators uses.
   const Plan& pairs_plan() const { return rest ? *rest : *this; }

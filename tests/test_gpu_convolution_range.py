@@ -180,3 +180,27 @@ def test_lattices_of_a_batch_share_launches(n_d, precision):
                       test_boxes=sample)
     parity(E[:, sample], ref[:, sample], TOL[precision], boxes=3 * n_d ** 3,
            label=f"batch of lattices n_d={n_d} {precision}")
+
+
+@pytest.mark.parametrize("basis", [False, True])
+def test_many_rows_beside_a_convolution(basis):
+    """A plate whose boxes have 592 rows each, pair by pair, in a plan with a
+    convolution's single rows: the row sums of both."""
+    parts = [W.grid_boxes(30, 10, 2), W.mask_boxes(600, 0.05, 2)]
+    starts = np.cumsum([0] + [len(p) for p in parts])
+    ff = U.FarField(None, 0.25, TWO_PI, 1, "full", max_nrhs=2, precision="split-fp16",
+                    scatterers=parts)
+    nb_ptr, S = 3 * np.arange(starts[-1] + 1), None
+    if basis:
+        nb_ptr, S = W.random_basis(np.full(starts[-1], 5), 3, 6)
+        ff.set_basis(nb_ptr, to_dev(S))
+    x = W.complex_normal((2, int(nb_ptr[-1])), 8)
+    announce("many rows beside a convolution", basis)
+    y = to_host(ff(to_dev(x)))
+    for i, p in enumerate(parts):
+        lo, hi = int(nb_ptr[starts[i]]), int(nb_ptr[starts[i + 1]])
+        q = nb_ptr[starts[i]:starts[i + 1] + 1] - lo
+        s = None if S is None else S[3 * lo:3 * hi].astype(np.complex128)
+        ref = O.far_mvm(x[:, lo:hi].astype(np.complex128), p, 0.25, TWO_PI, 1, q, s, mode="full")
+        parity(y[:, lo:hi], ref, 3e-6, boxes=q, box_tol=1e-5, label=f"uneven scatterer {i}")
+    ff.close()
