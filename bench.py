@@ -487,7 +487,8 @@ def run_form(U, W, torch, w, precision, basis, nrhs, warmup, steps, copy_mb=0,
         U.far_mvm(ff.plan, X[v], Y, nrhs, stream)
         Ys[v] = Y.cpu().numpy()
     torch.cuda.synchronize()
-    out = {"info": ff.info, "plan_ms": plan_ms, "dt": dt, "value": steps * nrhs / dt,
+    out = {"info": ff.info, "stage2": U.plan_stage2(ff.plan), "plan_ms": plan_ms, "dt": dt,
+           "value": steps * nrhs / dt,
            "avg_us": stage_ms / len(call_ms) * 1e3, "call_ms": call_ms, "latency": lat,
            "Y": Ys, "X": X.cpu().numpy(), "nb_ptr": nb_ptr, "S": S, "nb_total": nb_total,
            "tune": tune}
@@ -914,9 +915,8 @@ def main():
     dom = int(np.argmax(avg_us))
     peak = PEAK_BF16_MFMA_TFLOPS if split else PEAK_FP32_MFMA_TFLOPS
     ach = (issued if split else flops) / (avg_us[1] * 1e-6) / 1e12
-    # a FULL far set whose pairs would need more than the peak rate ran as a
-    # convolution: its stage 2 has no flops per pair, only its input and output
-    convolution = w.far_mode == "full" and ach > peak
+    # a convolution's stage 2 has no flops per pair, only its input and output
+    convolution = res["stage2"]["n_convolved"] > 0
     bytes_conv = 2 * nrhs * n_box * nu * 8
     if convolution:
         translate_kernel = "convolution"

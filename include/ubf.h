@@ -154,6 +154,16 @@ typedef struct ubf_info {
   int32_t operators;        /* enum ubf_operator_source */
 } ubf_info;
 
+/* How stage 2 runs on a plan as it stands (networks set or not). */
+typedef struct ubf_stage2 {
+  int32_t n_convolved; /* scatterers whose FULL product is a convolution */
+  int32_t rhs_block;   /* right-hand sides that pass through its lattices
+                          together, at the binding's max_nrhs; 0 without a
+                          convolution or a binding */
+  int64_t n_pairs;     /* far pairs per right-hand side that the translation
+                          kernels take (beside a convolution: the pairs left) */
+} ubf_stage2;
+
 /* Stage-2 kernels of the 16-bit forms (ubf_plan_schedule, ubf_plan_tune).
  * All compute each column with the same products in the same order, so
  * they agree bit for bit; they differ in how the work is scheduled. */
@@ -449,6 +459,9 @@ void ubf_gmres_destroy(ubf_gmres* solver);
 
 /* Plan sizes and work counts. Errors: UBF_EINVAL for null pointers. */
 int ubf_plan_info(const ubf_plan* plan, ubf_info* out);
+
+/* UBF_EINVAL for a null argument. */
+int ubf_plan_stage2(const ubf_plan* plan, ubf_stage2* out);
 
 /* Host copy of the distinct offsets w (3*n_offsets int32, in the plan's
  * offset order). Errors: UBF_EINVAL for null pointers. */

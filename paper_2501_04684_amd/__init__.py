@@ -80,6 +80,11 @@ class _Info(ctypes.Structure):
                 ("translate_kernel", ctypes.c_int32), ("operators", ctypes.c_int32)]
 
 
+class _Stage2(ctypes.Structure):
+    _fields_ = [("n_convolved", ctypes.c_int32), ("rhs_block", ctypes.c_int32),
+                ("n_pairs", ctypes.c_int64)]
+
+
 class _GmresStatus(ctypes.Structure):
     _fields_ = [("ready", ctypes.c_int32), ("done", ctypes.c_int32),
                 ("converged", ctypes.c_int32), ("steps", ctypes.c_int32),
@@ -108,6 +113,7 @@ _SIGS = {
     "ubf_translate": (ctypes.c_int, [_VP, _VP, _VP, _I32, _VP]),
     "ubf_disaggregate": (ctypes.c_int, [_VP, _VP, _VP, _I32, _VP]),
     "ubf_plan_info": (ctypes.c_int, [_VP, ctypes.POINTER(_Info)]),
+    "ubf_plan_stage2": (ctypes.c_int, [_VP, ctypes.POINTER(_Stage2)]),
     "ubf_plan_offsets": (ctypes.c_int, [_VP, _VP]),
     "ubf_plan_far_pairs": (ctypes.c_int, [_VP, _VP, _VP, _VP]),
     "ubf_plan_operator": (ctypes.c_int, [_VP, _I32, _VP]),
@@ -323,6 +329,14 @@ def plan_info(plan) -> dict:
     info = _Info()
     _check(lib().ubf_plan_info(plan, ctypes.byref(info)), "ubf_plan_info")
     return {name: getattr(info, name) for name, _ in _Info._fields_}
+
+
+def plan_stage2(plan) -> dict:
+    """How stage 2 runs: convolved scatterers, right-hand sides per block of
+    the convolution, pairs the translation kernels take."""
+    st = _Stage2()
+    _check(lib().ubf_plan_stage2(plan, ctypes.byref(st)), "ubf_plan_stage2")
+    return {name: getattr(st, name) for name, _ in _Stage2._fields_}
 
 
 def plan_offsets(plan) -> np.ndarray:

@@ -735,6 +735,23 @@ int ubf_plan_info(const ubf_plan* plan, ubf_info* out) {
   return ok();
 }
 
+int ubf_plan_stage2(const ubf_plan* plan, ubf_stage2* out) {
+  if (!plan || !out) return fail(UBF_EINVAL, "plan or out is NULL");
+  const ubf::Plan& p = plan->p;
+  std::memset(out, 0, sizeof(*out));
+  out->n_pairs = p.n_pairs();
+  if (!p.rest || p.hidden > 0) return ok();
+  out->n_convolved = (int32_t)p.fft.size();
+  out->n_pairs = p.rest->off_ptr.back();
+  if (p.ws) {
+    int64_t block = p.max_nrhs;
+    for (const ubf::FftGroup& g : p.fft_groups)
+      block = std::min(block, ubf::fft_block(g, p.max_nrhs));
+    out->rhs_block = (int32_t)block;
+  }
+  return ok();
+}
+
 int ubf_plan_offsets(const ubf_plan* plan, int32_t* out) {
   if (!plan || !out) return fail(UBF_EINVAL, "plan or out is NULL");
   // an empty far set has no offsets (and vector::data() may then be null)

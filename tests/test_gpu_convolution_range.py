@@ -60,6 +60,11 @@ def test_boxes_keep_their_own_error(n_d, precision, operators):
     P = _vectors(boxes, n_u, strong, 11 + n_d)
     ff = U.FarField(boxes, 0.25, TWO_PI, n_d, "full", max_nrhs=len(P), precision=precision,
                     operators=operators)
+    stage2 = U.plan_stage2(ff.plan)
+    assert stage2["n_convolved"] == 1
+    # the right-hand sides go through the lattices in blocks, the last part full
+    if n_d >= 3:
+        assert stage2["rhs_block"] < len(P) and len(P) % stage2["rhs_block"]
     E = torch.full(P.shape, float("nan"), dtype=torch.complex64, device="cuda")
     U.translate(ff.plan, to_dev(P), E, len(P))
     E = to_host(E)
@@ -81,6 +86,7 @@ def test_ranges_of_neighbouring_scatterers_are_their_own():
     n_u = 81
     ff = U.FarField(None, 0.25, TWO_PI, 3, "full", max_nrhs=2, precision="split-fp16",
                     scatterers=parts)
+    assert U.plan_stage2(ff.plan)["n_convolved"] == 3
     starts = np.cumsum([0] + [len(p) for p in parts])
     P = W.complex_normal((2, int(starts[-1]), n_u), 5)
     P[0, :starts[1]] *= np.float32(1e12)
@@ -130,6 +136,7 @@ def test_non_finite_coefficients_stay_with_their_pairs(n_d, precision, operators
     announce("non-finite", n_d, precision, operators)
     ff = U.FarField(None, 0.25, TWO_PI, n_d, "full", max_nrhs=len(P), precision=precision,
                     operators=operators, scatterers=parts)
+    assert U.plan_stage2(ff.plan)["n_convolved"] == 2
     E = torch.zeros(P.shape, dtype=torch.complex64, device="cuda")
     U.translate(ff.plan, to_dev(P), E, len(P))
     E = to_host(E)
@@ -165,6 +172,8 @@ def test_lattices_of_a_batch_share_launches(n_d, precision):
     def product(scatterers, x):
         ff = U.FarField(None, 0.25, TWO_PI, n_d, "full", max_nrhs=3, precision=precision,
                         scatterers=scatterers)
+        if len(scatterers) > 1:
+            assert U.plan_stage2(ff.plan)["n_convolved"] == 6  # not the 27 boxes
         E = torch.full(x.shape, float("nan"), dtype=torch.complex64, device="cuda")
         U.translate(ff.plan, to_dev(x), E, len(x))
         E = to_host(E)
@@ -190,6 +199,7 @@ def test_many_rows_beside_a_convolution(basis):
     starts = np.cumsum([0] + [len(p) for p in parts])
     ff = U.FarField(None, 0.25, TWO_PI, 1, "full", max_nrhs=2, precision="split-fp16",
                     scatterers=parts)
+    assert U.plan_stage2(ff.plan)["n_convolved"] == 1
     nb_ptr, S = 3 * np.arange(starts[-1] + 1), None
     if basis:
         nb_ptr, S = W.random_basis(np.full(starts[-1], 5), 3, 6)
