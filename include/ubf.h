@@ -138,8 +138,11 @@ typedef struct ubf_info {
   int32_t n_u;              /* uniform-basis coefficients per box, 3*n_d^3 */
   int32_t n_d;
   int64_t n_chunks;         /* translation work units (per RHS) */
-  int64_t table_bytes;      /* device operator table (with a convolution: that of
-                               the pairs left) */
+  int64_t table_bytes;      /* the distinct operators as the matrix cores take
+                               them (with a convolution: of the pairs left; 0
+                               where the kernel evaluates them). What the
+                               device stores: ubf_stage2.table_bytes, a tenth
+                               for the 16-bit forms at n_d = 4 */
   double translate_flops;   /* real flops per RHS: 8 * n_u^2 * n_pairs */
   int32_t mfma;             /* 1 if stage 2 runs on the matrix cores */
   int32_t precision;        /* enum ubf_precision of the plan */
@@ -162,6 +165,7 @@ typedef struct ubf_stage2 {
                           convolution or a binding */
   int64_t n_pairs;     /* far pairs per right-hand side that the translation
                           kernels take (beside a convolution: the pairs left) */
+  int64_t table_bytes; /* operator images in the workspace */
 } ubf_stage2;
 
 /* Stage-2 kernels of the 16-bit forms (ubf_plan_schedule, ubf_plan_tune).

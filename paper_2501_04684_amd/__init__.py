@@ -82,7 +82,7 @@ class _Info(ctypes.Structure):
 
 class _Stage2(ctypes.Structure):
     _fields_ = [("n_convolved", ctypes.c_int32), ("rhs_block", ctypes.c_int32),
-                ("n_pairs", ctypes.c_int64)]
+                ("n_pairs", ctypes.c_int64), ("table_bytes", ctypes.c_int64)]
 
 
 class _GmresStatus(ctypes.Structure):
@@ -333,7 +333,7 @@ def plan_info(plan) -> dict:
 
 def plan_stage2(plan) -> dict:
     """How stage 2 runs: convolved scatterers, right-hand sides per block of
-    the convolution, pairs the translation kernels take."""
+    the convolution, pairs the translation kernels take, stored operators."""
     st = _Stage2()
     _check(lib().ubf_plan_stage2(plan, ctypes.byref(st)), "ubf_plan_stage2")
     return {name: getattr(st, name) for name, _ in _Stage2._fields_}

@@ -740,6 +740,7 @@ int ubf_plan_stage2(const ubf_plan* plan, ubf_stage2* out) {
   const ubf::Plan& p = plan->p;
   std::memset(out, 0, sizeof(*out));
   out->n_pairs = p.n_pairs();
+  out->table_bytes = (int64_t)p.pairs_plan().table_bytes();
   if (!p.rest || p.hidden > 0) return ok();
   out->n_convolved = (int32_t)p.fft.size();
   out->n_pairs = p.rest->off_ptr.back();

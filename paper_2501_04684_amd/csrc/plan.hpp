@@ -264,8 +264,8 @@ struct Plan {
   // Box vectors of stage 1 -> 2, in floats: FP32 [re | im] halves, or in
   // split mode [re: hi, lo | im: hi, lo] BF16 runs of khb values.
   int vstride() const { return split() ? 2 * khb : 2 * kh; }
-  // Operator table as the plan's information reports it: the matrix-core
-  // operands of every offset's operator.
+  // The operators as the matrix cores take them (ubf_info.table_bytes): larger
+  // than the stored images where these hold lattice differences.
   size_t operand_bytes() const {
     if (!staged_split()) return table_bytes();
     return table_bytes() / (kLatticeHalves * sizeof(uint16_t)) * ((size_t)2 * nu * 2 * nu * 2);

@@ -42,9 +42,32 @@ def test_plans_without_a_convolution():
     boxes = W.grid_boxes(13, 9, 8)
     for far, n_d, precision in (("ilist", 3, "fp32"), ("full", 3, "fp16")):
         s, info = _stage2(n_d, precision, [boxes], far)
-        assert s == {"n_convolved": 0, "rhs_block": 0, "n_pairs": info["n_pairs"]}
+        assert (s["n_convolved"], s["rhs_block"], s["n_pairs"]) == (0, 0, info["n_pairs"])
     s, info = _stage2(3, "split-fp16", [W.grid_boxes(4, 4, 4)])
-    assert s == {"n_convolved": 0, "rhs_block": 0, "n_pairs": info["n_pairs"]}
+    assert (s["n_convolved"], s["rhs_block"], s["n_pairs"]) == (0, 0, info["n_pairs"])
+
+
+def test_stored_operators():
+    """table_bytes is what the workspace holds: at n_d = 4 in the 16-bit forms
+    1,204 runs of four values per source component and part, of 384 x 192
+    operands; in the others the operands themselves."""
+    boxes = W.grid_boxes(6, 6, 6)
+    ws = {}
+    for form, parts in (("fp16", 1), ("split-fp16", 2), ("split-bf16", 2)):
+        plan = U.plan_create(boxes, 0.125, K, 4, "ilist", precision=form)
+        try:
+            n_off = U.plan_info(plan)["n_offsets"]
+            assert U.plan_stage2(plan)["table_bytes"] == n_off * parts * 3 * 1204 * 4 * 2
+            ws[form] = U.workspace_bytes(plan, 1)
+        finally:
+            U.plan_destroy(plan)
+    assert 0 <= abs(ws["split-fp16"] - ws["fp16"] - n_off * 3 * 1204 * 4 * 2) < 256
+    assert ws["split-fp16"] == ws["split-bf16"]
+    for n_d, form in ((1, "fp32"), (3, "fp32"), (4, "fp32"), (3, "split-fp16"), (2, "fp16")):
+        s, info = _stage2(n_d, form, [boxes], "ilist")
+        assert s["table_bytes"] == info["table_bytes"] > 0
+    s, _ = _stage2(3, "split-fp16", [boxes], "ilist", "generated")
+    assert s["table_bytes"] == 0
 
 
 def test_a_scatterer_is_judged_alone():
