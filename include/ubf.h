@@ -338,7 +338,8 @@ int ubf_plan_replay(ubf_plan* plan, void* hip_stream);
  * goes to *groups_out (may be NULL), the kernel to ubf_info's
  * translate_kernel. If the environment variable UBF_TUNE_CACHE names a
  * file, a schedule recorded there for the same plan statistics (form, N_u,
- * nrhs, boxes, scatterers, pairs, offsets, chunks, items) is applied
+ * nrhs, boxes, scatterers, pairs, offsets, chunks, items; beside a
+ * convolution those of the pairs left, marked as such) is applied
  * without timing, and a new choice is appended to it with every
  * candidate's time. Runs and waits on hip_stream; overwrites the
  * workspace's internal vectors (never x or y). Results of later products

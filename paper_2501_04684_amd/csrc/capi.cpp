@@ -221,14 +221,18 @@ std::vector<Candidate> tune_candidates(const ubf::Plan& p, int nrhs) {
 }
 
 // The plan statistics a schedule is chosen for: the stage-2 form, box size,
-// vectors per call and the sizes of the far set and its partition.
-std::string tune_key(const ubf::Plan& p, int nrhs) {
+// vectors per call and the sizes of the far set and its partition, of the
+// pairs that the schedule is for; whether these are left beside a convolution,
+// and whether the grid counts items of the kernel that splits rows. (Lines
+// without these two words were written before there was either.)
+std::string tune_key(const ubf::Plan& p, bool left, int nrhs) {
   return "v2 precision=" + std::to_string(p.precision) +
          " operators=" + std::to_string(p.gen_ops ? 1 : 0) + " nu=" + std::to_string(p.nu) +
          " nrhs=" + std::to_string(nrhs) + " boxes=" + std::to_string(p.n_box) +
          " scatterers=" + std::to_string(p.n_scat()) + " pairs=" + std::to_string(p.n_pairs()) +
          " offsets=" + std::to_string(p.n_off()) + " chunks=" + std::to_string(p.n_chunks()) +
-         " items=" + std::to_string(p.n_items());
+         " items=" + std::to_string(p.n_items()) + (left ? " left" : "") +
+         (p.row_split() ? " rows" : "");
 }
 
 // Cache file (UBF_TUNE_CACHE): one line per key, "<key>\t<kernel> <groups>
@@ -507,14 +511,14 @@ int ubf_plan_tune(ubf_plan* plan, int32_t nrhs, int32_t reps, void* hip_stream,
   if (p.hidden > 0 || ubf::staged_translate_supported(p) || p.pairs_plan().n_chunks() == 0) {
     // stage 2 runs one workgroup per 32 pairs here, or has no pairs for the
     // translation kernels: nothing to choose
-    if (groups_out) *groups_out = (int32_t)p.pairs_plan().n_groups();
+    if (groups_out) *groups_out = (int32_t)ubf::rows_plan(p).n_groups();
     return ok();
   }
   plan->drop_graph();
   hipStream_t s = (hipStream_t)hip_stream;
   // beside a convolution the schedule is that of the pairs left
   ubf::Plan& q = p.pairs_plan();
-  const std::string key = tune_key(p, nrhs);
+  const std::string key = tune_key(q, p.rest != nullptr, nrhs);
   const char* cache = std::getenv("UBF_TUNE_CACHE");
   int kernel = -1, groups = 0;
   const auto usable = [&](int k) {  // a cache line may hold any kernel number
@@ -729,8 +733,8 @@ int ubf_plan_info(const ubf_plan* plan, ubf_info* out) {
   out->precision = p.precision;
   out->n_scatterers = p.n_scat();
   out->n_items = p.n_items();
-  out->translate_kernel = p.pairs_plan().split_kernel;
-  out->translate_groups = current_groups(p.pairs_plan());
+  out->translate_kernel = ubf::rows_plan(p).split_kernel;
+  out->translate_groups = current_groups(ubf::rows_plan(p));
   out->operators = p.gen_ops ? UBF_OPERATORS_GENERATED : UBF_OPERATORS_TABLE;
   return ok();
 }
