@@ -20,7 +20,6 @@ constexpr int kThreads = 512;
 constexpr int kWaves = kThreads / 64;
 constexpr int kColTile = 4;    // Krylov columns per pass over w
 constexpr int kElems = 2;      // elements of a slice per thread and batch of loads (dots)
-constexpr int kSlice = 2048;   // elements of a block's slice (larger once kDotBlocks are out)
 
 __device__ inline double2 cmul(double2 a, double2 b) {
   return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
@@ -48,10 +47,10 @@ __device__ inline double2 wave_sum(double2 v) {
 // kernel ran one thread per column over all blocks' partials, a chain of 256
 // dependent additions with exposed loads: 55 us each on the 762-box sphere
 // (one vector), 74 us on a 5,288-box mask (four), three times per step.
-// The block count depends on n alone, so that a right-hand side's sums do
-// not depend on its neighbours. partial: [R][ldp][kDotBlocks].
+// The block count depends on n alone (gmres_blocks), so that a right-hand
+// side's sums do not depend on its neighbours. partial: [R][ldp][blocks].
 __device__ inline double2* partial_of(double2* partial, int r, int ldp, int c) {
-  return partial + ((int64_t)r * ldp + c) * kDotBlocks;
+  return partial + ((int64_t)r * ldp + c) * gridDim.x;
 }
 
 // hs[c] = sum over the blocks of column c's partials, c < ncol (ends with a
@@ -61,7 +60,7 @@ __device__ __forceinline__ void gather_partials(const double2* __restrict__ part
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int nblk = gridDim.x;
   for (int c = wave; c < ncol; c += kWaves) {
-    const double2* p = partial + ((int64_t)r * ldp + c) * kDotBlocks;
+    const double2* p = partial + ((int64_t)r * ldp + c) * nblk;
     double2 s = make_double2(0.0, 0.0);
     for (int b = lane; b < nblk; b += 64) {
       s.x += p[b].x;
@@ -567,13 +566,7 @@ __global__ void inv_norm_kernel(const double2* __restrict__ nrm, double* __restr
   }
 }
 
-// Blocks per right-hand side: slices of kSlice elements, at most kDotBlocks
-// (a function of n alone, see gather_partials).
-unsigned slices(int64_t n) {
-  const int64_t b = (n + kSlice - 1) / kSlice;
-  return (unsigned)(b < 1 ? 1 : (b > kDotBlocks ? kDotBlocks : b));
-}
-constexpr int kLdp = kMaxRestart + 1;
+unsigned slices(int64_t n) { return (unsigned)gmres_blocks(n); }
 
 }  // namespace
 
@@ -582,13 +575,13 @@ int launch_gmres_step(const GmresState& st, const float2* V, int64_t vstride, in
                       double2* partial, double2* partial2, const int32_t* active_in,
                       int32_t* active_out, GmresStatusRow* status, hipStream_t s) {
   const dim3 grid(slices(n), R), block(kThreads);
-  const int ld = st.m + 1;
+  const int ld = st.m + 1;  // of h1, h2 and the partials
   hipLaunchKernelGGL(orth_first_kernel, grid, block, 0, s, V, vstride, j, w, sr, si, n, R,
-                     partial, kLdp);
+                     partial, ld);
   hipLaunchKernelGGL(orth_second_kernel, grid, block, 0, s, V, vstride, j + 1, w, n, R, partial,
-                     partial2, kLdp, st.h1, ld);
+                     partial2, ld, st.h1, ld);
   hipLaunchKernelGGL(orth_last_kernel, grid, block, 0, s, V, vstride, j + 1, w, n, R, partial2,
-                     kLdp, partial, st.h2, ld);
+                     ld, partial, st.h2, ld);
   hipLaunchKernelGGL(next_column_kernel, grid, block, 0, s, st, j, tol, partial, active_in,
                      active_out, w, vnext, n, R, status);
   return (int)hipGetLastError();

@@ -13,6 +13,13 @@ namespace ubf {
 constexpr int kMaxRestart = 128;  // Krylov columns per cycle (restart length)
 constexpr int kMaxGmresRhs = 64;  // right-hand sides per solver
 constexpr int kDotBlocks = 256;   // most blocks of the two-level sums
+constexpr int kSlice = 2048;      // elements of a block's slice (more once kDotBlocks are out)
+
+// Blocks per right-hand side of the vector kernels.
+inline int gmres_blocks(int64_t n) {
+  const int64_t b = (n + kSlice - 1) / kSlice;
+  return (int)(b < 1 ? 1 : (b > kDotBlocks ? kDotBlocks : b));
+}
 
 // Per-RHS row copied to the host after each step.
 struct GmresStatusRow {
@@ -42,8 +49,9 @@ struct GmresState {
 // One Arnoldi step after w = Z v_j (four launches): w += sigma v_j, two
 // classical Gram-Schmidt passes, v_{j+1}, the rotations and the status rows
 // (written by the kernel; the caller's pinned host memory). partial and
-// partial2 hold [R][kMaxRestart + 1][kDotBlocks] each. active_in/active_out:
-// the flags before and after the step (different arrays).
+// partial2 hold [R][m + 1][gmres_blocks(n)] each; partial2 may lie in vnext,
+// which is written last. active_in/active_out: the flags before and after the
+// step (different arrays).
 int launch_gmres_step(const GmresState& st, const float2* V, int64_t vstride, int j, float2* w,
                       float2* vnext, double sr, double si, double tol, int64_t n, int R,
                       double2* partial, double2* partial2, const int32_t* active_in,

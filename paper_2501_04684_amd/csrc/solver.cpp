@@ -30,7 +30,7 @@ struct ubf_gmres {
   float2* V = nullptr;  // (m+1) blocks of [R][n]
   float2* W = nullptr;  // [R][n]
   double2* partial = nullptr;
-  double2* partial2 = nullptr;
+  size_t partials = 0;  // double2 values of one Gram-Schmidt pass
   ubf::GmresState st{};
   int32_t* active[2] = {nullptr, nullptr};  // flags; active[cur] are the current ones
   int cur = 0;
@@ -54,9 +54,12 @@ namespace {
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
 struct GmresLayout {
-  size_t V, W, partial, partial2, H, h1, h2, nrm, cs, sn, g, y, scale, bnorm, res, active0,
+  size_t V, W, partial, H, h1, h2, nrm, cs, sn, g, y, scale, bnorm, res, active0,
       active1, k, iters, total;
 };
+
+// Room of the block partials (double2 values).
+size_t partial_room(int R) { return (size_t)ubf::kDotBlocks * R * (ubf::kMaxRestart + 1); }
 
 GmresLayout gmres_layout(int64_t n, int R, int m) {
   GmresLayout L{};
@@ -69,8 +72,7 @@ GmresLayout gmres_layout(int64_t n, int R, int m) {
   const size_t vec = (size_t)R * n * sizeof(float2);
   L.V = take((size_t)(m + 1) * vec);
   L.W = take(vec);
-  L.partial = take((size_t)ubf::kDotBlocks * R * (ubf::kMaxRestart + 1) * sizeof(double2));
-  L.partial2 = take((size_t)ubf::kDotBlocks * R * (ubf::kMaxRestart + 1) * sizeof(double2));
+  L.partial = take(partial_room(R) * sizeof(double2));
   L.H = take((size_t)R * m * (m + 1) * sizeof(double2));
   L.h1 = take((size_t)R * (m + 1) * sizeof(double2));
   L.h2 = take((size_t)R * (m + 1) * sizeof(double2));
@@ -91,6 +93,15 @@ GmresLayout gmres_layout(int64_t n, int R, int m) {
 }
 
 float2* col(const ubf_gmres* s, int c) { return s->V + (int64_t)c * s->R * s->n; }
+
+// Partials of the second Gram-Schmidt pass of step j: behind the first pass's
+// where both fit, else in the column that the step's last kernel writes (more
+// than 128 blocks then, so n > 262,144 and a column holds 2 MB per right-hand
+// side, against 528 KB of partials at most).
+double2* second_partials(const ubf_gmres* s, int j) {
+  if (2 * s->partials <= partial_room(s->R)) return s->partial + s->partials;
+  return (double2*)(((uintptr_t)col(s, j + 1) + 15) & ~(uintptr_t)15);
+}
 
 #define UBF_TRY(expr, what)                  \
   do {                                       \
@@ -182,7 +193,7 @@ int ubf_gmres_create(ubf_plan* plan, int32_t nrhs, int32_t restart, double sigma
   s->V = (float2*)(ws + L.V);
   s->W = (float2*)(ws + L.W);
   s->partial = (double2*)(ws + L.partial);
-  s->partial2 = (double2*)(ws + L.partial2);
+  s->partials = (size_t)nrhs * (restart + 1) * ubf::gmres_blocks(n);
   ubf::GmresState& st = s->st;
   st.m = restart;
   st.H = (double2*)(ws + L.H);
@@ -259,7 +270,7 @@ int ubf_gmres_step(ubf_gmres* s, void* hip_stream) {
   if (e) return e;
   // the shift, two classical Gram-Schmidt passes against v_0..v_j, v_{j+1}
   UBF_TRY(ubf::launch_gmres_step(s->st, s->V, vs, j, s->W, col(s, j + 1), s->sr, s->si, s->tol,
-                                 n, R, s->partial, s->partial2, s->active[s->cur],
+                                 n, R, s->partial, second_partials(s, j), s->active[s->cur],
                                  s->active[s->cur ^ 1], s->d_status, q),
           "arnoldi");
   s->cur ^= 1;
