@@ -654,8 +654,8 @@ __global__ __launch_bounds__(kBlock, 2) void translate_mfma_kernel(
 // divide evenly, but their products run at two thirds of the rate.) A
 // wavefront per 32 columns with all rows takes chunks of 128 columns, where
 // a wavefront without columns idles: 216-box grid (56 pairs per offset) 38 us
-// against 25 here; the 3,338-box shell (345 per offset) 76 against 83, so the
-// rule (Plan::row_split) lies between.
+// against 25 here; the 3,338-box shell (345 per offset) 76 against 83. The rule
+// is Plan::row_split.
 template <int NU>
 __global__ __launch_bounds__(kBlock, 2) void translate_rows_kernel(
     const float* __restrict__ table, const int32_t* __restrict__ items, int n_items,

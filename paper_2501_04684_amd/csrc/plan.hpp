@@ -226,12 +226,17 @@ struct Plan {
   int64_t n_chunks() const { return (int64_t)(chunks.size() / 4); }
   int64_t n_items() const { return (int64_t)(items.size() / 4); }
   // Work units that the persistent grid of stage 2 divides: items for the
-  // FP32 kernel that splits rows over wavefronts, else chunks. That kernel is
-  // taken where chunks of 128 pairs hold at most 2.5 items of 32 on average
-  // (both give the same bits): a workgroup spends about 10 us on an item and
-  // 21 to 24 on a chunk however full (sphere of 762 boxes, 2.2 items a chunk:
-  // 27 us against 38; 3,338-box shell, 3.7: 83 against 76).
-  bool row_split() const { return !split() && nu == 81 && 2 * n_items() <= 5 * n_chunks(); }
+  // FP32 kernel that splits rows over wavefronts, else chunks (both give the
+  // same bits). A workgroup spends about 10 us on an item of 32 pairs and 21 to
+  // 24 on a chunk of 128 however full, so items win where chunks are part
+  // empty, and where they are few: then the chip takes a second round of
+  // chunks for the sake of some. Tuned, items against chunks: 812 items, 2.2 a
+  // chunk, 24.9 and 35.7 us; 1,350 and 3.2, 35.9 and 36.6; 1,780 and 3.2, 44.5
+  // and 51.9; 2,472 and 3.3, 54.1 and 57.7; 2,964 and 3.7, 66.4 and 65.1; 3,792
+  // and 3.5, 86.6 and 81.0; 7,104 and 3.7, 143 and 124.
+  bool row_split() const {
+    return !split() && nu == 81 && (n_items() <= 2500 || 2 * n_items() <= 5 * n_chunks());
+  }
   int64_t grid_units() const { return row_split() ? n_items() : n_chunks(); }
   int32_t n_groups() const { return (int32_t)wg_ptr.size() - 1; }
   int32_t n_round_groups() const { return (int32_t)wg_round_ptr.size() - 1; }
