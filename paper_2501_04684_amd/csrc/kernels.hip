@@ -1949,7 +1949,8 @@ __global__ __launch_bounds__(kBlock) void disaggregate_wave_kernel(
 // Stage 3 with the identity basis, y_j = E_j: one thread per real value of a
 // row, 32 of the box's rows in flight per thread, added in order (the order
 // of disaggregate_wave_kernel, whose lanes take 16 bytes of a row and 16 rows
-// at a time).
+// at a time). Bound by latency for few boxes, then by the bytes of the rows
+// (5.3 TB/s on 223,000 rows of N_u = 192).
 __global__ __launch_bounds__(384) void sum_rows_kernel(const float* __restrict__ part,
                                                        const int32_t* __restrict__ test_ptr,
                                                        int64_t n_pairs, float2* __restrict__ y,
@@ -2240,11 +2241,16 @@ int launch_disaggregate(const Plan& p, const Plan* rows, const float* part,
       else UBF_WAVE(3, false, 4);
     }
   } else if (from_parts && mode == 0 &&
-             (p.nu == 192 || (p.nu == 81 && few_rows && p.n_box * nrhs <= 2048))) {
-    // a thread per value while the boxes are few (216 boxes of 83 rows: 7.0
-    // against 13.7 us, 762 of 30: 5.4 against 6.5); 16 bytes per lane moves
-    // long runs faster (464,440 box vectors: 2.75 against 3.25 ms). Both add
-    // the rows in order. Rows of 384 values do not fit one wavefront's lanes.
+             (p.nu == 192 || (p.nu == 81 && few_rows && p.n_box * nrhs <= 1200))) {
+    // N_u = 81: a thread per value while the boxes are few (216 boxes of 83
+    // rows: 6.2 us against 12.7; 1,000 of 119: 15.9, 18.8); 16 bytes per lane
+    // moves more of them faster (1,331 of 117: 20.3, 20.0; 1,728 of 129: 27.7,
+    // 24.7; 464,440 vectors: 3.25, 2.75 ms). Both add the rows in order.
+    // N_u = 192: rows of 384 values do not fit one wavefront's lanes; always, so
+    // that a box's sum does not depend on what else is in the plan. Against a
+    // workgroup per box (disaggregate_kernel): 216 boxes of 83 rows 8.7 us and
+    // 11.4, 2,197 of 126 62 and 67, 400 of 340 43.6 and 41.3 (four vectors 182
+    // and 167). 16 bytes per lane: 11.6, 65, 45.6 and 203.
     UBF_LAUNCH(ev, sum_rows_kernel, grid, dim3((2 * p.nu + 63) / 64 * 64), s, part, test_ptr,
                n_rows, (float2*)y, p.n_box, p.nu, p.pstride());
   } else if (from_parts && mode == 0 && small && few_rows) {
