@@ -384,28 +384,41 @@ struct Bounds {
 // The strong boxes of one lattice and right-hand side, and those whose
 // coefficients are not all finite. The latter are left out of the transforms,
 // and the boxes that one of them is far from get NaN, as from its pairs.
+// Without weak ones the boxes that no strong box is far from get zero.
 struct Reach {
   Bounds strong, bad;
+  int weak;  // whether any box is neither strong nor zero (nor bad)
+  // The box (x, y, z), which no strong box is far from, among the at most 27
+  // such boxes.
+  __device__ inline int slot(int x, int y, int z) const {
+    return ((x - strong.hi[0] + 1) * 3 + (y - strong.hi[1] + 1)) * 3 + (z - strong.hi[2] + 1);
+  }
 };
 
 static_assert(sizeof(Reach) == kReachBytes && alignof(Reach) <= 4, "fft_scratch_bytes");
 
-// Per lattice and right-hand side 27 workgroups, one for each box that may be
-// near all strong ones. Each finds the strong boxes (the first one also
-// leaves them for ifft_z); where its box exists and is near all, it sums the
-// site pairs that the convolution stands for, from the boxes that are not
-// zero: a thread per test site and every (512 / sites)-th source site, D
-// evaluated in FP64 for each. Reads 4 bytes per box in the ordinary case,
-// about 1 us of latency; a box that sees 3,338 weak ones would take about
-// 5 ms, as many as all pairs did.
+// Per lattice and right-hand side 27 x `splits` workgroups. Each finds the
+// strong boxes (the first one also leaves them for ifft_z). Where weak ones
+// are left, workgroup (slot, split) takes a box that no strong box is far from
+// and sums, for every kReachParts-th source box, the site pairs that the
+// convolution stands for: a few source boxes at a time, D once per lattice
+// difference of the box pair, then a thread per output coefficient and share
+// of the source sites. ifft_z adds the parts, in order whatever `splits` is.
+// Reads 4 bytes per box in the ordinary case (8 us, latency). With one of
+// 3,338 boxes 10^9 times the others the product takes 0.73 ms (11.7 with D for
+// each site pair and one workgroup per box; pair by pair 6.5), of 314 111 us
+// (1,232; 133).
 constexpr int kReachThreads = 512;
 __global__ __launch_bounds__(kReachThreads) void reach_kernel(
     Source src, const int2* __restrict__ map, const int4* __restrict__ cells,
     const int4* __restrict__ grids, const float* __restrict__ norm, double step, double k,
-    double eta, int nu, Reach* __restrict__ reach, float* __restrict__ part, int64_t part_rhs) {
+    double eta, int nu, Reach* __restrict__ reach, double2* __restrict__ parts, int splits) {
+  constexpr int kSources = 3 * kReachThreads;  // most coefficients of the boxes at a time
   __shared__ float wave_max[kReachThreads / 64];
   __shared__ Reach all;
-  __shared__ double2 sums[kReachThreads][3];
+  __shared__ double2 D[kReachThreads][6];  // [box][difference]; then the threads' sums
+  __shared__ double2 P[kSources];          // [box][coefficient]
+  __shared__ int at_site[kReachThreads];   // (box, source site) q: its part of the place in D
   const int rhs = blockIdx.z, t = threadIdx.x;
   src.select(rhs);
   norm += rhs * src.n_box;
@@ -425,6 +438,7 @@ __global__ __launch_bounds__(kReachThreads) void reach_kernel(
   if (t == 0) {
     all.strong.clear();
     all.bad.clear();
+    all.weak = 0;
   }
   __syncthreads();
 #pragma unroll
@@ -433,6 +447,7 @@ __global__ __launch_bounds__(kReachThreads) void reach_kernel(
   Reach mine;
   mine.strong.clear();
   mine.bad.clear();
+  bool weak = false;
 #pragma unroll 4
   for (int i = t; i < count; i += kReachThreads) {
     const float v = norm[first + i];
@@ -441,7 +456,10 @@ __global__ __launch_bounds__(kReachThreads) void reach_kernel(
       mine.bad.add(c.x, c.y, c.z);
     else if (v > 0.f && v >= bar)
       mine.strong.add(c.x, c.y, c.z);
+    else
+      weak = weak || v > 0.f;
   }
+  if (weak) all.weak = 1;  // every writer writes the same
   auto join = [t](Bounds& to, Bounds& b) {
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
@@ -461,55 +479,67 @@ __global__ __launch_bounds__(kReachThreads) void reach_kernel(
   __syncthreads();
   if (blockIdx.x == 0 && t == 0) reach[rhs * gridDim.y + blockIdx.y] = all;
   const Bounds strong = all.strong;
-  if (strong.empty()) return;
-  const int x = strong.hi[0] - 1 + (int)blockIdx.x / 9, y = strong.hi[1] - 1 + (int)blockIdx.x / 3 % 3,
-            z = strong.hi[2] - 1 + (int)blockIdx.x % 3;
+  if (strong.empty() || !all.weak) return;
+  const int slot = blockIdx.x / splits;
+  const int x = strong.hi[0] - 1 + slot / 9, y = strong.hi[1] - 1 + slot / 3 % 3,
+            z = strong.hi[2] - 1 + slot % 3;
   if (x < 0 || y < 0 || z < 0 || x >= nx || y >= ny || z >= nz || !strong.near(x, y, z) ||
-      !all.bad.near(x, y, z))
+      !all.bad.near(x, y, z) || map[cell0 + ((int64_t)x * ny + y) * nz + z].y < 0)
     return;
-  const int at = map[cell0 + ((int64_t)x * ny + y) * nz + z].y;
-  if (at < 0) return;
-  // site l of the test box, source sites chunk, chunk + chunks, ...
-  const int nd = src.nd, nd2 = nd * nd, nd3 = nd2 * nd;
-  const int chunks = kReachThreads / nd3, l = t % nd3, chunk = t / nd3;
-  const int lx = x * nd + l / nd2, ly = y * nd + l / nd % nd, lz = z * nd + l % nd;
-  double2 E[3];
+  const int nd = src.nd, nd2 = nd * nd, nd3 = nd2 * nd, span = 2 * nd - 1, span3 = span * span * span;
+  const int boxes = kReachThreads / span3;  // source boxes at a time: 512, 18, 4, 1
+  // this thread's difference of a source box, and output coefficient u with
+  // its share of the source sites
+  const int db = t / span3, dd = t - db * span3;
+  const int ox = dd / (span * span) - (nd - 1), oy = dd / span % span - (nd - 1),
+            oz = dd % span - (nd - 1);
+  const int shares = kReachThreads / nu, share = t / nu, u = t - share * nu;
+  const int l = u / 3, al = u - 3 * l;
+  const int e0 = al == 0 ? 0 : 2 + al, e1 = al == 0 ? 3 : (al == 1 ? 1 : 5),
+            e2 = al == 2 ? 2 : 4 + al;  // (al, x), (al, y), (al, z)
+  // difference l - s of the sites: (3 digits of l) - (of s) + nd - 1 each, base span
+  auto digits = [=](int i) { return (i / nd2 * span + i / nd % nd) * span + i % nd; };
+  if (t < boxes * nd3) at_site[t] = t / nd3 * span3 - digits(t % nd3);
+  const int at_l = digits(l) + ((nd - 1) * span + nd - 1) * span + nd - 1;
+  parts += (((int64_t)rhs * gridDim.y + blockIdx.y) * 27 + slot) * kReachParts * nu;
+  for (int part = blockIdx.x - slot * splits; part < kReachParts; part += splits) {
+    double2 E = make_double2(0.0, 0.0);
+    for (int base = part; base < count; base += kReachParts * boxes) {
+      __syncthreads();  // every thread is done with the last boxes
+      for (int e = t; e < boxes * nu; e += kReachThreads) {
+        const int b = e / nu, i = base + kReachParts * b;
+        const bool on = i < count && norm[first + min(i, count - 1)] <= FLT_MAX;
+        P[e] = on ? src.at(first + i, e - b * nu) : make_double2(0.0, 0.0);
+      }
+      if (db < boxes) {
+        const int i = min(base + kReachParts * db, count - 1);
+        const int4 c = cells[first + i];
+        const int dx = nd * (x - c.x) + ox, dy = nd * (y - c.y) + oy, dz = nd * (z - c.z) + oz;
+        double2 v[6];
+        const bool on = norm[first + i] > 0.f && max(abs(dx), max(abs(dy), abs(dz))) >= 2 * nd;
+        if (on) green(dx, dy, dz, step, k, eta, v);
 #pragma unroll
-  for (int al = 0; al < 3; ++al) E[al] = make_double2(0.0, 0.0);
-  if (chunk < chunks)
-    for (int q = chunk; q < count * nd3; q += chunks) {
-      const int i = q / nd3, s = q - i * nd3;
-      if (!(norm[first + i] > 0.f && norm[first + i] <= FLT_MAX)) continue;
-      const int4 c = cells[first + i];
-      const int dx = lx - (c.x * nd + s / nd2), dy = ly - (c.y * nd + s / nd % nd),
-                dz = lz - (c.z * nd + s % nd);
-      if (max(abs(dx), max(abs(dy), abs(dz))) < 2 * nd) continue;
-      double2 D[6];
-      green(dx, dy, dz, step, k, eta, D);
-      const double2 px = src.at(first + i, 3 * s), py = src.at(first + i, 3 * s + 1),
-                    pz = src.at(first + i, 3 * s + 2);
-      E[0] = cfma(D[0], px, cfma(D[3], py, cfma(D[4], pz, E[0])));
-      E[1] = cfma(D[3], px, cfma(D[1], py, cfma(D[5], pz, E[1])));
-      E[2] = cfma(D[4], px, cfma(D[5], py, cfma(D[2], pz, E[2])));
+        for (int e = 0; e < 6; ++e) D[t][e] = on ? v[e] : make_double2(0.0, 0.0);
+      }
+      __syncthreads();
+      if (share < shares)
+        for (int q = share; q < boxes * nd3; q += shares) {
+          const double2* d = D[at_l + at_site[q]];
+          const double2* p = P + 3 * q;
+          E = cfma(d[e0], p[0], cfma(d[e1], p[1], cfma(d[e2], p[2], E)));
+        }
     }
-#pragma unroll
-  for (int al = 0; al < 3; ++al) sums[t][al] = E[al];
-  __syncthreads();
-  for (int left = chunks; left > 1;) {
-    const int half = (left + 1) / 2;
-    if (chunk < left - half)
-#pragma unroll
-      for (int al = 0; al < 3; ++al) sums[t][al] = cadd(sums[t][al], sums[t + half * nd3][al]);
     __syncthreads();
-    left = half;
-  }
-  if (t < nd3) {
-    float* row = part + rhs * part_rhs + (int64_t)at * 2 * src.kh + 3 * t;  // [Er | Ei]
-#pragma unroll
-    for (int al = 0; al < 3; ++al) {
-      row[al] = (float)sums[t][al].x;
-      row[nu + al] = (float)sums[t][al].y;
+    double2* sums = D[0];
+    sums[t] = E;
+    __syncthreads();
+    for (int left = shares; left > 1;) {
+      const int half = (left + 1) / 2;
+      if (share < left - half) sums[t] = cadd(sums[t], sums[t + half * nu]);
+      __syncthreads();
+      left = half;
     }
+    if (t < nu) parts[part * nu + t] = sums[t];
   }
 }
 
@@ -664,14 +694,14 @@ __global__ __launch_bounds__(kMaxFftThreads) void fft_x_kernel(
 }
 
 // Backward z transforms into the boxes' rows: the lines of fft_z_kernel. The
-// rows of boxes that no strong box is far from are reach_kernel's, or zero
-// where no box is strong; those that a box without finite coefficients is far
-// from are NaN.
+// rows of boxes that no strong box is far from are the sum of reach_kernel's
+// parts, or zero without weak boxes; those that a box without finite
+// coefficients is far from are NaN.
 __global__ __launch_bounds__(kMaxFftThreads) void ifft_z_kernel(
     const int2* __restrict__ maps, const FftTask* __restrict__ tasks, int n_tasks,
     const double2* __restrict__ twiddles, const double2* __restrict__ scratch,
     int64_t scratch_rhs, float* __restrict__ part, int nd, int kh, int64_t part_rhs,
-    const Reach* __restrict__ reach, int n_grid) {
+    const Reach* __restrict__ reach, const double2* __restrict__ parts, int n_grid) {
   const FftTask& task = task_of(tasks, n_tasks, 0, blockIdx.x);
   const FftGrid& g = task.g;
   const ZBlock blk(task, nd);
@@ -701,16 +731,20 @@ __global__ __launch_bounds__(kMaxFftThreads) void ifft_z_kernel(
     const int bz = fdiv(i, inv_values), v = i - bz * values;
     const int ln = fdiv(v, inv_line), q = v - ln * 3 * nd;
     const int mz = q / 3, al = q - 3 * mz;
-    const int at = col[bz].y;
+    const int at = col[bz].y, u = mx * row + my0 * 3 * nd + v;
     if (at < 0) continue;
     double2 z = a[((bz * nd + mz) * w + ln) * 3 + al];
     if (!of.bad.near(bx, by, bz)) {
       z.x = z.y = __builtin_nan("");
     } else if (of.strong.near(bx, by, bz)) {
-      if (!of.strong.empty()) continue;
       z = make_double2(0.0, 0.0);
+      if (!of.strong.empty() && of.weak) {
+        const double2* q = parts + (((int64_t)blockIdx.y * n_grid + task.index) * 27 +
+                                    of.slot(bx, by, bz)) * kReachParts * nu + u;
+        for (int k = 0; k < kReachParts; ++k) z = cadd(z, q[k * nu]);
+      }
     }
-    float* e = part + (int64_t)at * 2 * kh + mx * row + my0 * 3 * nd + v;  // [Er | Ei]
+    float* e = part + (int64_t)at * 2 * kh + u;  // [Er | Ei]
     e[0] = (float)z.x;
     e[nu] = (float)z.y;
   }
@@ -837,7 +871,9 @@ int launch_fft(const Plan& p, const float* P, float* part, int nrhs, hipStream_t
   const int64_t part_rhs = p.rest->n_pairs() * p.pstride();
   const int n_grid = (int)p.fft.size();
   double2* lattices = reinterpret_cast<double2*>(p.d_fft);
-  float* norm = reinterpret_cast<float*>(lattices + fft_scratch_len(p, p.max_nrhs));
+  double2* parts = lattices + fft_scratch_len(p, p.max_nrhs);
+  const int64_t parts_rhs = 27LL * n_grid * kReachParts * p.nu;
+  float* norm = reinterpret_cast<float*>(parts + p.max_nrhs * parts_rhs);
   Reach* reach = reinterpret_cast<Reach*>(norm + p.n_box * p.max_nrhs);
   const int2* maps = reinterpret_cast<const int2*>(p.d_fft_map);
   const int4* cells = reinterpret_cast<const int4*>(p.d_fft_cells);
@@ -851,9 +887,11 @@ int launch_fft(const Plan& p, const float* P, float* part, int nrhs, hipStream_t
                    p.n_box};
   launch(norm_kernel, dim3((unsigned)((p.n_box + kThreads / 64 - 1) / (kThreads / 64)), nrhs),
          dim3(kThreads), 0, s, start, nullptr, all, cells, p.nu, norm);
-  launch(reach_kernel, dim3(27, n_grid, nrhs), dim3(kReachThreads), 0, s, nullptr, nullptr, all,
-         maps, cells, cells + p.n_box, (const float*)norm, p.a / p.n_d, p.k, p.eta, p.nu, reach,
-         part, part_rhs);
+  int splits = kReachParts;  // all resident at once (two per compute unit) or one each
+  while (splits > 1 && 27 * splits * n_grid * nrhs > 512) splits /= 2;
+  launch(reach_kernel, dim3(27 * splits, n_grid, nrhs), dim3(kReachThreads), 0, s, nullptr, nullptr,
+         all, maps, cells, cells + p.n_box, (const float*)norm, p.a / p.n_d, p.k, p.eta, p.nu,
+         reach, parts, splits);
   for (const FftGroup& g : p.fft_groups) {
     const FftTask* tasks = p.d_fft_tasks + g.first;
     const int n = g.count, block = (int)fft_block(g, p.max_nrhs);
@@ -876,7 +914,8 @@ int launch_fft(const Plan& p, const float* P, float* part, int nrhs, hipStream_t
       launch(ifft_z_kernel, dim3(zb, nr), dim3(g.threads[0]), g.lds[0], s, nullptr,
              last ? stop : nullptr, maps, tasks, n, tw, (const double2*)lattices, g.len,
              part + r0 * part_rhs, p.n_d, p.kh, part_rhs,
-             (const Reach*)(reach + (int64_t)r0 * n_grid), n_grid);
+             (const Reach*)(reach + (int64_t)r0 * n_grid),
+             (const double2*)(parts + r0 * parts_rhs), n_grid);
     }
   }
   return (int)hipGetLastError();

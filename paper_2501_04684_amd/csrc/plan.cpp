@@ -434,8 +434,9 @@ int64_t fft_scratch_len(const Plan& p, int32_t nrhs) {
 }
 
 size_t fft_scratch_bytes(const Plan& p, int32_t nrhs) {
+  const size_t parts = 27 * kReachParts * (size_t)p.nu * 16;
   return (size_t)fft_scratch_len(p, nrhs) * 16 +
-         (size_t)nrhs * (p.n_box * sizeof(float) + p.fft.size() * kReachBytes);
+         (size_t)nrhs * (p.n_box * sizeof(float) + p.fft.size() * (kReachBytes + parts));
 }
 
 Layout workspace_layout(const Plan& p, int32_t max_nrhs) {
@@ -670,9 +671,10 @@ void build_fft_tasks(Plan& P) {
 bool convolution_pays(const Plan& P, const FftGrid& g, double n_box, double n_pairs,
                       double n_rest, double n_off) {
   const double row = 4.0 * P.pstride();
-  // the lattices have to fit where the rows of the pairs would be (a caller
+  // the scratch has to fit where the rows of the pairs would be (a caller
   // without allocation has room for those)
-  if (16.0 * (g.zlen() + g.yzlen()) + row * (n_rest + 2.0 * n_box) > 0.9 * row * n_pairs)
+  if (16.0 * (g.zlen() + g.yzlen() + 27.0 * kReachParts * P.nu) + row * (n_rest + 2.0 * n_box) >
+      0.9 * row * n_pairs)
     return false;
   // of the pair kernels: per chunk (N_u = 192: item) of pairs of one offset,
   // and with few of them

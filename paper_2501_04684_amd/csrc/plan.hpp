@@ -122,7 +122,8 @@ void operator_fp64(const int32_t w[3], double a, double k, double eta, int n_d,
 constexpr int kMaxFftLength = 768;
 constexpr int kMaxFftStages = 6;
 constexpr int kMaxFftThreads = 1024;  // threads of a transform's workgroup
-constexpr size_t kReachBytes = 48;    // the convolution's record of a lattice's boxes (Reach)
+constexpr size_t kReachBytes = 52;    // the convolution's record of a lattice's boxes (Reach)
+constexpr int kReachParts = 16;       // partial sums of a box that sees no strong one
 // Transform along one axis: length (5-smooth), its radices, and where its
 // twiddle factors exp(-2 pi i k / L) start in Plan::fft_twiddles.
 struct FftAxis {
@@ -376,8 +377,8 @@ constexpr int64_t kFftScratch = (64 << 20) / 16;  // complex values
 // Right-hand sides of a group that pass through the scratch together.
 int64_t fft_block(const FftGroup& g, int32_t nrhs);
 // Scratch of the convolution for nrhs right-hand sides: the lattices of a
-// block of them, then per right-hand side a float for each box and a
-// kReachBytes record for each lattice.
+// block of them, then per right-hand side and lattice the partial sums of 27
+// boxes and a kReachBytes record, and a float for each box.
 int64_t fft_scratch_len(const Plan& p, int32_t nrhs);  // lattices, complex values
 size_t fft_scratch_bytes(const Plan& p, int32_t nrhs);
 
