@@ -32,6 +32,7 @@ namespace {
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef float floatx4u __attribute__((ext_vector_type(4), aligned(4)));
 typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
 
 constexpr int kBlock = 256;
@@ -255,7 +256,10 @@ __device__ inline bool load_item(const int32_t* __restrict__ items, int n_items,
 // row, whose positions are the output rows [Er | Ei]. Bound by the FP32
 // matrix cores and the uneven deal of items to CUs: 816 items of 192 inputs
 // and 50 hidden units are 34 us of products spread evenly, 42 us on a CU that
-// has four, and take 64.5 us (72 with an image of twice the bytes).
+// has four, and take 64.5 us (72 with an image of twice the bytes). The rows
+// leave in 16-byte stores at N_u = 81 too, where Ei is only 4-byte aligned:
+// 1,538 boxes, 5 hidden units, 32.2 us (41.7 with 4-byte stores), 45 units 54.9
+// (59.9).
 template <int NU, int HB>
 __global__ __launch_bounds__(kBlock, 5) void translate_cvfcnn_kernel(
     const float* __restrict__ net, const int32_t* __restrict__ items,
@@ -405,12 +409,12 @@ __global__ __launch_bounds__(kBlock, 5) void translate_cvfcnn_kernel(
           const int u0 = (ob / 2) * 32 + 8 * q + 4 * h;  // first of this lane's 4 rows
           const float* b2 = bias + 2 * HP + (im ? KH : 0) + u0;
           float* e = prow + (im ? NU : 0) + u0;
-          if (NU % 4 == 0) {
+          if (NU % 4 == 0 || u0 + 4 <= NU) {  // Ei of an odd N_u: 4-byte aligned
             if (u0 >= NU) continue;
             floatx4 v;
 #pragma unroll
             for (int jj = 0; jj < 4; ++jj) v[jj] = s * (acc[i][4 * q + jj] + b2[jj]);
-            *reinterpret_cast<floatx4*>(e) = v;
+            *reinterpret_cast<floatx4u*>(e) = v;
           } else {
 #pragma unroll
             for (int jj = 0; jj < 4; ++jj)
