@@ -1743,7 +1743,9 @@ __global__ __launch_bounds__(kBlock, EQ <= 21 ? 3 : 2) void disaggregate_kernel(
 // before the E_j are gathered and each used for the NR right-hand sides; the
 // four wavefronts' sums of a row are added in order through LDS, so a
 // right-hand side gets the same bits whatever NR is. Boxes with more than 64
-// rows repeat this. Bound by the bytes of T_j and the partial rows: 2,168
+// rows repeat this, and with very few boxes gridDim.z workgroups take every
+// gridDim.z-th 64 rows each (50 boxes of up to 120 rows: 5.9 us against 7.8;
+// from 200 boxes on it gains nothing). Bound by the bytes of T_j and the partial rows: 2,168
 // boxes of 20 to 100 rows at N_u = 81 with two right-hand sides take 39.7 us;
 // one thread per output row, walking the 81 columns after E_j was gathered
 // and once per right-hand side, kept a quarter of the lanes busy (73.9 us).
@@ -1762,7 +1764,8 @@ __global__ __launch_bounds__(kBlock, EQ <= 21 ? 4 : 2) void disaggregate_explici
   const int g = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t start = nb_ptr[j];
   const int64_t nb = nb_ptr[j + 1] - start;
-  if (nb <= 0) return;  // uniform
+  const int64_t first = 64 * blockIdx.z, step = 64 * gridDim.z;
+  if (nb <= first) return;  // uniform
   const float2* Tb = T + start * nu;
   float2 v[EQ];
   auto load = [&](int64_t c0) {
@@ -1770,13 +1773,13 @@ __global__ __launch_bounds__(kBlock, EQ <= 21 ? 4 : 2) void disaggregate_explici
 #pragma unroll
     for (int i = 0; i < EQ; ++i) v[i] = col[nb * min(g + 4 * i, nu - 1)];
   };
-  load(0);
+  load(first);
 #pragma unroll
   for (int q = 0; q < NR; ++q)
     if (r0 + q < nrhs)  // uniform
       gather_E<FROM_PARTS, 8>(part, test_ptr, n_pairs, Ein, j, r0 + q, n_box, nu, kh, scratch4,
                               Es4[q]);
-  for (int64_t c0 = 0; c0 < nb; c0 += 64) {
+  for (int64_t c0 = first; c0 < nb; c0 += step) {
 #pragma unroll
     for (int q = 0; q < NR; ++q) {
       const float* Es = reinterpret_cast<const float*>(Es4[q]);
@@ -1792,7 +1795,7 @@ __global__ __launch_bounds__(kBlock, EQ <= 21 ? 4 : 2) void disaggregate_explici
       }
       sums[q][g][c] = make_float2(sr, si);
     }
-    if (c0 + 64 < nb) load(c0 + 64);
+    if (c0 + step < nb) load(c0 + step);
     __syncthreads();
     if (g < NR && r0 + g < nrhs && c0 + c < nb) {
       float2 a = sums[g][0][c];
@@ -2203,9 +2206,17 @@ int launch_disaggregate(const Plan& p, const Plan* rows, const float* part,
     else UBF_WAVE_NT(PQ, IDENT, RB, false);                                                \
   } while (0)
   if (mode == 2) {
-    // T_j is read once for two or four right-hand sides
-    const int nr = nrhs <= 2 ? nrhs : 4;
-    const dim3 tgrid((unsigned)p.n_box, (unsigned)((nrhs + nr - 1) / nr));
+    // T_j is read once for two or four right-hand sides, where that leaves
+    // enough workgroups: a workgroup sums its right-hand sides' rows one after
+    // another. Stage 3 with 1, 2 and 4 of them at a time, N_u = 81, four
+    // vectors: 50 boxes 6.4, 10.3 and 16.8 us, 350 17.4, 16.4 and 19.4, 762
+    // 30.0, 25.7 and 24.7. Small blocks T_j leave more to the launch: N_u = 3,
+    // 762 boxes 12.8, 10.9 and 18.0, 1,382 17.2, 18.6 and 18.5.
+    const int64_t enough = p.nu <= 24 ? 1400 : 700;
+    int nr = nrhs <= 2 ? nrhs : 4;
+    while (nr > 1 && p.n_box * ((nrhs + nr - 1) / nr) < enough) nr /= 2;
+    const int64_t groups = (nrhs + nr - 1) / nr;
+    const dim3 tgrid((unsigned)p.n_box, (unsigned)groups, p.n_box * groups <= 160 ? 2 : 1);
 #define UBF_EXPLICIT(PARTS, NR, EQ)                                                        \
   UBF_LAUNCH(ev, (disaggregate_explicit_kernel<PARTS, NR, EQ>), tgrid, dim3(kBlock), s, part, \
              test_ptr, n_rows, (const float2*)E, p.d_nb_ptr, (const float2*)p.d_T, (float2*)y, \
