@@ -256,7 +256,8 @@ __device__ inline bool load_item(const int32_t* __restrict__ items, int n_items,
 // row, whose positions are the output rows [Er | Ei]. Bound by the FP32
 // matrix cores and the uneven deal of items to CUs: 816 items of 192 inputs
 // and 50 hidden units are 34 us of products spread evenly, 42 us on a CU that
-// has four, and take 64.5 us (72 with an image of twice the bytes). The rows
+// has four, and take 64.5 us with two sets of weights in turn (72 with an image
+// of twice the bytes; 59 and 62 with one set, which the caches hold). The rows
 // leave in 16-byte stores at N_u = 81 too, where Ei is only 4-byte aligned:
 // 1,538 boxes, 5 hidden units, 32.2 us (41.7 with 4-byte stores), 45 units 54.9
 // (59.9).

@@ -49,7 +49,7 @@ def test_boxes_keep_their_own_error(n_d, precision, operators):
     announce("range", n_d, precision, operators)
     n_u, c = 3 * n_d ** 3, (6, 4, 4)
     strong = [
-        ([c], 1e4, 1), ([c], 1e6, 1),
+        ([c], 1e4, 1), ([c], 4e6, 1),
         ([c], 1e9, 1),                               # its neighbours see weak boxes only
         ([c, (7, 4, 4), (7, 5, 5)], 1e9, 1),         # fewer boxes do
         ([(5, 3, 3), c, (7, 5, 5)], 1e9, 1),         # the middle one alone does
